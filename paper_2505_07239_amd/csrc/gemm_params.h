@@ -31,7 +31,7 @@ struct GemmParams {
     // packed digit planes of [E | A']
     unsigned char* xp;
     int mpad;       // rows of xp, multiple of 128
-    int chunk;      // contraction steps per scheduling slice, 1 .. MAX_SEG
+    int chunk;      // contraction units per scheduling slice fixed by the caller, or 0
     int ks_cap;     // contraction steps per half, ceil(kc_cap / 32)
     // general forms of Protocols 2 and 3 (null when unused)
     const int* row_comp;      // SOMM blocks: component number of each listed row

@@ -43,9 +43,10 @@
 //                  to v_mfma_i32_32x32x32_i8; they are never re-written to
 //                  memory.  Weight-side PLANES (COMET_WEIGHT_PLANES: F opened in
 //                  that format, B_i packed offline, see wplanes.hip) go to LDS
-//                  by LDS-DMA like the activation planes: a step then holds
-//                  nothing but matrix instructions and their fragment reads.
-#include "ring_gemm_kernel.h"
+//                  by LDS-DMA, activation planes straight into registers: a step
+//                  then holds nothing but matrix instructions and their fragment
+//                  reads (ring_gemm_planes.h).
+#include "ring_gemm_planes.h"
 
 #include <mutex>
 
@@ -461,22 +462,23 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
         return comet_launch_skinny(ctx, what, p);
     // Tile shape and launch plan first: the packing kernel has to know whether the share kernel
     // will own its tiles (and then initialise Z itself).
-    using T128 = Tile<2, 2, 2, 1>;
-    using T64 = Tile<2, 2, 1, 1>;
-    using T32W = Tile<1, 4, 1, 2>;
-    using T32P = Tile<1, 4, 1, 1>;
-    const int gm = p.w_planes ? W_PLANES : GATHER_NONE;     // what decides the LDS footprint
+    const int narrow_bn = p.w_planes ? 128 : 64, flat_bn = p.w_planes ? 128 : 256;   // columns of the 64- and 32-row tiles
     auto plan = [&](int bm) {
-        if (bm == 128) plan_gemm(ctx, p, T128::BM, T128::BN, T128::wg_per_cu(gm));
-        else if (bm == 64) plan_gemm(ctx, p, T64::BM, T64::BN, T64::wg_per_cu(gm));
-        else if (p.w_planes) plan_gemm(ctx, p, T32P::BM, T32P::BN, T32P::wg_per_cu(gm));
-        else plan_gemm(ctx, p, T32W::BM, T32W::BN, T32W::wg_per_cu(gm));
+        if (p.w_planes) plan_gemm(ctx, p, bm, bm == 128 ? 64 : 128, 1, 2);
+        else if (bm == 128) plan_gemm(ctx, p, 128, 64, Tile<2, 2, 2, 1>::WG_PER_CU, 1);
+        else if (bm == 64) plan_gemm(ctx, p, 64, 64, Tile<2, 2, 1, 1>::WG_PER_CU, 1);
+        else plan_gemm(ctx, p, 32, 256, Tile<1, 4, 1, 2>::WG_PER_CU, 1);
     };
     auto launch = [&](int bm) {
         plan(bm);
+        if (p.w_planes) {
+            if (bm == 128) return launch_planes<2, 2, 4, 2>(ctx, what, p);
+            if (bm == 64) return launch_planes<1, 4, 4, 2>(ctx, what, p);
+            return launch_planes<1, 4, 2, 2>(ctx, what, p);
+        }
         if (bm == 128) return launch_gemm<2, 2, 2, 1>(ctx, what, p);
         if (bm == 64) return launch_gemm<2, 2, 1, 1>(ctx, what, p);
-        return p.w_planes ? launch_gemm<1, 4, 1, 1>(ctx, what, p) : launch_gemm<1, 4, 1, 2>(ctx, what, p);
+        return launch_gemm<1, 4, 1, 2>(ctx, what, p);
     };
     // rows per workgroup tile: 128, 64 or 32
     int bm = 128;
@@ -523,7 +525,7 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
         p.tile_list = list_a;
         if (bm != 128) {
             hipLaunchKernelGGL(tile_list_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, bm,
-                               bm == 64 ? 64 : (p.w_planes ? 128 : 256), list_a, (const int*)nullptr, 0,
+                               bm == 64 ? narrow_bn : flat_bn, list_a, (const int*)nullptr, 0,
                                (int*)nullptr);
             COMET_LAUNCH_CHECK(ctx, what);
             return launch(bm);
@@ -531,8 +533,8 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
         hipLaunchKernelGGL(tile_list_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, 128, 64, list_a,
                            (const int*)nullptr, 0, (int*)nullptr);
         COMET_LAUNCH_CHECK(ctx, what);
-        hipLaunchKernelGGL(tile_list_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, 64, 64, list_b,
-                           (const int*)list_a, 128 * 64, sel);
+        hipLaunchKernelGGL(tile_list_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, 64, narrow_bn,
+                           list_b, (const int*)list_a, 128 * 64, sel);
         COMET_LAUNCH_CHECK(ctx, what);
         p.tile_sel = sel;
         p.tile_sel_want = 0;
@@ -575,8 +577,8 @@ int run_share_group(comet_ctx* ctx, const char* what, GemmParams* ps, int n, voi
     // contraction steps per workgroup.  Below that the single calls shrink their grid instead;
     // above it the fixed cost of a launch is amortised already and one long launch only runs
     // at a lower sustained clock than the same work in pieces.
-    using T = Tile<2, 2, 2, 1>;
-    long grid = (ctx->num_cu / 8) * 8 * T::wg_per_cu(W_PLANES);
+    using T = PlaneTile<2, 2, 4, 2>;
+    long grid = (ctx->num_cu / 8) * 8;
     if (grid < 8) grid = 8;
     if (ctx->gemm_grid > 0) grid = ctx->gemm_grid;
     const long tiles = (long)((p0.m + T::BM - 1) / T::BM) * ((p0.n_cap + T::BN - 1) / T::BN);
@@ -600,9 +602,8 @@ int run_share_group(comet_ctx* ctx, const char* what, GemmParams* ps, int n, voi
         GemmParams& p = grp.p[j];
         p = ps[j];
         place_in_workspace(p, base + (size_t)j * each);
-        // units tile by tile (all of a tile's contraction in a row): a workgroup's share of the
-        // whole sequence then covers few tiles, and whole ones when the grid divides their number
-        p.chunk = 2 * p.ks_cap > 0 ? 2 * p.ks_cap : 1;
+        // (units tile by tile, all of a tile's contraction in a row: a workgroup's share of the whole
+        // sequence then covers few tiles, and whole ones when the grid divides their number)
         p.grid = (int)grid;
         p.tile_bm = T::BM;
         p.tile_bn = T::BN;
@@ -621,7 +622,7 @@ int run_share_group(comet_ctx* ctx, const char* what, GemmParams* ps, int n, voi
                            ctx->stream, grp);
         COMET_LAUNCH_CHECK(ctx, what);
     }
-    return launch_gemm_group<2, 2, 2, 1>(ctx, what, grp);
+    return launch_planes_group<2, 2, 4, 2>(ctx, what, grp);
 }
 
 int check_common(comet_ctx* ctx, const char* what, int party, int64_t m, int bs, int n_blk_cap,

@@ -1,5 +1,5 @@
 // The grouped matrix-core kernel (several products of one shape in one launch), 128 x 64 output
 // tile, weight planes: the variants that share output tiles between workgroups.
-#include "ring_gemm_kernel.h"
+#include "ring_gemm_planes.h"
 
-template comet_gemm::GemmGroupKernel comet_gemm::gemm_group_kernel_for<2, 2, 2, 1, false>(const GemmParams&);
+template comet_gemm::GemmGroupKernel comet_gemm::planes_group_kernel_for<2, 2, 4, 2, false>(const GemmParams&);

@@ -1,5 +1,5 @@
 // The grouped matrix-core kernel (several products of one shape in one launch), 128 x 64 output
-// tile, weight planes: the variants in which every workgroup owns whole output tiles.
-#include "ring_gemm_kernel.h"
+// tile, weight planes: the variants for launches whose workgroups own their tiles.
+#include "ring_gemm_planes.h"
 
-template comet_gemm::GemmGroupKernel comet_gemm::gemm_group_kernel_for<2, 2, 2, 1, true>(const GemmParams&);
+template comet_gemm::GemmGroupKernel comet_gemm::planes_group_kernel_for<2, 2, 4, 2, true>(const GemmParams&);

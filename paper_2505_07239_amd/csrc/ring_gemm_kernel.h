@@ -1,7 +1,9 @@
-// The int8 matrix-core kernel behind the share calls (see ring_gemm.hip for the formulation):
-// tile shapes, the loader that stages both operands, one contraction step, the stream-K kernel
-// and its launcher.  The kernel variants are instantiated in translation units of their own
-// (ring_gemm_tile_*.hip), so that they compile side by side.
+// The int8 matrix-core kernel behind the share calls on weight WORDS (see ring_gemm.hip for the
+// formulation): tile shapes, the loader that stages both operands, one contraction step, the
+// stream-K kernel and its launcher; and what it shares with the kernel on weight planes
+// (ring_gemm_planes.h): the packed activation format, the walk over the work units, the launch plan.
+// The kernel variants are instantiated in translation units of their own (ring_gemm_tile_*.hip),
+// so that they compile side by side.
 #pragma once
 
 #include "common.h"
@@ -28,11 +30,10 @@ constexpr int GATHER_POW2 = 1;   // block gather, bs a power of two >= 8
 constexpr int GATHER_ANY = 2;    // block gather, any bs
 // SOMM with neuron-major weights: B_i and F hold one row of k contiguous words per output column
 constexpr int WEIGHTS_TR = 3;
-// B_i and F arrive as digit planes (see PlaneLoader); with W_PLANES_GATHER the rows of a
+// B_i and F arrive as digit planes (ring_gemm_planes.h); with W_PLANES_GATHER the rows of a
 // full-size B_i are gathered by block (SIMM, bs a multiple of 16)
 constexpr int W_PLANES = 4;
 constexpr int W_PLANES_GATHER = 5;
-constexpr bool is_planes(int gmode) { return gmode == W_PLANES || gmode == W_PLANES_GATHER; }
 
 // Packed layout of [E | A'] in 16-byte units: group (half h, step s, digit t,
 // k-half g) is a run of mpad units, one per row; the 16 bytes of a unit are
@@ -56,31 +57,19 @@ struct Tile {
     static constexpr int WSTAGES = 2;                // written from registers one step ahead
     static constexpr int WBASE = XSTAGES * XBYTES;
     static constexpr int SMEM = XSTAGES * XBYTES + WSTAGES * WBYTES;
-    // four wavefronts, one per SIMD (the plane variants also build with eight -- Tile<4, 2, 1, 1>,
-    // two wavefronts per SIMD on the 128 x 64 tile -- which measured no faster and is not instantiated)
-    static constexpr int THREADS = WAVES_M * WAVES_N * 64;
+    // four wavefronts, one per SIMD
+    static constexpr int THREADS = GT;
+    static_assert(WAVES_M * WAVES_N * 64 == GT, "four wavefronts per workgroup");
     static constexpr int XVEC = XBYTES / 16 / THREADS;    // 16-byte units per thread per stage
-    static constexpr int WVEC = WBYTES / 16 / THREADS;    // same for a weight stage filled by LDS-DMA
-    static constexpr int WTASK = BN * 4 / GT;        // (column, octet) tasks per thread per stage (word loader: 256 threads)
+    static constexpr int WTASK = BN * 4 / GT;        // (column, octet) tasks per thread per stage
     // vector-memory loads a thread issues per step: the LDS-DMA units plus, per weight task,
     // eight 8-byte loads (or four 16-byte loads when the weights are neuron-major)
-    // and one load of a block id with the power-of-two row gather; with weight planes only
-    // LDS-DMA units
+    // and one load of a block id with the power-of-two row gather
     static constexpr int vm_per_step(int gmode) {
-        if (is_planes(gmode)) return XVEC + WVEC;
         return XVEC + (gmode == WEIGHTS_TR ? 4 : 8) * WTASK + (gmode == GATHER_POW2 ? WTASK : 0);
     }
-    // weight planes are written by LDS-DMA two steps ahead, like the activation planes: three
-    // stages, plus the step table of the segment
-    static constexpr int wstages(int gmode) { return is_planes(gmode) ? 3 : WSTAGES; }
-    static constexpr int smem(int gmode) {
-        return XSTAGES * XBYTES + wstages(gmode) * WBYTES + (is_planes(gmode) ? MAX_SEG * 16 : 0);
-    }
     // two workgroups share a compute unit when one needs at most half of its registers and LDS
-    static constexpr int wg_per_cu(int gmode) {
-        return (WM * WN == 1 && THREADS == GT && smem(gmode) <= 80 * 1024) ? 2 : 1;
-    }
-    static_assert(THREADS == GT || THREADS == 2 * GT, "four or eight wavefronts per workgroup");
+    static constexpr int WG_PER_CU = (WM * WN == 1 && SMEM <= 80 * 1024) ? 2 : 1;
     static_assert(XVEC >= 1 && WTASK >= 1, "tile too small for the loader");
     static_assert(vm_per_step(GATHER_POW2) < 63, "outstanding-load counter has 6 bits");
     static_assert(SMEM <= 160 * 1024, "LDS of one CDNA4 compute unit");
@@ -393,152 +382,6 @@ struct Loader {
 };
 
 
-// Loader for weight-side operands that arrive as digit planes (W_PLANES, W_PLANES_GATHER).
-//
-// B_i and F are stored in the unit format of the packed activation planes, transposed: a
-// 16-byte unit holds digit t of the sixteen contraction words k = 32 s + 16 g + 0..15 of ONE
-// column, and units are ordered (step s, chunk of 64 columns, digit t, k-half g, column inside
-// the chunk): the sixteen runs (t, g) of a step and a column chunk are 16 KB of consecutive
-// memory.  A weight stage of a tile is sixteen runs of BN units, each run of 64 columns one
-// wavefront-wide LDS-DMA transfer:
-// the step needs no vector arithmetic, no registers and no LDS store for either operand, only
-// the matrix instructions and their fragment reads.  The planes of F come out of the opening
-// kernel, those of B_i (triple material) are packed offline.
-//
-// Everything a step's transfers depend on -- which half of the stacked contraction it is in,
-// where its activation planes start, which rows of the weight operand it contracts (after the
-// block gather of a full-size B_i, or through the step list of Protocol 3's row sets) -- is put
-// into a small LDS table once per segment (build_table) and read one step ahead, so that a
-// step contains no global index loads and no address arithmetic beyond a few scalar operations.
-template <class T, int KIND, int GMODE, bool LISTED>
-struct PlaneLoader {
-    static constexpr int XV = T::XVEC, WV = T::WVEC;
-    static constexpr int P_END = XV + WV;
-    static constexpr int VM_PER_STEP = XV + WV;
-    static constexpr int XGRP_PER_PASS = T::THREADS / T::BM;
-    static_assert(T::THREADS % T::BM == 0, "tile rows must divide the block");
-    static_assert(T::BN % 64 == 0, "a wavefront's transfer stays inside one run of units");
-
-    unsigned pcb[WV], pcf[WV], pcsel[WV];   // lane's byte offset of its column inside a run: B_i, F, selected
-    const unsigned char* xsrc;              // this thread's first 16-byte unit of step (h = 0, s = 0)
-    size_t xstride;
-    const unsigned char* xs2;               // same for the look-ahead step
-    const char* pbase;                      // planes of the half the look-ahead step is in
-    size_t prow;                            // bytes per contraction step of the whole operand (its column chunks x 16 KB)
-    int n0a, n0b;                           // first row of the two k-halves in the operand's own row numbering
-    v4i pend;                               // table entry of the step after the look-ahead step
-    const int* tab;                         // LDS: per position of the segment {x group, n0a, n0b, half}
-    const int* steps;                       // listed contraction steps of this row tile, or null
-
-    __device__ __forceinline__ void setup(const GemmParams& p, int tm, int tn, int n_eff) {
-#pragma unroll
-        for (int j = 0; j < WV; ++j) {
-            const int u = threadIdx.x + T::THREADS * j;            // unit of the stage: run u / BN, column u % BN
-            int col = tn * T::BN + u % T::BN;
-            col = col < n_eff ? col : n_eff - 1;
-            long bcol = col;
-            if (KIND == KIND_SOMM && p.b_full) {
-                const int blk = col / p.bs;
-                const long st = block_start(p, blk);
-                bcol = (st < 0 ? 0 : st) + (col - blk * p.bs);
-            }
-            // chunk of 64 columns, then the column inside it (columns stay below 2^24: host check)
-            pcb[j] = ((unsigned)bcol >> 6) * 16384u + ((unsigned)bcol & 63u) * 16u;
-            pcf[j] = ((unsigned)col >> 6) * 16384u + ((unsigned)col & 63u) * 16u;
-        }
-        steps = nullptr;
-        const int grp = threadIdx.x / T::BM, within = threadIdx.x % T::BM;
-        xsrc = p.xp + ((size_t)grp * p.mpad + (size_t)tm * T::BM + within) * 16;
-        xstride = (size_t)XGRP_PER_PASS * p.mpad * 16;
-    }
-
-    // Table of the segment that starts at position ks0 of the stacked contraction and has L
-    // steps (all threads; the caller synchronises).  Rows past the end of the contraction keep
-    // a valid address: their activation digits are zero.
-    __device__ __forceinline__ void build_table(const GemmParams& p, int* table, int ks0, int L, int KS, int kc) {
-        for (int q = threadIdx.x; q < L; q += T::THREADS) {
-            const int ks = ks0 + q;
-            const int h = ks >= KS ? 1 : 0;
-            int s = ks - h * KS;
-            if constexpr (LISTED) s = steps[s];
-            int n0[2];
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                const int k0 = s * KSTEP + 16 * g;
-                n0[g] = k0;
-                if (GMODE == W_PLANES_GATHER && h == 0) {
-                    // bs is a multiple of 16 (host check), so a half lies inside one block
-                    const int kb = k0 <= kc - 16 ? k0 : kc - 16;
-                    const int blk = kb / p.bs;
-                    const long st = block_start(p, blk);
-                    n0[g] = (int)(st < 0 ? 0 : st) + (kb - blk * p.bs);
-                }
-            }
-            v4i e = {h * p.ks_cap + s, n0[0], n0[1], h};
-            *reinterpret_cast<v4i*>(table + 4 * q) = e;
-        }
-        tab = table;
-    }
-
-    __device__ __forceinline__ void prime() { pend = *reinterpret_cast<const v4i*>(tab); }
-
-    // Fix the step (position q of the segment) the following transfers work on.  Positions are
-    // visited in order (q, then q + 1 capped at qlimit), which lets the entry of the next one be
-    // read here, a whole step before it is needed.
-    __device__ __forceinline__ void begin(const GemmParams& p, int q, int, int, int qlimit) {
-        const int xg = __builtin_amdgcn_readfirstlane(pend.x);
-        n0a = __builtin_amdgcn_readfirstlane(pend.y);
-        n0b = __builtin_amdgcn_readfirstlane(pend.z);
-        const int h2 = __builtin_amdgcn_readfirstlane(pend.w);
-        const int qn = q + 1 < qlimit ? q + 1 : qlimit;
-        pend = *reinterpret_cast<const v4i*>(tab + 4 * qn);
-        xs2 = xsrc + (size_t)xg * 16 * p.mpad * 16;
-        pbase = reinterpret_cast<const char*>(h2 ? p.F : p.B);
-        prow = (size_t)(((h2 ? p.ldf : p.ldb) + 63) >> 6) * 16384u;
-#pragma unroll
-        for (int j = 0; j < WV; ++j) pcsel[j] = pcb[j] + ((pcf[j] - pcb[j]) & (0u - (unsigned)h2));
-    }
-
-    template <int J>
-    __device__ __forceinline__ void xdma_piece(unsigned char* xstage) {
-        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-        const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)xstage;
-        const unsigned lds = __builtin_amdgcn_readfirstlane(lds0 + (wave * 64 + T::THREADS * J) * 16);
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                     :
-                     : "s"(lds), "v"(xs2 + J * xstride)
-                     : "memory", "m0");
-    }
-
-    // run (digit t, k-half g) of the weight stage: scalar start of the run in the operand, the
-    // lane's column offset, one transfer per wavefront
-    template <int J>
-    __device__ __forceinline__ void wdma_piece(unsigned char* wstage) {
-        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-        const int run = __builtin_amdgcn_readfirstlane((int)((threadIdx.x + T::THREADS * J) / T::BN));   // t * 2 + g
-        const int r0 = (run & 1) ? n0b : n0a;
-        const char* sb = pbase + (size_t)(r0 >> 5) * prow + (size_t)((run & ~1) | ((r0 >> 4) & 1)) * 1024u;
-        const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)wstage;
-        const unsigned lds = __builtin_amdgcn_readfirstlane(lds0 + (wave * 64 + T::THREADS * J) * 16);
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                     :
-                     : "s"(lds), "v"(pcsel[J]), "s"(sb)
-                     : "memory", "m0");
-    }
-
-    template <int P, bool SPLIT>
-    __device__ __forceinline__ void piece(const GemmParams&, int, unsigned char* xstage, unsigned char* wstage) {
-        if constexpr (P < XV) xdma_piece<P>(xstage);
-        else if constexpr (P < P_END) wdma_piece<P - XV>(wstage);
-    }
-
-    template <int P0, bool SPLIT, int... Ps>
-    __device__ __forceinline__ void pieces(std::integer_sequence<int, Ps...>, const GemmParams& p,
-                                           int kc, unsigned char* xstage, unsigned char* wstage) {
-        (piece<P0 + Ps, SPLIT>(p, kc, xstage, wstage), ...);
-    }
-};
-
 __device__ __forceinline__ v4i lds_frag(const unsigned char* p) {
     return *reinterpret_cast<const v4i*>(p);
 }
@@ -660,180 +503,181 @@ __device__ __forceinline__ void gemm_step(const GemmParams& p, L& ld,
                                  xs, ws, ws_next, xs_next2, a_off, b_off, ks_next2, ks_limit, KS, kc);
 }
 
-// ---------------------------------------------------------------------------
-// step with the barrier in its middle (weight planes)
-// ---------------------------------------------------------------------------
-// With both operands arriving by LDS-DMA a step has nothing left to hide in the shadow of its
-// matrix instructions, and what then costs time is the step boundary: a barrier, and behind it a
-// full LDS round trip before the first matrix instruction has its fragments.  So here
-//   * the digit pairs are walked with the activation digit DESCENDING (7, 6, .., 0; weight digit
-//     ascending inside), which makes every fragment that the first instructions of a step need
-//     dead in the last instructions of the step before;
-//   * fragment reads run READ_LEAD instructions ahead straight across the step boundary: the last
-//     instructions of step i already read, from the stage of step i + 1, what the first ones of
-//     step i + 1 consume;
-//   * the barrier sits in the MIDDLE of the step.  Barrier b_i publishes the stage of step i + 1
-//     (requested after b_(i-1), a whole step earlier), so reads of that stage may start right
-//     after it, and it retires the stage of step i - 1 (every wavefront's reads of it are older
-//     than its b_i), which the transfers for step i + 2, issued behind b_i, then overwrite.
-// No instruction after a barrier waits for a read that was issued after that barrier.
-template <int WM, int WN>
-struct SlotMapDesc {
-    static constexpr int per_group(int g) { return (g + 1) * WM * WN; }      // group g holds digit t = 7 - g
-    static constexpr int group_of(int m) {
-        int g = 0;
-        while (m >= per_group(g)) { m -= per_group(g); ++g; }
-        return g;
-    }
-    static constexpr int in_group(int m) {
-        int g = 0;
-        while (m >= per_group(g)) { m -= per_group(g); ++g; }
-        return m;
-    }
-    static constexpr int t_of(int m) { return 7 - group_of(m); }
-    static constexpr int u_of(int m) { return in_group(m) / (WM * WN); }
-    static constexpr int i_of(int m) { return (in_group(m) / WN) % WM; }
-    static constexpr int j_of(int m) { return in_group(m) % WN; }
-};
-
-template <int WM, int WN>
-struct ReadMapMid {
-    using SM = SlotMapDesc<WM, WN>;
-    static constexpr int NR = 8 * (WM + WN);
-    static constexpr int NM = 36 * WM * WN;
-    static constexpr int READ_LEAD = 8;
-    static constexpr int MID = NM / 2;
-    static_assert(READ_LEAD < NM - MID, "reads of the next stage start behind the barrier");
-    static constexpr bool is_a(int r) { return r < 8 * WM; }
-    static constexpr int need(int r) {
-        for (int m = 0; m < NM; ++m) {
-            if (is_a(r)) {
-                if (SM::t_of(m) == r / WM && SM::i_of(m) == r % WM) return m;
-            } else {
-                if (SM::u_of(m) == (r - 8 * WM) / WN && SM::j_of(m) == (r - 8 * WM) % WN) return m;
-            }
-        }
-        return NM;
-    }
-    // instruction of the SAME step after which read R is issued, or, when negative, NM + slot is
-    // the instruction of the step BEFORE after which it is issued
-    static constexpr int slot(int r) { return need(r) - READ_LEAD; }
-};
-
-template <class T, int WM, int WN, int R>
-__device__ __forceinline__ void read_frag_mid(v4i (&a)[8][WM], v4i (&bf)[WN][8], const unsigned char* xs,
-                                              const unsigned char* ws, int a_off, int b_off) {
-    using RM = ReadMapMid<WM, WN>;
-    if constexpr (RM::is_a(R)) {
-        constexpr int t = R / WM, ii = R % WM;
-        a[t][ii] = lds_frag(xs + a_off + (t * 2 * T::BM + ii * 32) * 16);
-    } else {
-        constexpr int uu = (R - 8 * WM) / WN, j = (R - 8 * WM) % WN;
-        bf[j][uu] = lds_frag(ws + b_off + (uu * 2 * T::BN + j * 32) * 16);
-    }
-}
-
-// the reads a step's first instructions need, issued before the first step of a segment
-template <class T, int WM, int WN>
-__device__ __forceinline__ void prefetch_first_frags(v4i (&a)[8][WM], v4i (&bf)[WN][8], const unsigned char* xs,
-                                                     const unsigned char* ws, int a_off, int b_off) {
-    using RM = ReadMapMid<WM, WN>;
-    [&]<int... Rs>(std::integer_sequence<int, Rs...>) {
-        ([&] { if constexpr (RM::slot(Rs) < 0) read_frag_mid<T, WM, WN, Rs>(a, bf, xs, ws, a_off, b_off); }(), ...);
-    }(std::make_integer_sequence<int, RM::NR>{});
-}
-
-template <class T, class L, int WM, int WN, int... Ms>
-__device__ __forceinline__ void gemm_step_mid_impl(std::integer_sequence<int, Ms...>, const GemmParams& p, L& ld,
-                                                   v16i (&acc)[WM][WN][8], v4i (&a)[8][WM], v4i (&bf)[WN][8],
-                                                   const unsigned char* xs, const unsigned char* ws,
-                                                   const unsigned char* xs_next, const unsigned char* ws_next,
-                                                   unsigned char* xs_fill, unsigned char* ws_fill, int a_off,
-                                                   int b_off, int q_fill, int q_limit, int KS, int kc) {
-    using SM = SlotMapDesc<WM, WN>;
-    using RM = ReadMapMid<WM, WN>;
-    constexpr int NM = RM::NM, MID = RM::MID;
-    (
-        [&] {
-            constexpr int M = Ms;
-            if constexpr (M == MID) {
-                // b_i: this wavefront's transfers for the next step have landed and its reads of the
-                // previous step's stage are done; behind the barrier that holds for all wavefronts
-                wait_and_barrier<0>();
-                ld.begin(p, q_fill, KS, kc, q_limit);
-            }
-            constexpr int t = SM::t_of(M), uu = SM::u_of(M), ii = SM::i_of(M), j = SM::j_of(M);
-            acc[ii][j][t + uu] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[t][ii], bf[j][uu],
-                                                                        acc[ii][j][t + uu], 0, 0, 0);
-            // reads for this step (its own stage) and, near the end, for the first instructions of
-            // the next step (the next stage, published by this step's barrier)
-            [&]<int... Rs>(std::integer_sequence<int, Rs...>) {
-                ([&] {
-                    if constexpr (RM::slot(Rs) == M) read_frag_mid<T, WM, WN, Rs>(a, bf, xs, ws, a_off, b_off);
-                    if constexpr (RM::slot(Rs) + NM == M)
-                        read_frag_mid<T, WM, WN, Rs>(a, bf, xs_next, ws_next, a_off, b_off);
-                }(), ...);
-            }(std::make_integer_sequence<int, RM::NR>{});
-            if constexpr (M >= MID) {
-                constexpr int p0 = (int)((long)(M - MID) * L::P_END / (NM - MID)),
-                              p1 = (int)((long)(M - MID + 1) * L::P_END / (NM - MID));
-                ld.template pieces<p0, true>(std::make_integer_sequence<int, p1 - p0>{}, p, kc, xs_fill, ws_fill);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }(),
-        ...);
-}
-
-template <class T, class L, int WM, int WN>
-__device__ __forceinline__ void gemm_step_mid(const GemmParams& p, L& ld, v16i (&acc)[WM][WN][8],
-                                              v4i (&a)[8][WM], v4i (&bf)[WN][8], const unsigned char* xs,
-                                              const unsigned char* ws, const unsigned char* xs_next,
-                                              const unsigned char* ws_next, unsigned char* xs_fill,
-                                              unsigned char* ws_fill, int a_off, int b_off, int q_fill,
-                                              int q_limit, int KS, int kc) {
-    gemm_step_mid_impl<T, L, WM, WN>(std::make_integer_sequence<int, 36 * WM * WN>{}, p, ld, acc, a, bf, xs, ws,
-                                     xs_next, ws_next, xs_fill, ws_fill, a_off, b_off, q_fill, q_limit, KS, kc);
-}
-
-// What a launch computes, from the device-resident counts.
+// What a launch computes, from the device-resident counts.  PER: contraction steps (of 32 words) in
+// a work unit: one with weight words, two with weight planes (ring_gemm_planes.h).
 struct Geometry {
     int n_eff, kc, KS, KT, m_eff, tiles_m, tiles_n, tiles;
-    long units;     // work units: (tile, contraction step) pairs
+    long units;     // (tile, contraction unit) pairs; a tile has KT = 2 KS / PER of them
 };
 
-template <class T, int KIND, bool LISTED>
+template <int BM, int BN, int KIND, bool LISTED, int PER>
 __device__ __forceinline__ Geometry gemm_geometry(const GemmParams& p) {
     Geometry q;
     const int nblk = n_blocks(p);
     q.n_eff = KIND == KIND_SOMM ? nblk * p.bs : p.n_cap;
     q.kc = KIND == KIND_SOMM ? p.kc_cap : nblk * p.bs;
     q.KS = (q.kc + KSTEP - 1) / KSTEP;
-    q.KT = 2 * q.KS;
+    q.KT = 2 * q.KS / PER;
     q.m_eff = n_rows(p);
-    q.tiles_m = (q.m_eff + T::BM - 1) / T::BM;
-    q.tiles_n = (q.n_eff + T::BN - 1) / T::BN;
+    q.tiles_m = (q.m_eff + BM - 1) / BM;
+    q.tiles_n = (q.n_eff + BN - 1) / BN;
     // with result blocks only the listed tiles are computed
     q.tiles = p.row_comp ? p.tile_list[0] : q.tiles_m * q.tiles_n;
     // with per-token row sets only the listed steps of each row tile are computed
-    q.units = LISTED ? (long)q.tiles_n * 2 * p.step_off[q.tiles_m] : (long)q.tiles * q.KT;
+    q.units = LISTED ? (long)q.tiles_n * (2 / PER) * p.step_off[q.tiles_m] : (long)q.tiles * q.KT;
     return q;
 }
 
-// The work units [u, u_end) of one product: segment by segment (a run of contraction steps of one
-// output tile), the main loop and the write-out of the partial sum.  G: workgroups of the launch.
+// A run of contraction units of one output tile, what a workgroup computes between two write-outs.
+struct Segment {
+    int tm, tn;             // output tile
+    int k0, L;              // units [k0, k0 + L)
+    int KS;                 // contraction steps of one half of the tile's stacked contraction
+    const int* steps;       // listed contraction steps of this row tile, or null (all steps)
+};
+
+// What a workgroup computes of one product, segment by segment, in one of two ways.
+//
+// One slice of one tile (the default when there are at least as many workgroups as tiles): the
+// contraction of every tile is cut into S = G / tiles slices, a workgroup takes one of them, so it pays
+// for filling its pipeline and for writing out its partial sum once.  (An even split of all units
+// makes most workgroups straddle two slices: a call with 64 x 4096 x 1664 on weight planes, 6.5
+// units each, took 73 us against 56, and one with 20 rows on weight words 56 against 43.)
+//
+// An even share [u, u_end) of the units: when the slices would leave the longest workgroup more than
+// SPLIT_COST units above an even share, with more tiles than workgroups, and where the caller
+// fixes the slice length (p.chunk).  Units are ordered chunk-major: all tiles for contraction
+// units [0, CH), then all tiles for [CH, 2 CH), ...
+//
+// Either way, workgroups that run side by side sweep the same slice of the contraction at the same
+// time (the activation planes of that slice stay hot in L2) and each XCD ends up with whole
+// slices, so a weight word is fetched from HBM by one XCD only.
+template <bool LISTED, int PER>
+struct UnitWalk {
+    static constexpr int SPLIT_COST = 6 / PER;      // units: what a second segment costs a workgroup
+    const GemmParams& p;
+    const Geometry& q;
+    long u_begin, u_end, u;
+    const int team_tm, tiles;
+    int CH, n_chunks;
+    int slice_tile;                                 // tile of this workgroup's slice, or -1: an even share
+
+    // workgroup b of G; own: every workgroup gets whole tiles
+    __device__ __forceinline__ UnitWalk(const GemmParams& p_, const Geometry& q_, int b, int G, bool own)
+        : p(p_), q(q_), team_tm(-1), tiles(q_.tiles) {
+        slice_tile = -1;
+        if (!LISTED && !own && p.chunk == 0 && tiles <= G) {
+            const int S = G / tiles < q.KT ? G / tiles : q.KT;
+            if ((q.KT + S - 1) / S <= q.units / G + SPLIT_COST) {
+                slice_tile = b % tiles;
+                const int c = b / tiles;
+                u_begin = u = c < S ? (long)q.KT * c / S : 0;
+                u_end = c < S ? (long)q.KT * (c + 1) / S : 0;
+                return;
+            }
+        }
+        u_begin = u = q.units * b / G;
+        u_end = q.units * (b + 1) / G;
+        CH = p.chunk;
+        if (own) CH = q.KT;                    // units tile by tile, all of a tile's contraction in a row
+        else if (CH == 0) {
+            int slices = (G + tiles / 2) / tiles;      // as many slices as workgroups per tile
+            if (slices < 1) slices = 1;
+            CH = (q.KT + slices - 1) / slices;
+            if (CH > MAX_SEG / PER) CH = MAX_SEG / PER;
+            if (CH < 1) CH = 1;
+        }
+        n_chunks = (q.KT + CH - 1) / CH;
+    }
+
+    // The units [u0, u1), tile by tile.  team >= 0: the workgroup computes row tile team only and the
+    // units are (column tile, contraction unit) pairs; the workgroups of a team walk the same
+    // units side by side.
+    __device__ __forceinline__ UnitWalk(const GemmParams& p_, const Geometry& q_, long u0, long u1, int team)
+        : p(p_), q(q_), u_begin(u0), u_end(u1), u(u0), team_tm(team), tiles(team >= 0 ? q_.tiles_n : q_.tiles),
+          CH(q_.KT), n_chunks(1), slice_tile(-1) {}
+
+    __device__ __forceinline__ bool next(Segment& g) {
+        if (u >= u_end) return false;
+        long len;
+        g.KS = q.KS;
+        g.steps = nullptr;
+        if constexpr (LISTED) {
+            // units are ordered row tile by row tile, inside a row tile column tile by column
+            // tile, inside a tile along its listed steps (E B_i half, then A' F half)
+            constexpr int F = 2 / PER;         // units per listed step
+            int lo = 0, hi = q.tiles_m;
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if ((long)q.tiles_n * F * p.step_off[mid] <= u) lo = mid; else hi = mid;
+            }
+            g.tm = lo;
+            g.KS = p.step_cnt[lo];
+            const long rem = u - (long)q.tiles_n * F * p.step_off[lo];
+            g.tn = (int)(rem / (F * g.KS));
+            g.k0 = (int)(rem - (long)g.tn * F * g.KS);
+            len = F * g.KS - g.k0;
+            g.steps = p.step_list + (size_t)lo * p.ks_cap;
+        } else {
+            int tile_pos;
+            if (slice_tile >= 0) {
+                tile_pos = slice_tile;
+                g.k0 = (int)u;
+                len = u_end - u;
+            } else {
+                const long full = (long)tiles * CH;
+                int c = (int)(u / full);
+                if (c > n_chunks - 1) c = n_chunks - 1;
+                const long rem = u - (long)c * full;
+                const int clen = (c == n_chunks - 1) ? q.KT - c * CH : CH;
+                tile_pos = (int)(rem / clen);
+                g.k0 = c * CH + (int)(rem - (long)tile_pos * clen);
+                len = c * CH + clen - g.k0;
+            }
+            const int tile = p.row_comp ? p.tile_list[1 + tile_pos] : tile_pos;
+            g.tm = tile % q.tiles_m;
+            g.tn = tile / q.tiles_m;
+            if (team_tm >= 0) { g.tm = team_tm; g.tn = tile; }
+        }
+        if (len > MAX_SEG / PER) len = MAX_SEG / PER;      // (an owned tile's contraction may be longer than a segment)
+        if (len > u_end - u) len = u_end - u;
+        g.L = (int)len;
+        if (!LISTED && p.k_rotate) {
+            // Units tile by tile, a tile cut into parts by the workgroup ranges: the parts take their
+            // contraction units in reverse order of their positions (the part [c, d) of a tile gets
+            // the units [KT - d, KT - c); any order gives the same sum).  A workgroup that starts
+            // in the middle of a tile thus begins at unit 0 like one that starts on a tile, and
+            // all workgroups sweep the contraction in two phases only, KT - share apart: the
+            // activation planes of a phase are shared through L2 instead of being fetched per tile.
+            const long tile_u0 = u - g.k0;
+            const long c_lo = u_begin - tile_u0, c_hi = u_end - tile_u0;
+            g.k0 += q.KT - (c_lo > 0 ? (int)c_lo : 0) - (c_hi < q.KT ? (int)c_hi : q.KT);
+        }
+        u += len;
+        return true;
+    }
+};
+
+// sum_s sext64(S_s) << 8s: the four low planes as 32 x 32 -> 64 bit signed multiply-adds, the four
+// high planes only reach the upper word
+__device__ __forceinline__ u64 recombine(int s0, int s1, int s2, int s3, int s4, int s5, int s6, int s7) {
+    long long lo = (long long)s0;
+    lo += (long long)s1 * (1 << 8);
+    lo += (long long)s2 * (1 << 16);
+    lo += (long long)s3 * (1 << 24);
+    const u32 hi = (u32)s4 + ((u32)s5 << 8) + ((u32)s6 << 16) + ((u32)s7 << 24);
+    return (u64)lo + ((u64)hi << 32);
+}
+
+// One workgroup's share of a product: segment by segment, the main loop and the write-out of the
+// partial sum.
 template <int WAVES_M, int WAVES_N, int WM, int WN, int KIND, int GMODE, bool LISTED>
-__device__ __forceinline__ void gemm_sweep(const GemmParams& p, const Geometry& q, long u, const long u_end,
-                                           const int G, const bool own, unsigned char* xs0, unsigned char* xs1,
-                                           unsigned char* xs2, unsigned char* wsm, int* steptab,
-                                           const int team_tm = -1) {
+__device__ __forceinline__ void gemm_sweep(const GemmParams& p, const Geometry& q, UnitWalk<LISTED, 1>& walk,
+                                           const bool own, unsigned char* xs0, unsigned char* xs1,
+                                           unsigned char* xs2, unsigned char* wsm) {
     using T = Tile<WAVES_M, WAVES_N, WM, WN>;
-    constexpr bool PLANES = is_planes(GMODE);
-    using LD = std::conditional_t<PLANES, PlaneLoader<T, KIND, GMODE, LISTED>, Loader<T, KIND, GMODE, LISTED>>;
-    constexpr bool listed = LISTED;
-    const int n_eff = q.n_eff, kc = q.kc, KS = q.KS, KT = q.KT, m_eff = q.m_eff;
-    // team_tm >= 0: this workgroup computes row tile team_tm only and the units are (column tile,
-    // contraction step) pairs; the workgroups of a team walk the same units side by side
-    const int tiles_m = q.tiles_m, tiles_n = q.tiles_n, tiles = team_tm >= 0 ? q.tiles_n : q.tiles;
+    using LD = Loader<T, KIND, GMODE, LISTED>;
+    const int n_eff = q.n_eff, kc = q.kc, m_eff = q.m_eff;
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave % WAVES_M, wn = wave / WAVES_M;
@@ -843,76 +687,11 @@ __device__ __forceinline__ void gemm_sweep(const GemmParams& p, const Geometry& 
     const int b_off = (g * T::BN + wn * WN * 32 + r) * 16;
 
     LD ld;
-    const long u_begin = u;
-
-    // Work units are ordered chunk-major: all tiles for contraction steps
-    // [0, CH), then all tiles for [CH, 2 CH), ...  Workgroups that run side by
-    // side therefore sweep the same slice of the contraction at the same time
-    // (the activation planes of that slice stay hot in L2) and each XCD ends up
-    // with whole slices, so a weight word is fetched from HBM by one XCD only.
-    int CH = p.chunk;
-    // every workgroup owns whole tiles: units tile by tile, all of a tile's contraction in a row
-    if (own) CH = KT;
-    if (p.row_comp) {
-        // the number of listed tiles is only known here: as many slices as workgroups per tile
-        int slices = (int)((G + tiles / 2) / tiles);
-        if (slices < 1) slices = 1;
-        CH = (KT + slices - 1) / slices;
-        if (CH > MAX_SEG) CH = MAX_SEG;
-        if (CH < 1) CH = 1;
-    }
-    const long full_chunk_units = (long)tiles * CH;
-    const int n_chunks = (KT + CH - 1) / CH;
-    while (u < u_end) {
-        int tm, tn, ks0, KSt = KS;
-        long len;
-        const int* listed_steps = nullptr;
-        if (listed) {
-            // units are ordered row tile by row tile, inside a row tile column tile by column
-            // tile, inside a tile along its listed steps (E B_i half, then A' F half)
-            int lo = 0, hi = tiles_m;
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if ((long)tiles_n * 2 * p.step_off[mid] <= u) lo = mid; else hi = mid;
-            }
-            tm = lo;
-            KSt = p.step_cnt[tm];
-            const long rem = u - (long)tiles_n * 2 * p.step_off[tm];
-            tn = (int)(rem / (2 * KSt));
-            ks0 = (int)(rem - (long)tn * 2 * KSt);
-            len = 2 * KSt - ks0;
-            if (len > MAX_SEG) len = MAX_SEG;
-            listed_steps = p.step_list + (size_t)tm * p.ks_cap;
-        } else {
-            int c = (int)(u / full_chunk_units);
-            if (c > n_chunks - 1) c = n_chunks - 1;
-            const long rem = u - (long)c * full_chunk_units;
-            const int clen = (c == n_chunks - 1) ? KT - c * CH : CH;
-            const int tile_pos = (int)(rem / clen);
-            ks0 = c * CH + (int)(rem - (long)tile_pos * clen);
-            const int tile = p.row_comp ? p.tile_list[1 + tile_pos] : tile_pos;
-            len = c * CH + clen - ks0;
-            if (len > MAX_SEG) len = MAX_SEG;      // (an owned tile's contraction may be longer than a segment)
-            tm = tile % tiles_m;
-            tn = tile / tiles_m;
-            if (team_tm >= 0) { tm = team_tm; tn = tile; }
-        }
-        if (len > u_end - u) len = u_end - u;
-        const int L = (int)len;
-        if (!listed && p.k_rotate) {
-            // Units tile by tile, a tile cut into parts by the workgroup ranges: the parts take their
-            // contraction steps in reverse order of their positions (the part [c, d) of a tile gets
-            // the steps [KT - d, KT - c); any order gives the same sum).  A workgroup that starts
-            // in the middle of a tile thus begins at step 0 like one that starts on a tile, and
-            // all workgroups sweep the contraction in two phases only, KT - share apart: the
-            // activation planes of a phase are shared through L2 instead of being fetched per tile.
-            const long tile_u0 = u - ks0;
-            const long c_lo = u_begin - tile_u0, c_hi = u_end - tile_u0;
-            ks0 += KT - (c_lo > 0 ? (int)c_lo : 0) - (c_hi < KT ? (int)c_hi : KT);
-        }
-
+    Segment sg;
+    while (walk.next(sg)) {
+        const int tm = sg.tm, tn = sg.tn, ks0 = sg.k0, L = sg.L, KSt = sg.KS;
         ld.setup(p, tm, tn, n_eff);
-        ld.steps = listed_steps;
+        ld.steps = sg.steps;
         v16i acc[WM][WN][8];
 #pragma unroll
         for (int i = 0; i < WM; ++i)
@@ -925,75 +704,31 @@ __device__ __forceinline__ void gemm_sweep(const GemmParams& p, const Geometry& 
 
         // prologue: step ks0 staged, step ks0+1 in flight
         const int ks_last = ks0 + L - 1;
-        if constexpr (PLANES) {
-            // the segment's step table first (the stages and the table of the previous segment
-            // are no longer read: every wavefront has passed that segment's last barrier)
-            ld.build_table(p, steptab, ks0, L, KSt, kc);
-            __syncthreads();
-            ld.prime();
-            ld.begin(p, 0, KSt, kc, L - 1);
-            ld.template pieces<0, true>(std::make_integer_sequence<int, LD::P_END>{}, p, kc, xs0, wsm);
-            ld.begin(p, 1 < L - 1 ? 1 : L - 1, KSt, kc, L - 1);
-            ld.template pieces<0, true>(std::make_integer_sequence<int, LD::P_END>{}, p, kc, xs1, wsm + T::WBYTES);
-            wait_and_barrier<0>();
-            // Positions of the segment instead of contraction steps; stage i % 3 of both operands.
-            // Step i reads stage i % 3, prefetches from stage (i + 1) % 3 and, behind its barrier,
-            // requests position i + 2 into stage (i + 2) % 3.
-            v4i fa[8][WM], fb[WN][8];
-            prefetch_first_frags<T, WM, WN>(fa, fb, xs0, wsm, a_off, b_off);
-            for (int i = 0; i < L; i += 3) {
-                const int q2 = i + 2;
-                gemm_step_mid<T, LD, WM, WN>(p, ld, acc, fa, fb, xs0, wsm, xs1, wsm + T::WBYTES, xs2,
-                                             wsm + 2 * T::WBYTES, a_off, b_off, q2 < L - 1 ? q2 : L - 1, L - 1,
-                                             KSt, kc);
-                if (i + 1 < L)
-                    gemm_step_mid<T, LD, WM, WN>(p, ld, acc, fa, fb, xs1, wsm + T::WBYTES, xs2,
-                                                 wsm + 2 * T::WBYTES, xs0, wsm, a_off, b_off,
-                                                 q2 + 1 < L - 1 ? q2 + 1 : L - 1, L - 1, KSt, kc);
-                if (i + 2 < L)
-                    gemm_step_mid<T, LD, WM, WN>(p, ld, acc, fa, fb, xs2, wsm + 2 * T::WBYTES, xs0, wsm, xs1,
-                                                 wsm + T::WBYTES, a_off, b_off, q2 + 2 < L - 1 ? q2 + 2 : L - 1,
-                                                 L - 1, KSt, kc);
-            }
-        } else {
-            ld.prime(p, ks0, KSt, kc);
-            ld.begin(p, ks0, KSt, kc, ks_last);
-            ld.template pieces<LD::P_DMA, false>(std::make_integer_sequence<int, LD::P_END - LD::P_DMA>{}, p, kc, xs0, wsm);
-            ld.begin(p, ks0 + 1 < ks_last ? ks0 + 1 : ks_last, KSt, kc, ks_last);
-            ld.template pieces<LD::P_DMA, true>(std::make_integer_sequence<int, LD::P_END - LD::P_DMA>{}, p, kc, xs1, wsm);
-            wait_and_barrier<0>();
+        ld.prime(p, ks0, KSt, kc);
+        ld.begin(p, ks0, KSt, kc, ks_last);
+        ld.template pieces<LD::P_DMA, false>(std::make_integer_sequence<int, LD::P_END - LD::P_DMA>{}, p, kc, xs0, wsm);
+        ld.begin(p, ks0 + 1 < ks_last ? ks0 + 1 : ks_last, KSt, kc, ks_last);
+        ld.template pieces<LD::P_DMA, true>(std::make_integer_sequence<int, LD::P_END - LD::P_DMA>{}, p, kc, xs1, wsm);
+        wait_and_barrier<0>();
 
-            for (int i = 0; i < L; i += 3) {
-                const int k2 = ks0 + i + 2;
-                gemm_step<T, LD, WM, WN>(p, ld, acc, xs0, wsm + (i & 1) * T::WBYTES,
-                                         wsm + ((i + 1) & 1) * T::WBYTES, xs2, a_off, b_off,
-                                         k2 < ks_last ? k2 : ks_last, ks_last, KSt, kc);
-                if (i + 1 < L)
-                    gemm_step<T, LD, WM, WN>(p, ld, acc, xs1, wsm + ((i + 1) & 1) * T::WBYTES,
-                                             wsm + (i & 1) * T::WBYTES, xs0, a_off, b_off,
-                                             k2 + 1 < ks_last ? k2 + 1 : ks_last, ks_last, KSt, kc);
-                if (i + 2 < L)
-                    gemm_step<T, LD, WM, WN>(p, ld, acc, xs2, wsm + (i & 1) * T::WBYTES,
-                                             wsm + ((i + 1) & 1) * T::WBYTES, xs1, a_off, b_off,
-                                             k2 + 2 < ks_last ? k2 + 2 : ks_last, ks_last, KSt, kc);
-            }
+        for (int i = 0; i < L; i += 3) {
+            const int k2 = ks0 + i + 2;
+            gemm_step<T, LD, WM, WN>(p, ld, acc, xs0, wsm + (i & 1) * T::WBYTES,
+                                     wsm + ((i + 1) & 1) * T::WBYTES, xs2, a_off, b_off,
+                                     k2 < ks_last ? k2 : ks_last, ks_last, KSt, kc);
+            if (i + 1 < L)
+                gemm_step<T, LD, WM, WN>(p, ld, acc, xs1, wsm + ((i + 1) & 1) * T::WBYTES,
+                                         wsm + (i & 1) * T::WBYTES, xs0, a_off, b_off,
+                                         k2 + 1 < ks_last ? k2 + 1 : ks_last, ks_last, KSt, kc);
+            if (i + 2 < L)
+                gemm_step<T, LD, WM, WN>(p, ld, acc, xs2, wsm + (i & 1) * T::WBYTES,
+                                         wsm + ((i + 1) & 1) * T::WBYTES, xs1, a_off, b_off,
+                                         k2 + 2 < ks_last ? k2 + 2 : ks_last, ks_last, KSt, kc);
         }
         // the look-ahead transfers of the last steps are redundant; let them land before the
         // stages are reused
         wait_and_barrier<0>();
 
-        // recombine the eight planes and add the partial sum onto Z
-        auto recombine = [&](int i, int j, int e) -> u64 {
-            // sum_s sext64(S_s) << 8s: the four low planes as 32 x 32 -> 64 bit signed
-            // multiply-adds, the four high planes only reach the upper word
-            long long lo = (long long)acc[i][j][0][e];
-            lo += (long long)acc[i][j][1][e] * (1 << 8);
-            lo += (long long)acc[i][j][2][e] * (1 << 16);
-            lo += (long long)acc[i][j][3][e] * (1 << 24);
-            const u32 hi = (u32)acc[i][j][4][e] + ((u32)acc[i][j][5][e] << 8) +
-                           ((u32)acc[i][j][6][e] << 16) + ((u32)acc[i][j][7][e] << 24);
-            return (u64)lo + ((u64)hi << 32);
-        };
         // The only writer of a tile (own) stores Z = C + sum (Z += sum for a later segment of a long
         // contraction: this lane's own earlier store, complete since the barrier above); the loads of
         // a sub-tile go out together, ahead of the arithmetic.  Slices of a shared tile meet in Z,
@@ -1015,7 +750,8 @@ __device__ __forceinline__ void gemm_sweep(const GemmParams& p, const Geometry& 
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const int row = tm * T::BM + (wm * WM + i) * 32 + 8 * (e >> 2) + 4 * g + (e & 3);
-                    const u64 z = recombine(i, j, e);
+                    const u64 z = recombine(acc[i][j][0][e], acc[i][j][1][e], acc[i][j][2][e], acc[i][j][3][e],
+                                            acc[i][j][4][e], acc[i][j][5][e], acc[i][j][6][e], acc[i][j][7][e]);
                     bool live = row < m_eff && col < n_eff;
                     if (live && p.row_comp) live = p.row_comp[row] == ccomp;   // on a result block
                     if (live) {
@@ -1024,20 +760,8 @@ __device__ __forceinline__ void gemm_sweep(const GemmParams& p, const Geometry& 
                     }
                 }
             }
-        u += len;
     }
 }
-
-// LDS of the kernels: three activation stages filled by LDS-DMA two steps ahead, as separate
-// arrays so that the compiler can tell a stage being filled from the one
-// being read; two weight stages written from registers one step ahead (three, filled by
-// LDS-DMA, for weight planes, with the step table of a segment).
-#define COMET_GEMM_LDS(T, GMODE)                                                        \
-    __shared__ __align__(16) unsigned char xs0[T::XBYTES];                              \
-    __shared__ __align__(16) unsigned char xs1[T::XBYTES];                              \
-    __shared__ __align__(16) unsigned char xs2[T::XBYTES];                              \
-    __shared__ __align__(16) unsigned char wsm[T::wstages(GMODE) * T::WBYTES];          \
-    __shared__ __align__(16) int steptab[is_planes(GMODE) ? MAX_SEG * 4 : 4]
 
 // Workgroups are dealt round-robin to the 8 XCDs; give each XCD one contiguous range of work.
 __device__ __forceinline__ int xcd_contiguous(int b, int G) {
@@ -1048,56 +772,24 @@ __device__ __forceinline__ int xcd_contiguous(int b, int G) {
 // owns_tiles()); it still checks that on the device, where the counts are, and falls back to the
 // shared-tile path.  The other variant never owns: it carries none of that code.
 template <int WAVES_M, int WAVES_N, int WM, int WN, int KIND, int GMODE, bool LISTED, bool OWN = false>
-__global__ __launch_bounds__((Tile<WAVES_M, WAVES_N, WM, WN>::THREADS), (Tile<WAVES_M, WAVES_N, WM, WN>::wg_per_cu(GMODE))) void ring_gemm_kernel(GemmParams p) {
+__global__ __launch_bounds__(GT, (Tile<WAVES_M, WAVES_N, WM, WN>::WG_PER_CU)) void ring_gemm_kernel(GemmParams p) {
     using T = Tile<WAVES_M, WAVES_N, WM, WN>;
-    COMET_GEMM_LDS(T, GMODE);
+    // three activation stages filled by LDS-DMA two steps ahead, as separate arrays so that the
+    // compiler can tell a stage being filled from the one being read; two weight stages
+    // written from registers one step ahead
+    __shared__ __align__(16) unsigned char xs0[T::XBYTES];
+    __shared__ __align__(16) unsigned char xs1[T::XBYTES];
+    __shared__ __align__(16) unsigned char xs2[T::XBYTES];
+    __shared__ __align__(16) unsigned char wsm[T::WSTAGES * T::WBYTES];
     if (p.tile_sel && *p.tile_sel != p.tile_sel_want) return;   // the other tile shape was chosen
-    const Geometry q = gemm_geometry<T, KIND, LISTED>(p);
+    const Geometry q = gemm_geometry<T::BM, T::BN, KIND, LISTED, 1>(p);
     if (q.units == 0) return;
     const int G = gridDim.x;
     const int b = xcd_contiguous(blockIdx.x, G);
     bool own = false;
     if constexpr (OWN) own = owns_tiles(p, q.m_eff, q.n_eff, q.kc);
-    gemm_sweep<WAVES_M, WAVES_N, WM, WN, KIND, GMODE, LISTED>(p, q, q.units * b / G, q.units * (b + 1) / G, G, own,
-                                                             xs0, xs1, xs2, wsm, steptab);
-}
-
-// Several products of one shape and one index list (so: one geometry) in one launch: the work
-// units of the members follow each other, tile by tile inside a member, and the workgroups share
-// out the whole sequence.  A workgroup's range may run across members.
-constexpr int GROUP_MAX = COMET_SHARE_GROUP_MAX;
-struct GemmGroup {
-    int n;
-    GemmParams p[GROUP_MAX];
-};
-
-template <int WAVES_M, int WAVES_N, int WM, int WN, int KIND, int GMODE, bool OWN>
-__global__ __launch_bounds__((Tile<WAVES_M, WAVES_N, WM, WN>::THREADS), (Tile<WAVES_M, WAVES_N, WM, WN>::wg_per_cu(GMODE))) void ring_gemm_group_kernel(GemmGroup grp) {
-    using T = Tile<WAVES_M, WAVES_N, WM, WN>;
-    COMET_GEMM_LDS(T, GMODE);
-    const Geometry q = gemm_geometry<T, KIND, false>(grp.p[0]);
-    if (q.units == 0) return;
-    const int G = gridDim.x;
-    const int b = xcd_contiguous(blockIdx.x, G);
-    // Teams: when the row tiles divide the grid, tiles_m consecutive workgroups (same XCD) form a
-    // team that walks one sequence of (column tile, contraction step) units, each member for its
-    // own row tile: the weight planes of a unit are fetched once for all row tiles, in lockstep.
-    const bool team = grp.p[0].team && q.tiles_m > 1 && G % q.tiles_m == 0;
-    const long units = team ? q.units / q.tiles_m : q.units;        // of one member
-    const int parts = team ? G / q.tiles_m : G, part = team ? b / q.tiles_m : b;
-    const long total = units * grp.n;
-    long u = total * part / parts;
-    const long u_end = total * (part + 1) / parts;
-    bool own = false;
-    if constexpr (OWN) own = owns_tiles(grp.p[0], q.m_eff, q.n_eff, q.kc);
-#pragma nounroll
-    for (int j = (int)(u / units); u < u_end; ++j) {
-        const long base = (long)j * units;
-        const long hi = u_end - base < units ? u_end - base : units;
-        gemm_sweep<WAVES_M, WAVES_N, WM, WN, KIND, GMODE, false>(grp.p[j], q, u - base, hi, G, own, xs0, xs1, xs2,
-                                                                 wsm, steptab, team ? b % q.tiles_m : -1);
-        u = base + units;
-    }
+    UnitWalk<LISTED, 1> walk(p, q, b, G, own);
+    gemm_sweep<WAVES_M, WAVES_N, WM, WN, KIND, GMODE, LISTED>(p, q, walk, own, xs0, xs1, xs2, wsm);
 }
 
 // The kernel variant for a call: the kind of product, how the weight side is addressed, and
@@ -1105,17 +797,7 @@ __global__ __launch_bounds__((Tile<WAVES_M, WAVES_N, WM, WN>::THREADS), (Tile<WA
 // (tile shape, LISTED), so that the variants compile side by side.
 using GemmKernel = void (*)(GemmParams);
 
-// the OWN variants (128 x 64 tile, no step lists): translation units of their own
-template <int WAVES_M, int WAVES_N, int WM, int WN>
-GemmKernel gemm_own_planes_kernel_for(const GemmParams& p) {
-    if (p.kind == KIND_SIMM) {
-        if (p.b_full) return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, W_PLANES_GATHER, false, true>;
-        return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, W_PLANES, false, true>;
-    }
-    return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SOMM, W_PLANES, false, true>;
-}
-extern template GemmKernel gemm_own_planes_kernel_for<2, 2, 2, 1>(const GemmParams&);
-
+// the OWN variants (128 x 64 tile, no step lists): a translation unit of their own
 template <int WAVES_M, int WAVES_N, int WM, int WN>
 GemmKernel gemm_own_kernel_for(const GemmParams& p) {
     if (p.kind == KIND_SIMM) {
@@ -1143,57 +825,28 @@ GemmKernel gemm_kernel_for(const GemmParams& p) {
     }
 }
 
-// The variants that read weight planes: their own translation units (ring_gemm_planes_*.hip).
-template <int WAVES_M, int WAVES_N, int WM, int WN, bool LISTED>
-GemmKernel gemm_planes_kernel_for(const GemmParams& p) {
-    if (p.kind == KIND_SIMM) {
-        if (p.b_full) return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, W_PLANES_GATHER, LISTED>;
-        return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, W_PLANES, LISTED>;
-    }
-    if constexpr (LISTED) {
-        return nullptr;
-    } else {
-        return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SOMM, W_PLANES, false>;
-    }
-}
-
-extern template GemmKernel gemm_planes_kernel_for<2, 2, 2, 1, false>(const GemmParams&);
-extern template GemmKernel gemm_planes_kernel_for<2, 2, 1, 1, false>(const GemmParams&);
-extern template GemmKernel gemm_planes_kernel_for<2, 2, 1, 1, true>(const GemmParams&);
-extern template GemmKernel gemm_planes_kernel_for<1, 4, 1, 1, false>(const GemmParams&);
-extern template GemmKernel gemm_planes_kernel_for<1, 4, 1, 1, true>(const GemmParams&);
-
 extern template GemmKernel gemm_kernel_for<2, 2, 2, 1, false>(const GemmParams&);
 extern template GemmKernel gemm_kernel_for<2, 2, 1, 1, false>(const GemmParams&);
 extern template GemmKernel gemm_kernel_for<2, 2, 1, 1, true>(const GemmParams&);
 extern template GemmKernel gemm_kernel_for<1, 4, 1, 2, false>(const GemmParams&);
 extern template GemmKernel gemm_kernel_for<1, 4, 1, 2, true>(const GemmParams&);
 
-// Launch plan of the matrix-core kernel for an output tile BM x BN: the grid, the slice length and
-// whether the launch may turn out to own its tiles.  Fixed before the packing kernel is launched,
-// which has to know whether the share kernel will initialise Z itself.
-inline void plan_gemm(const comet_ctx* ctx, GemmParams& p, int BM, int BN, int wg_per_cu) {
+// Launch plan of the matrix-core kernels for an output tile BM x BN: the grid and whether the launch may turn out to own its tiles.  per: contraction steps per work unit (see
+// Geometry).  Fixed before the packing kernel is launched, which has to know whether the share
+// kernel will initialise Z itself.
+inline void plan_gemm(const comet_ctx* ctx, GemmParams& p, int BM, int BN, int wg_per_cu, int per) {
     const long tiles = (long)((p.m + BM - 1) / BM) * ((p.n_cap + BN - 1) / BN);
-    const long kt = 2l * p.ks_cap;
+    const long kt = 2l * p.ks_cap / per;
     const long units_cap = tiles * kt;
     // a chip-sized grid, shrunk when there is too little work to share out
     long grid = (ctx->num_cu / 8) * 8 * wg_per_cu;
     if (grid < 8) grid = 8;
-    const long want = (units_cap + 1) / 2;      // at least two contraction steps per workgroup
+    const long want = (units_cap * per + 1) / 2;      // at least two contraction steps per workgroup
     if (want < grid) grid = want < 8 ? (want < 1 ? 1 : want) : (want / 8) * 8;
     if (ctx->gemm_grid > 0) grid = ctx->gemm_grid;
-    // Slice length: as many slices as there are workgroups per tile, so that a workgroup's
-    // share of the units is one slice of one tile and all workgroups sweep their slice in
-    // lockstep (the activation planes of a slice are then shared through L2).
-    if (ctx->gemm_chunk > 0) {
-        p.chunk = ctx->gemm_chunk;
-    } else {
-        long slices = (grid + tiles / 2) / tiles;
-        if (slices < 1) slices = 1;
-        p.chunk = (int)((kt + slices - 1) / slices);
-    }
-    if (p.chunk > MAX_SEG) p.chunk = MAX_SEG;
-    if (p.chunk < 1) p.chunk = 1;
+    // how the contraction is cut is decided on the device (UnitWalk), unless the caller fixes it
+    p.chunk = ctx->gemm_chunk > 0 ? (ctx->gemm_chunk + per - 1) / per : 0;
+    if (p.chunk > MAX_SEG / per) p.chunk = MAX_SEG / per;
     p.grid = (int)grid;
     p.tile_bm = BM;
     p.tile_bn = BN;
@@ -1202,85 +855,39 @@ inline void plan_gemm(const comet_ctx* ctx, GemmParams& p, int BM, int BN, int w
     p.own_try = (!p.row_comp && !p.tmask && ctx->gemm_chunk == 0 && BM == 128 && tiles % grid == 0) ? 1 : 0;
 }
 
-template <int WAVES_M, int WAVES_N, int WM, int WN>
-int launch_gemm(comet_ctx* ctx, const char* what, GemmParams p) {
-    using T = Tile<WAVES_M, WAVES_N, WM, WN>;
-    GemmKernel kern = nullptr;
-    constexpr bool PLANES_ONLY = WAVES_N == 4 && WN == 1;     // the 32 x 128 tile exists for weight planes only
-    constexpr bool WORDS_ONLY = WAVES_N == 4 && WN == 2;      // the 32 x 256 tile needs two weight stages
-    constexpr bool HAS_OWN = WM * WN == 2 && WAVES_N == 2;    // the 128 x 64 tile
-    if (p.own_try) {
-        if constexpr (HAS_OWN)
-            kern = p.w_planes ? gemm_own_planes_kernel_for<WAVES_M, WAVES_N, WM, WN>(p)
-                              : gemm_own_kernel_for<WAVES_M, WAVES_N, WM, WN>(p);
-    } else if (p.w_planes) {
-        if constexpr (WORDS_ONLY) {
-            kern = nullptr;
-        } else if (p.step_list) {
-            if constexpr (WM * WN == 2 && WAVES_N == 2) kern = nullptr;
-            else kern = gemm_planes_kernel_for<WAVES_M, WAVES_N, WM, WN, true>(p);
-        } else {
-            kern = gemm_planes_kernel_for<WAVES_M, WAVES_N, WM, WN, false>(p);
-        }
-    } else if constexpr (PLANES_ONLY) {
-        kern = nullptr;
-    } else if (p.step_list) {
-        // per-token row sets: only the tile shapes the dispatch picks for them have such variants
-        if constexpr (WM * WN == 2 && WAVES_N == 2) kern = nullptr;
-        else kern = gemm_kernel_for<WAVES_M, WAVES_N, WM, WN, true>(p);
-    } else {
-        kern = gemm_kernel_for<WAVES_M, WAVES_N, WM, WN, false>(p);
-    }
-    if (!kern) return comet_fail(ctx, COMET_EINVAL, "%s: no kernel variant for this call", what);
-    if (p.tile_bm != T::BM || p.tile_bn != T::BN || p.grid < 1)
-        return comet_fail(ctx, COMET_EINVAL, "%s: launch plan does not match the kernel", what);
-    const long grid = p.grid;
-    const bool timed = comet_time_this_launch(ctx);
-    if (timed) {
-        // the event pair rides on the dispatch itself (its start and end timestamps): no marker
-        // packets before or after the kernel, so timing leaves the stream's schedule as it is
-        hipExtLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(T::THREADS), 0, ctx->stream, ctx->ev[ctx->ev_used],
+// Launches a share kernel; when this launch is a timed one the event pair rides on the dispatch
+// itself (its start and end timestamps): no marker packets before or after the kernel, so
+// timing leaves the stream's schedule as it is.
+template <class K, class P>
+int launch_share_kernel(comet_ctx* ctx, const char* what, K kern, int grid, const P& p) {
+    if (comet_time_this_launch(ctx)) {
+        hipExtLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(GT), 0, ctx->stream, ctx->ev[ctx->ev_used],
                               ctx->ev[ctx->ev_used + 1], 0, p);
         ctx->ev_used += 2;
     } else {
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(T::THREADS), 0, ctx->stream, p);
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(GT), 0, ctx->stream, p);
     }
     COMET_LAUNCH_CHECK(ctx, what);
     return COMET_OK;
 }
-
-// The grouped kernel exists for weight planes and the 128 x 64 tile (translation units
-// ring_gemm_group_128x64*.hip).
-using GemmGroupKernel = void (*)(GemmGroup);
-
-template <int WAVES_M, int WAVES_N, int WM, int WN, bool OWN>
-GemmGroupKernel gemm_group_kernel_for(const GemmParams& p) {
-    if (p.kind == KIND_SIMM) {
-        if (p.b_full) return ring_gemm_group_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, W_PLANES_GATHER, OWN>;
-        return ring_gemm_group_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, W_PLANES, OWN>;
-    }
-    return ring_gemm_group_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SOMM, W_PLANES, OWN>;
-}
-extern template GemmGroupKernel gemm_group_kernel_for<2, 2, 2, 1, false>(const GemmParams&);
-extern template GemmGroupKernel gemm_group_kernel_for<2, 2, 2, 1, true>(const GemmParams&);
 
 template <int WAVES_M, int WAVES_N, int WM, int WN>
-int launch_gemm_group(comet_ctx* ctx, const char* what, const GemmGroup& grp) {
+int launch_gemm(comet_ctx* ctx, const char* what, const GemmParams& p) {
     using T = Tile<WAVES_M, WAVES_N, WM, WN>;
-    const GemmParams& p = grp.p[0];
-    if (grp.n < 1 || grp.n > GROUP_MAX || !p.w_planes || p.tile_bm != T::BM || p.tile_bn != T::BN || p.grid < 1)
-        return comet_fail(ctx, COMET_EINVAL, "%s: launch plan does not match the grouped kernel", what);
-    GemmGroupKernel kern = p.own_try ? gemm_group_kernel_for<WAVES_M, WAVES_N, WM, WN, true>(p)
-                                     : gemm_group_kernel_for<WAVES_M, WAVES_N, WM, WN, false>(p);
-    if (comet_time_this_launch(ctx)) {
-        hipExtLaunchKernelGGL(kern, dim3((unsigned)p.grid), dim3(T::THREADS), 0, ctx->stream, ctx->ev[ctx->ev_used],
-                              ctx->ev[ctx->ev_used + 1], 0, grp);
-        ctx->ev_used += 2;
+    GemmKernel kern = nullptr;
+    if constexpr (WM * WN == 2 && WAVES_N == 2) {
+        // the 128 x 64 tile: no variants for per-token row sets (the dispatch picks 64 rows for them)
+        if (p.own_try) kern = gemm_own_kernel_for<WAVES_M, WAVES_N, WM, WN>(p);
+        else if (!p.step_list) kern = gemm_kernel_for<WAVES_M, WAVES_N, WM, WN, false>(p);
     } else {
-        hipLaunchKernelGGL(kern, dim3((unsigned)p.grid), dim3(T::THREADS), 0, ctx->stream, grp);
+        if (!p.own_try)
+            kern = p.step_list ? gemm_kernel_for<WAVES_M, WAVES_N, WM, WN, true>(p)
+                               : gemm_kernel_for<WAVES_M, WAVES_N, WM, WN, false>(p);
     }
-    COMET_LAUNCH_CHECK(ctx, what);
-    return COMET_OK;
+    if (!kern || p.w_planes) return comet_fail(ctx, COMET_EINVAL, "%s: no kernel variant for this call", what);
+    if (p.tile_bm != T::BM || p.tile_bn != T::BN || p.grid < 1)
+        return comet_fail(ctx, COMET_EINVAL, "%s: launch plan does not match the kernel", what);
+    return launch_share_kernel(ctx, what, kern, p.grid, p);
 }
 
 }  // namespace comet_gemm

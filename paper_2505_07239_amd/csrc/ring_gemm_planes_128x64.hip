@@ -1,5 +1,5 @@
-// The 128 x 64 output tile of the int8 matrix-core kernel: the variants whose weight-side operands
-// arrive as digit planes (see PlaneLoader in ring_gemm_kernel.h).
-#include "ring_gemm_kernel.h"
+// The 128 x 64 output tile of the int8 matrix-core kernel on weight planes: the variants that share
+// output tiles between workgroups.
+#include "ring_gemm_planes.h"
 
-template comet_gemm::GemmKernel comet_gemm::gemm_planes_kernel_for<2, 2, 2, 1, false>(const GemmParams&);
+template comet_gemm::GemmKernel comet_gemm::planes_kernel_for<2, 2, 4, 2, false, false>(const GemmParams&);

@@ -1,5 +1,4 @@
-// The 32 x 128 output tile of the int8 matrix-core kernel: the variants whose weight-side operands
-// arrive as digit planes (see PlaneLoader in ring_gemm_kernel.h).
-#include "ring_gemm_kernel.h"
+// The 32 x 128 output tile of the int8 matrix-core kernel on weight planes.
+#include "ring_gemm_planes.h"
 
-template comet_gemm::GemmKernel comet_gemm::gemm_planes_kernel_for<1, 4, 1, 1, false>(const GemmParams&);
+template comet_gemm::GemmKernel comet_gemm::planes_kernel_for<1, 4, 2, 2, false, false>(const GemmParams&);

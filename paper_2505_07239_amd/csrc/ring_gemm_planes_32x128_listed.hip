@@ -1,5 +1,5 @@
-// The 32 x 128, step lists output tile of the int8 matrix-core kernel: the variants whose weight-side operands
-// arrive as digit planes (see PlaneLoader in ring_gemm_kernel.h).
-#include "ring_gemm_kernel.h"
+// The 32 x 128 output tile of the int8 matrix-core kernel on weight planes: the variants that walk a
+// step list (per-token row sets).
+#include "ring_gemm_planes.h"
 
-template comet_gemm::GemmKernel comet_gemm::gemm_planes_kernel_for<1, 4, 1, 1, true>(const GemmParams&);
+template comet_gemm::GemmKernel comet_gemm::planes_kernel_for<1, 4, 2, 2, true, false>(const GemmParams&);

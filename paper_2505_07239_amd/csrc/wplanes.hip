@@ -1,5 +1,5 @@
-// Weight-side operands of the share calls as digit planes (the format PlaneLoader of
-// ring_gemm_kernel.h reads with LDS-DMA): the opening of the masked weights, F = [G]_0 + [G]_1
+// Weight-side operands of the share calls as digit planes (the format that ring_gemm_planes.h reads
+// with LDS-DMA): the opening of the masked weights, F = [G]_0 + [G]_1
 // (paper Sec. 2.1; Protocols 2 and 3 open only the indexed sub-matrices), written directly in
 // that format, and the same packing for a single operand (the triple share B_i, which is
 // offline material, Sec. 3.2).

@@ -1,0 +1,88 @@
+"""GPU parity of the share kernels at the sizes where their tilings can go wrong: every output element
+against the oracle's Eq. 1, at tile edges, remainders of the contraction units and the longest runs
+between two recombinations."""
+import sys
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import oracle as co                                   # noqa: E402
+from workloads import rng                             # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2505_07239_amd as comet
+    c = comet.Context(0)
+    yield c
+    c.close()
+
+
+def up(a):
+    return torch.from_numpy(np.ascontiguousarray(a).view(np.int64)).cuda()
+
+
+def down(t):
+    return t.cpu().numpy().view(np.uint64)
+
+
+def u64(seed, stream, *shape):
+    return rng.uniform_u64(seed, stream, int(np.prod(shape))).reshape(shape)
+
+
+def check(ctx, kind, m, other, bs, kept, fmt, full, party=1, seed=900):
+    """One share call: ``other`` is the axis that is not indexed (k of SOMM, n of SIMM)."""
+    print("[gpu-kernels] %s m=%d other=%d bs=%d blocks=%d %s full=%s" % (kind, m, other, bs, len(kept), fmt, full),
+          flush=True)
+    sys.stdout.flush()
+    idx = np.array(kept, dtype=np.int32)
+    t, nb = len(idx), int(idx.max()) + 2
+    na, nf = t * bs, nb * bs
+    if kind == "somm":
+        e, a, f, b, c = u64(seed, 1, m, other), u64(seed, 2, m, other), u64(seed, 3, other, na), u64(seed, 4, other, nf), \
+            u64(seed, 5, m, na)
+        a_sel, b_sel = a, co.index_cols(b, idx, bs)
+    else:
+        e, a, f, b, c = u64(seed, 1, m, na), u64(seed, 2, m, nf), u64(seed, 3, na, other), u64(seed, 4, nf, other), \
+            u64(seed, 5, m, other)
+        a_sel, b_sel = co.index_cols(a, idx, bs), co.index_rows(b, idx, bs)
+    want = co.beaver_share(party, e, f, a_sel, b_sel, c)
+    gi = torch.from_numpy(idx).cuda()
+    f_d, b_d = up(f), up(b if full else b_sel)
+    if fmt == "planes":
+        f_d, b_d = ctx.open_weight_planes(f_d), ctx.open_weight_planes(b_d)
+    if kind == "somm":
+        z = ctx.somm_share(party, bs, gi, None, t, up(e), f_d, up(a), b_d, up(c), b_full=full)
+    else:
+        z = ctx.simm_share(party, bs, gi, None, t, up(e), f_d, up(a if full else a_sel), b_d, up(c), a_full=full,
+                           b_full=full)
+    torch.cuda.synchronize()
+    assert np.array_equal(down(z), want)
+
+
+# Contraction of one half in words (steps of 32, stacked and taken in pairs): one step (the only pair
+# takes one step of each half), odd and even step counts, and one that no single run may cover
+# (more than 128 pairs for one workgroup when the tiles are as many as the workgroups).
+@pytest.mark.parametrize("m", [33, 64, 65, 128, 129])
+@pytest.mark.parametrize("k", [1, 31, 33, 64, 95, 160])
+def test_planes_tiles_and_step_pairs(ctx, m, k):
+    check(ctx, "somm", m, k, 16, (0, 2, 3, 5, 6), "planes", True)
+    if k >= 16:
+        check(ctx, "simm", m, 65, 16, tuple(range(0, 2 * ((k + 15) // 16), 2)), "planes", True)
+
+
+@pytest.mark.parametrize("m,n", [(33, 64), (128, 64)])
+def test_planes_long_contraction(ctx, m, n):
+    """One workgroup, 4 x 128 + 1 pairs: the planes are flushed between the runs."""
+    import paper_2505_07239_amd as comet
+    ctx.set_tuning(comet.TUNE_GEMM_GRID, 1)
+    try:
+        check(ctx, "somm", m, 513 * 32, n, (0,), "planes", True)
+    finally:
+        ctx.set_tuning(comet.TUNE_GEMM_GRID, 0)
