@@ -12,6 +12,19 @@ constexpr int EW_UNROLL = 4;
 
 typedef u64 u64x2 __attribute__((ext_vector_type(2)));
 
+// How a result is stored.  The next call of a protocol step reads it (the opening reads both masked
+// shares, the packing or the product the opened matrix), so a result that the 256 MB memory-side cache
+// can hold until then is stored through the caches (KEEP); a larger one would only push out what is
+// still to be read, and streams past them.  Masking both shares of a matrix and opening them took
+// 98 -> 85 us at 64 MB a matrix, 192 -> 174 us at 128 MB, 286 -> 270 us at 192 MB, and 477 -> 515 us
+// at 320 MB with every store cached: the line lies at 192 MB.
+constexpr size_t KEEP_BYTES = (size_t)192 << 20;
+template <bool KEEP, class T>
+__device__ __forceinline__ void store_result(T v, T* p) {
+    if (KEEP) *p = v;
+    else __builtin_nontemporal_store(v, p);
+}
+
 template <bool SUB>
 __device__ __forceinline__ u64x2 combine(u64x2 a, u64x2 b) {
     return SUB ? (a - b) : (a + b);
@@ -22,7 +35,7 @@ __device__ __forceinline__ u64x2 combine(u64x2 a, u64x2 b) {
 // 2 * EW_UNROLL requests in flight.
 // The output may be one of the inputs (same address): every element is read and then written by
 // the same lane, so the pointers carry no no-alias promise.
-template <bool SUB>
+template <bool SUB, bool KEEP>
 __global__ __launch_bounds__(EW_THREADS) void ew_kernel(const u64* a, const u64* b, u64* o,
                                                         size_t n_elems) {
     const size_t nvec = n_elems >> 1;
@@ -43,7 +56,7 @@ __global__ __launch_bounds__(EW_THREADS) void ew_kernel(const u64* a, const u64*
 #pragma unroll
         for (int j = 0; j < EW_UNROLL; ++j) {
             const size_t i = base + (size_t)j * EW_THREADS + threadIdx.x;
-            if (i < nvec) __builtin_nontemporal_store(combine<SUB>(ra[j], rb[j]), ov + i);
+            if (i < nvec) store_result<KEEP>(combine<SUB>(ra[j], rb[j]), ov + i);
         }
     }
     if ((n_elems & 1) && blockIdx.x == 0 && threadIdx.x == 0) {
@@ -56,7 +69,7 @@ __global__ __launch_bounds__(EW_THREADS) void ew_kernel(const u64* a, const u64*
 // pair of adjacent kept columns (a pair never straddles a block when bs is
 // even; the scalar variant covers odd bs or odd widths).
 constexpr int GC_THREADS = 128;   // a workgroup covers eight 32-word blocks of a row (measured: 256 threads 3 % slower, 512 8 %)
-template <int VEC>
+template <int VEC, bool KEEP>
 __global__ __launch_bounds__(GC_THREADS) void gather_cols_kernel(
     const u64* __restrict__ w, const u64* __restrict__ b, u64* __restrict__ g, int cols, int ld,
     int bs, const int* __restrict__ blk_idx, const int* __restrict__ n_blk_dev, int n_blk_cap, int gy) {
@@ -74,16 +87,16 @@ __global__ __launch_bounds__(GC_THREADS) void gather_cols_kernel(
         if (VEC == 2) {
             const u64x2 x = __builtin_nontemporal_load(reinterpret_cast<const u64x2*>(w + src));
             const u64x2 y = __builtin_nontemporal_load(reinterpret_cast<const u64x2*>(b + src));
-            __builtin_nontemporal_store(x - y, reinterpret_cast<u64x2*>(g + dst));
+            store_result<KEEP>(x - y, reinterpret_cast<u64x2*>(g + dst));
         } else {
-            g[dst] = w[src] - b[src];
+            store_result<KEEP>(w[src] - b[src], g + dst);
         }
     }
 }
 
 // Indexed masking along rows: the workgroups of a kept matrix row follow each other.
 constexpr int GR_THREADS = 128;
-template <int VEC>
+template <int VEC, bool KEEP>
 __global__ __launch_bounds__(GR_THREADS) void gather_rows_kernel(
     const u64* __restrict__ w, const u64* __restrict__ b, u64* __restrict__ g, int rows, int cols,
     int bs, const int* __restrict__ blk_idx, const int* __restrict__ n_blk_dev, int n_blk_cap, int gy) {
@@ -101,9 +114,9 @@ __global__ __launch_bounds__(GR_THREADS) void gather_rows_kernel(
         if (VEC == 2) {
             const u64x2 x = __builtin_nontemporal_load(reinterpret_cast<const u64x2*>(w + src + c));
             const u64x2 y = __builtin_nontemporal_load(reinterpret_cast<const u64x2*>(b + src + c));
-            __builtin_nontemporal_store(x - y, reinterpret_cast<u64x2*>(g + dst + c));
+            store_result<KEEP>(x - y, reinterpret_cast<u64x2*>(g + dst + c));
         } else {
-            g[dst + c] = w[src + c] - b[src + c];
+            store_result<KEEP>(w[src + c] - b[src + c], g + dst + c);
         }
     }
 }
@@ -125,7 +138,8 @@ int launch_ew(comet_ctx* ctx, const char* what, const u64* a, const u64* b, u64*
     // kernel only matters beyond 2^30 chunks
     const size_t cap = (size_t)1 << 30;
     const unsigned grid = (unsigned)(need < 1 ? 1 : (need < cap ? need : cap));
-    hipLaunchKernelGGL((ew_kernel<SUB>), dim3(grid), dim3(EW_THREADS), 0, ctx->stream, a, b, o, n);
+    auto kern = n * sizeof(u64) <= KEEP_BYTES ? ew_kernel<SUB, true> : ew_kernel<SUB, false>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(EW_THREADS), 0, ctx->stream, a, b, o, n);
     COMET_LAUNCH_CHECK(ctx, what);
     return COMET_OK;
 }
@@ -176,6 +190,7 @@ int comet_mask_share_gather(comet_ctx* ctx, const uint64_t* w_i, const uint64_t*
     if (rows == 0 || cols == 0 || ld == 0) return COMET_OK;
     comet_device_guard guard(ctx);
     if (!guard.ok) return comet_fail(ctx, COMET_EDEVICE, "%s: cannot select device", what);
+    const bool keep = (size_t)ld * (size_t)(axis == COMET_AXIS_COLS ? rows : cols) * sizeof(u64) <= KEEP_BYTES;
     if (axis == COMET_AXIS_COLS) {
         const bool vec = (bs % 2 == 0) && (cols % 2 == 0);
         const int per = GC_THREADS * (vec ? 2 : 1);
@@ -184,14 +199,9 @@ int comet_mask_share_gather(comet_ctx* ctx, const uint64_t* w_i, const uint64_t*
         const long gy_max = (1l << 31) / (rows > 0 ? rows : 1) - 1;
         if (gy > gy_max) gy = gy_max < 1 ? 1 : gy_max;
         const dim3 grid((unsigned)(rows * gy));
-        if (vec)
-            hipLaunchKernelGGL((gather_cols_kernel<2>), grid, dim3(GC_THREADS), 0, ctx->stream,
-                               (const u64*)w_i, (const u64*)b_i, (u64*)g_i, (int)cols, ld, bs,
-                               blk_idx, n_blk_dev, n_blk_cap, (int)gy);
-        else
-            hipLaunchKernelGGL((gather_cols_kernel<1>), grid, dim3(GC_THREADS), 0, ctx->stream,
-                               (const u64*)w_i, (const u64*)b_i, (u64*)g_i, (int)cols, ld, bs,
-                               blk_idx, n_blk_dev, n_blk_cap, (int)gy);
+        auto kern = !vec ? gather_cols_kernel<1, true> : keep ? gather_cols_kernel<2, true> : gather_cols_kernel<2, false>;
+        hipLaunchKernelGGL(kern, grid, dim3(GC_THREADS), 0, ctx->stream, (const u64*)w_i, (const u64*)b_i, (u64*)g_i,
+                           (int)cols, ld, bs, blk_idx, n_blk_dev, n_blk_cap, (int)gy);
     } else {
         const bool vec = (cols % 2 == 0);
         const int per = GR_THREADS * (vec ? 2 : 1) * 2;
@@ -199,14 +209,9 @@ int comet_mask_share_gather(comet_ctx* ctx, const uint64_t* w_i, const uint64_t*
         const long gy_max = (1l << 31) / ld - 1;           // rows x pieces stays a valid one-dimensional grid
         if (gy > gy_max) gy = gy_max < 1 ? 1 : gy_max;
         const dim3 grid((unsigned)((long)ld * gy));
-        if (vec)
-            hipLaunchKernelGGL((gather_rows_kernel<2>), grid, dim3(GR_THREADS), 0, ctx->stream,
-                               (const u64*)w_i, (const u64*)b_i, (u64*)g_i, (int)rows, (int)cols, bs,
-                               blk_idx, n_blk_dev, n_blk_cap, (int)gy);
-        else
-            hipLaunchKernelGGL((gather_rows_kernel<1>), grid, dim3(GR_THREADS), 0, ctx->stream,
-                               (const u64*)w_i, (const u64*)b_i, (u64*)g_i, (int)rows, (int)cols, bs,
-                               blk_idx, n_blk_dev, n_blk_cap, (int)gy);
+        auto kern = !vec ? gather_rows_kernel<1, true> : keep ? gather_rows_kernel<2, true> : gather_rows_kernel<2, false>;
+        hipLaunchKernelGGL(kern, grid, dim3(GR_THREADS), 0, ctx->stream, (const u64*)w_i, (const u64*)b_i, (u64*)g_i,
+                           (int)rows, (int)cols, bs, blk_idx, n_blk_dev, n_blk_cap, (int)gy);
     }
     COMET_LAUNCH_CHECK(ctx, what);
     return COMET_OK;

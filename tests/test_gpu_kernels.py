@@ -86,3 +86,30 @@ def test_planes_long_contraction(ctx, m, n):
         check(ctx, "somm", m, 513 * 32, n, (0,), "planes", True)
     finally:
         ctx.set_tuning(comet.TUNE_GEMM_GRID, 0)
+
+
+
+# Results are stored through the caches up to 192 MB (masked shares, opened words) and 112 MB (planes) and
+# past them beyond: just below, at and just above each line.
+@pytest.mark.parametrize("words", [(192 << 17) - 512, 192 << 17, (192 << 17) + 512])
+def test_store_rule_of_the_streaming_kernels(ctx, words):
+    import paper_2505_07239_amd as comet
+    print("[gpu-kernels] stores, %d words" % words, flush=True)
+    a = torch.randint(-2 ** 63, 2 ** 63 - 1, (words // 512, 512), dtype=torch.int64, device="cuda")
+    b = a.roll(1, 0)
+    assert torch.equal(ctx.mask_share(a, b), a - b) and torch.equal(ctx.open(a, b), a + b)
+    for axis, bs in ((comet.AXIS_ROWS, 1), (comet.AXIS_COLS, 2)):
+        idx = torch.arange(a.shape[axis == comet.AXIS_COLS] // bs, dtype=torch.int32, device="cuda")
+        assert torch.equal(ctx.mask_share_gather(a, b, axis, bs, idx, None, idx.numel()), a - b)
+
+
+@pytest.mark.parametrize("neuron_major", [False, True])
+@pytest.mark.parametrize("k", [(112 << 17) // 512 - 32, (112 << 17) // 512 + 32])
+def test_store_rule_of_the_plane_packing(ctx, k, neuron_major):
+    """Digit t of word (row, col) sits at byte row % 16 of unit (row / 32, col / 64, t, row / 16 % 2, col % 64)."""
+    print("[gpu-kernels] plane stores, k=%d neuron_major=%s" % (k, neuron_major), flush=True)
+    w = torch.randint(-2 ** 63, 2 ** 63 - 1, (k, 512), dtype=torch.int64, device="cuda")
+    buf = ctx.open_weight_planes(w.t().contiguous() if neuron_major else w, neuron_major=neuron_major).buf
+    bias = 0x0080808080808080
+    want = ((w + bias) ^ bias).view(torch.uint8).view(k // 32, 2, 16, 8, 64, 8).permute(0, 3, 5, 1, 4, 2)
+    assert torch.equal(buf.view(-1)[:w.numel() * 8].view(want.shape), want)
