@@ -100,8 +100,11 @@ def workspace_bytes(op: int, m: int, k: int, n: int, bs: int) -> int:
     return int(load_library().comet_workspace_bytes(op, m, k, n, bs))
 
 
+# A call of this module costs a few microseconds of host time and a small layer makes two dozen of
+# them, so the helpers stay with plain integers: the argument types are declared above, and ctypes
+# converts an address by itself.
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _words(t: torch.Tensor, what: str) -> torch.Tensor:
@@ -167,7 +170,7 @@ def _index_list(blk_idx, n_blk_dev, n_blk_cap: int, required: bool):
 
 
 def _shape(t: torch.Tensor, shape, what: str):
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError("%s has shape %s, expected %s" % (what, tuple(t.shape), tuple(shape)))
 
 
@@ -200,8 +203,8 @@ class Context:
             raise CometError(rc, self.lib.comet_last_error(self.h).decode())
 
     def _sync_stream(self):
-        s = torch.cuda.current_stream(self.device).cuda_stream
-        self._check(self.lib.comet_set_stream(self.h, ctypes.c_void_p(s)))
+        # (the handle itself: torch.cuda.current_stream builds a stream object around it on every call)
+        self._check(self.lib.comet_set_stream(self.h, torch._C._cuda_getCurrentRawStream(self.device)))
 
     def workspace(self, nbytes: int) -> Optional[torch.Tensor]:
         """A cached device buffer of at least ``nbytes`` (torch allocation, 256-byte aligned)."""
