@@ -84,7 +84,8 @@ __device__ __forceinline__ int wave_excl_scan(int v, int lane, int* total) {
     return inc - v;
 }
 
-// Exclusive prefix over the workgroup (CT threads).  sm: CT/64 + 1 ints.
+// Exclusive prefix over the workgroup (T threads).  sm: T/64 + 1 ints.
+template <int T = CT>
 __device__ __forceinline__ int block_excl_scan(int v, int* sm, int* block_total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int wtot;
@@ -93,7 +94,7 @@ __device__ __forceinline__ int block_excl_scan(int v, int* sm, int* block_total)
     __syncthreads();
     int base = 0, tot = 0;
 #pragma unroll
-    for (int w = 0; w < CT / 64; ++w) {
+    for (int w = 0; w < T / 64; ++w) {
         const int x = sm[w];
         if (w < wave) base += x;
         tot += x;
@@ -272,21 +273,24 @@ __device__ __forceinline__ void flat_or(const uint8_t* __restrict__ mask, long t
     }
 }
 
-// One workgroup: whole mask -> index list (nb <= 4096, so one 16-bit word per thread).
-__global__ __launch_bounds__(CT) void compact_flat_one_kernel(const uint8_t* __restrict__ mask, long n_tok,
+// One workgroup: whole mask -> index list (nb <= 4096, so one 16-bit word per thread of the first 256).
+// Bound by the trips over the mask, which is why it has sixteen wavefronts: 256 tokens x 344 blocks
+// took 14.5 us with four wavefronts and 11 us with sixteen.
+constexpr int OT = FLAT_WIDE * CT;
+__global__ __launch_bounds__(OT) void compact_flat_one_kernel(const uint8_t* __restrict__ mask, long n_tok,
                                                               long nb, int lead, int period,
                                                               int* __restrict__ blk_idx,
                                                               int* __restrict__ n_blk_dev) {
-    __shared__ int sm[CT / 64 + 1];
+    __shared__ int sm[OT / 64 + 1];
     __shared__ u32 bm[CT * FL / 32 + 1];
     if (threadIdx.x <= CT * FL / 32) bm[threadIdx.x] = 0;
     __syncthreads();
     const long total = n_tok * nb;
-    flat_or<CT>(mask, total, nb, lead, period, 0, (lead + total + 15) >> 4, bm);
+    flat_or<OT>(mask, total, nb, lead, period, 0, (lead + total + 15) >> 4, bm);
     __syncthreads();
-    const u32 bits = (bm[threadIdx.x >> 1] >> (16 * (threadIdx.x & 1))) & 0xffffu;
+    const u32 bits = threadIdx.x < CT ? (bm[threadIdx.x >> 1] >> (16 * (threadIdx.x & 1))) & 0xffffu : 0u;
     int count;
-    const int off = block_excl_scan(__builtin_popcount(bits), sm, &count);
+    const int off = block_excl_scan<OT>(__builtin_popcount(bits), sm, &count);
     emit_bits(bits, (int)threadIdx.x * FL, blk_idx + off);
     if (threadIdx.x == 0) *n_blk_dev = count;
 }
@@ -429,16 +433,36 @@ __global__ __launch_bounds__(ST) void compact_scan_kernel(int* __restrict__ coun
 // in the stage at the same position inside a 16-byte quad as in the output, so that aligned quads of the
 // stage are aligned quads of the output, and only the ragged ends are written one by one.
 // A denser chunk writes its indices directly.
+//
+// Where a workgroup's run starts: from the scanned counts (a launch of its own), or found by the
+// workgroup itself where that is little to read -- the words of the chunks before it, at most
+// OWN_WORDS_MAX of them (narrow masks: no count and no scan launch), or their counts, one per
+// thread (no scan launch).  Such a mask is bound by its launches: 4096 tokens x 13824 blocks
+// took 28 us in five launches and 21.5 us in three.
 constexpr int STAGE_CAP = 4092;
+enum { START_SCANNED, START_FROM_WORDS, START_FROM_COUNTS };
+constexpr int OWN_WORDS_MAX = 4;                  // chunks in all; three 8-byte loads per thread at most
+constexpr int OWN_COUNTS_MAX = CT;
+template <int START>
 __global__ __launch_bounds__(CT) void compact_emit_kernel(const unsigned short* __restrict__ words,
                                                           const int* __restrict__ offsets, long nb,
-                                                          int* __restrict__ blk_idx) {
+                                                          int* __restrict__ blk_idx, int* __restrict__ n_blk_dev) {
     __shared__ int sm[CT / 64 + 1];
     __shared__ __align__(16) int stage[STAGE_CAP + 4];
     const long w0 = (long)blockIdx.x * (CHUNK / FL) + (long)threadIdx.x * ITEMS;
     static_assert(ITEMS == 4, "one 8-byte load per lane");
     // the word array is padded to whole workgroup chunks, so the load is always in range
     const unsigned long long packed = *reinterpret_cast<const unsigned long long*>(words + w0);
+    int before = 0;
+    if (START == START_FROM_WORDS) {
+#pragma unroll
+        for (int q = 0; q + 1 < OWN_WORDS_MAX; ++q)            // (chunks before this one are whole)
+            if (q < (int)blockIdx.x)
+                before += __builtin_popcountll(*reinterpret_cast<const unsigned long long*>(
+                    words + (long)q * (CHUNK / FL) + (long)threadIdx.x * ITEMS));
+    } else if (START == START_FROM_COUNTS) {
+        before = threadIdx.x < blockIdx.x ? offsets[threadIdx.x] : 0;
+    }
     u32 bits[ITEMS];
     int cnt = 0;
 #pragma unroll
@@ -448,7 +472,15 @@ __global__ __launch_bounds__(CT) void compact_emit_kernel(const unsigned short* 
     }
     int total;
     int pos = block_excl_scan(cnt, sm, &total);
-    const long off = offsets[blockIdx.x];
+    long off;
+    if (START == START_SCANNED) {
+        off = offsets[blockIdx.x];
+    } else {
+        int sum;
+        (void)block_excl_scan(before, sm, &sum);
+        off = sum;
+        if (blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) *n_blk_dev = sum + total;
+    }
     int* out = blk_idx + off;
     if (total <= STAGE_CAP) {
         const int ph = (int)((reinterpret_cast<uintptr_t>(out) >> 2) & 3);   // position inside a 16-byte quad
@@ -569,8 +601,8 @@ extern "C" int comet_compact_mask(comet_ctx* ctx, const uint8_t* mask, int64_t n
         return COMET_OK;
     }
     if (p.path == PATH_FLAT_ONE) {
-        hipLaunchKernelGGL(compact_flat_one_kernel, dim3(1), dim3(CT), 0, ctx->stream, mask, (long)n_tok,
-                           (long)nb, lead, wide ? 0 : period, blk_idx, n_blk_dev);
+        hipLaunchKernelGGL(compact_flat_one_kernel, dim3(1), dim3(OT), 0, ctx->stream, mask, (long)n_tok,
+                           (long)nb, lead, period, blk_idx, n_blk_dev);
         COMET_LAUNCH_CHECK(ctx, what);
         return COMET_OK;
     }
@@ -615,16 +647,29 @@ extern "C" int comet_compact_mask(comet_ctx* ctx, const uint8_t* mask, int64_t n
         COMET_LAUNCH_CHECK(ctx, what);
         return COMET_OK;
     }
-    if (p.gy > 1 || p.path == PATH_FLAT) {
+    const bool counted = p.gy == 1 && p.path != PATH_FLAT;     // (the packing pass has counted its chunks)
+    if (!counted && groups <= OWN_WORDS_MAX) {
+        hipLaunchKernelGGL(compact_emit_kernel<START_FROM_WORDS>, dim3(groups), dim3(CT), 0, ctx->stream, words,
+                           counts, (long)nb, blk_idx, n_blk_dev);
+        COMET_LAUNCH_CHECK(ctx, what);
+        return COMET_OK;
+    }
+    if (!counted) {
         hipLaunchKernelGGL(compact_count_kernel, dim3(groups), dim3(CT), 0, ctx->stream, words, (long)nb,
                            counts);
         COMET_LAUNCH_CHECK(ctx, what);
     }
+    if (groups <= OWN_COUNTS_MAX) {
+        hipLaunchKernelGGL(compact_emit_kernel<START_FROM_COUNTS>, dim3(groups), dim3(CT), 0, ctx->stream, words,
+                           counts, (long)nb, blk_idx, n_blk_dev);
+        COMET_LAUNCH_CHECK(ctx, what);
+        return COMET_OK;
+    }
     hipLaunchKernelGGL(compact_scan_kernel, dim3(1), dim3(ST), 0, ctx->stream, counts, groups,
                        n_blk_dev);
     COMET_LAUNCH_CHECK(ctx, what);
-    hipLaunchKernelGGL(compact_emit_kernel, dim3(groups), dim3(CT), 0, ctx->stream, words, counts,
-                       (long)nb, blk_idx);
+    hipLaunchKernelGGL(compact_emit_kernel<START_SCANNED>, dim3(groups), dim3(CT), 0, ctx->stream, words, counts,
+                       (long)nb, blk_idx, n_blk_dev);
     COMET_LAUNCH_CHECK(ctx, what);
     return COMET_OK;
 }

@@ -113,3 +113,16 @@ def test_store_rule_of_the_plane_packing(ctx, k, neuron_major):
     bias = 0x0080808080808080
     want = ((w + bias) ^ bias).view(torch.uint8).view(k // 32, 2, 16, 8, 64, 8).permute(0, 3, 5, 1, 4, 2)
     assert torch.equal(buf.view(-1)[:w.numel() * 8].view(want.shape), want)
+
+
+# Where a chunk's run of indices starts: from the words of at most three chunks before it (16384 blocks a
+# chunk), from at most 255 counts, or from the scanned counts; and the one-workgroup masks of several tokens.
+@pytest.mark.parametrize("n_tok,nb", [(2, 16384), (2, 16385), (3, 49153), (2, 65536), (2, 65537), (1, 65537),
+                                      (1, 256 * 16384), (1, 256 * 16384 + 1), (31, 4096), (33, 3971), (70, 17)])
+@pytest.mark.parametrize("density", [0.0, 0.3, 1.0])
+def test_compact_chunk_starts(ctx, n_tok, nb, density):
+    print("[gpu-kernels] compact %d x %d, %g" % (n_tok, nb, density), flush=True)
+    mask = (rng.uniform_u64(7 + nb, 1, n_tok * nb) < np.uint64(min(int(density * 2 ** 64), 2 ** 64 - 1))).astype(np.uint8).reshape(n_tok, nb)
+    idx, n = ctx.compact_mask(torch.from_numpy(mask).cuda())
+    want = np.nonzero(mask.any(axis=0))[0]
+    assert int(n.item()) == len(want) and np.array_equal(idx[:len(want)].cpu().numpy(), want)
