@@ -259,7 +259,11 @@ __device__ __forceinline__ void xpack_body(const GemmParams& p, const int part) 
     }
 }
 
-__global__ __launch_bounds__(GT) void xpack_kernel(GemmParams p) { xpack_body(p, blockIdx.z); }
+__global__ __launch_bounds__(GT) void xpack_kernel(GemmParams p) {
+    // (the ticket of step_list_kernel)
+    if (p.tmask && (blockIdx.x | blockIdx.y | blockIdx.z | threadIdx.x) == 0) p.tile_list[0] = 0;
+    xpack_body(p, blockIdx.z);
+}
 
 // the members of a group (one shape): grid.z = 3 * member + part
 __global__ __launch_bounds__(GT) void xpack_group_kernel(GemmGroup grp) {
@@ -273,20 +277,17 @@ __global__ __launch_bounds__(GT) void xpack_group_kernel(GemmGroup grp) {
 // when the component ranges of its rows and of its columns overlap.  One workgroup writes the
 // numbers of those tiles, in the order the GEMM enumerates tiles (tile = tn * tiles_m + tm),
 // to list[1 ..] and their count to list[0]; the GEMM then deals out work over that list only.
-// For tall operands two shapes are listed (128 x 64 and 64 x 64) and the choice between them is
-// made here, on the device, from the area each would compute: both GEMM kernels are launched
+// For tall operands two shapes are listed (128 x 64 and the narrow tile) and the choice between them
+// is made here, on the device, from the area each would compute: both GEMM kernels are launched
 // and the one that was not chosen returns at once, so the host never waits for the counts.
-__global__ __launch_bounds__(GT) void tile_list_kernel(GemmParams p, int BM, int BN, int* list,
-                                                        const int* other, int other_area, int* sel) {
+__device__ int list_tiles(const GemmParams& p, int BM, int BN, int* list) {
     __shared__ int wave_tot[GT / 64];
-    __shared__ int base;
     const int nblk = n_blocks(p);
     const int m_eff = n_rows(p), n_eff = nblk * p.bs;
     const int tiles_m = (m_eff + BM - 1) / BM, tiles_n = (n_eff + BN - 1) / BN;
     const int tiles = tiles_m * tiles_n;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (threadIdx.x == 0) base = 0;
-    __syncthreads();
+    int base = 0;
     for (int t0 = 0; t0 < tiles; t0 += GT) {
         const int tile = t0 + threadIdx.x;
         bool on = false;
@@ -302,22 +303,29 @@ __global__ __launch_bounds__(GT) void tile_list_kernel(GemmParams p, int BM, int
         if (lane == 0) wave_tot[wave] = __builtin_popcountll(bal);
         __syncthreads();
         int pos = base + __builtin_popcountll(bal & ((1ull << lane) - 1));
-        for (int w = 0; w < wave; ++w) pos += wave_tot[w];
+#pragma unroll
+        for (int w = 0; w < GT / 64; ++w) {
+            const int v = wave_tot[w];
+            if (w < wave) pos += v;
+            base += v;
+        }
         if (on) list[1 + pos] = tile;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            int s = 0;
-            for (int w = 0; w < GT / 64; ++w) s += wave_tot[w];
-            base += s;
-        }
-        __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        list[0] = base;
-        // second of two shapes: this one runs when it computes at most 80 % of the other's area
-        // (smaller tiles follow the block structure more closely but reuse operands less)
-        if (sel) *sel = (5l * base * BM * BN < 4l * other[0] * other_area) ? 1 : 0;
+    if (threadIdx.x == 0) list[0] = base;
+    return base;
+}
+
+// One shape, or (list_b) two of them, 128 x 64 in list and the narrow tile BM x BN in list_b.
+__global__ __launch_bounds__(GT) void tile_list_kernel(GemmParams p, int BM, int BN, int* list, int* list_b, int* sel) {
+    if (!list_b) {
+        (void)list_tiles(p, BM, BN, list);
+        return;
     }
+    const long a = list_tiles(p, 128, 64, list), b = list_tiles(p, BM, BN, list_b);
+    // the second shape runs when it computes at most 80 % of the other's area
+    // (smaller tiles follow the block structure more closely but reuse operands less)
+    if (threadIdx.x == 0) *sel = 5l * b * BM * BN < 4l * a * 128 * 64 ? 1 : 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -326,12 +334,21 @@ __global__ __launch_bounds__(GT) void tile_list_kernel(GemmParams p, int BM, int
 // Protocol 3 multiplies column j of X only on its row set R_j.  At tile granularity: a row tile
 // needs contraction step s (32 consecutive kept neurons) only if one of its tokens uses one of
 // the blocks the step touches; for all other steps the tile's activation digits are zero.  One
-// workgroup per row tile lists its steps in ascending order (grid.x = row tiles); a second,
-// one-workgroup kernel turns the counts into offsets.  The GEMM then deals out work over the
-// listed steps only.
-__global__ __launch_bounds__(GT) void step_list_kernel(GemmParams p, int BM) {
-    __shared__ int wave_tot[GT / 64];
-    __shared__ int base;
+// workgroup per row tile lists its steps in ascending order (grid.x = row tiles), and the last of them to
+// finish turns the counts into offsets (step_off[t] = step_cnt[0] + ... + step_cnt[t - 1] for
+// t = 0 .. tiles).  The GEMM then deals out work over the listed steps only.
+//
+// What bounds it is the chain of dependent loads (a block's id, then the tokens' flags), so the flags of
+// every (block, group of four tokens) are requested by a thread of its own: first "does some token of the
+// tile use block t" for the blocks of a chunk of steps (a byte each in LDS), then the steps from those.
+// 256 tokens x 344 blocks, 64-row tiles: 10 us (38 with one thread per step, token after token, and the
+// offsets in a launch of their own).
+constexpr int SLT = 1024;              // threads per workgroup
+constexpr int SL_STEPS = 1024;         // steps per chunk, one per thread
+constexpr int SL_ROWS = 4;             // tokens per thread and block
+__global__ __launch_bounds__(SLT) void step_list_kernel(GemmParams p, int BM) {
+    __shared__ unsigned char used[SL_STEPS * KSTEP + 1];       // (blocks of one neuron: as many as words, and one cut by the start)
+    __shared__ int wave_tot[SLT / 64];
     const int nblk = n_blocks(p);
     const int m_eff = n_rows(p);
     const int kc = nblk * p.bs;
@@ -340,47 +357,61 @@ __global__ __launch_bounds__(GT) void step_list_kernel(GemmParams p, int BM) {
     const int r0 = tm * BM, r1 = (tm + 1) * BM < m_eff ? (tm + 1) * BM : m_eff;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int* list = p.step_list + (size_t)tm * p.ks_cap;
-    if (threadIdx.x == 0) base = 0;
-    __syncthreads();
-    for (int s0 = 0; s0 < KS; s0 += GT) {
+    int base = 0;
+    const int groups = r0 < r1 ? (r1 - r0 + SL_ROWS - 1) / SL_ROWS : 0;
+    for (int s0 = 0; s0 < KS; s0 += SL_STEPS) {
+        const int s1 = s0 + SL_STEPS < KS ? s0 + SL_STEPS : KS;
+        const int t0 = s0 * KSTEP / p.bs;
+        int t1 = (s1 * KSTEP - 1) / p.bs;                      // blocks t0 .. t1 lie in the chunk
+        t1 = t1 < nblk - 1 ? t1 : nblk - 1;
+        const int nt = t1 - t0 + 1;
+        for (int t = threadIdx.x; t < nt; t += SLT) used[t] = 0;
+        __syncthreads();
+        for (int i = threadIdx.x; i < nt * groups; i += SLT) {
+            const int t = i % nt, r = r0 + i / nt * SL_ROWS;
+            const long b = p.blk_idx[t0 + t];
+            if (b < 0 || b >= p.tmask_nb) continue;            // (see token_uses)
+            const unsigned char* flag = p.tmask + (long)r * p.tmask_nb + b;
+            unsigned any = 0;
+#pragma unroll
+            for (int j = 0; j < SL_ROWS; ++j) any |= flag[(r + j < r1 ? j : 0) * p.tmask_nb];
+            if (any) used[t] = 1;
+        }
+        __syncthreads();
         const int st = s0 + threadIdx.x;
         bool on = false;
-        if (st < KS && r0 < r1) {
-            const int t0 = st * KSTEP / p.bs;
-            int t1 = (st * KSTEP + KSTEP - 1) / p.bs;
-            t1 = t1 < nblk - 1 ? t1 : nblk - 1;
-            for (int t = t0; t <= t1 && !on; ++t)
-                for (int r = r0; r < r1 && !on; ++r) on = token_uses(p, r, t);
+        if (st < s1) {
+            int u1 = (st * KSTEP + KSTEP - 1) / p.bs;
+            u1 = u1 < t1 ? u1 : t1;
+            for (int t = st * KSTEP / p.bs; t <= u1; ++t) on = on || used[t - t0];
         }
         const unsigned long long bal = __ballot(on);
         if (lane == 0) wave_tot[wave] = __builtin_popcountll(bal);
         __syncthreads();
         int pos = base + __builtin_popcountll(bal & ((1ull << lane) - 1));
-        for (int w = 0; w < wave; ++w) pos += wave_tot[w];
+#pragma unroll
+        for (int w = 0; w < SLT / 64; ++w) {
+            const int v = wave_tot[w];
+            if (w < wave) pos += v;
+            base += v;
+        }
         if (on) list[pos] = st;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            int sum = 0;
-            for (int w = 0; w < GT / 64; ++w) sum += wave_tot[w];
-            base += sum;
-        }
-        __syncthreads();
     }
-    if (threadIdx.x == 0) p.step_cnt[tm] = base;
-}
-
-// step_off[t] = step_cnt[0] + ... + step_cnt[t - 1] for t = 0 .. tiles (one workgroup)
-__global__ __launch_bounds__(GT) void step_offsets_kernel(GemmParams p, int BM) {
-    __shared__ int wave_tot[GT / 64];
-    __shared__ int base;
-    const int m_eff = n_rows(p);
-    const int tiles = (m_eff + BM - 1) / BM;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (threadIdx.x == 0) base = 0;
+    // p.tile_list[0] counts the workgroups that are done (set to zero by the packing kernel); the counts pass
+    // between the XCDs as device-scope atomics
+    __shared__ int last;
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(p.step_cnt + tm, base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = __hip_atomic_fetch_add(p.tile_list, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    }
     __syncthreads();
-    for (int t0 = 0; t0 < tiles; t0 += GT) {
+    if (!last) return;
+    const int tiles = (m_eff + BM - 1) / BM;
+    int off = 0;
+    for (int t0 = 0; t0 < tiles; t0 += SLT) {
         const int t = t0 + threadIdx.x;
-        const int v = t < tiles ? p.step_cnt[t] : 0;
+        const int v = t < tiles ? __hip_atomic_load(p.step_cnt + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
         int inc = v;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
@@ -389,19 +420,19 @@ __global__ __launch_bounds__(GT) void step_offsets_kernel(GemmParams p, int BM) 
         }
         if (lane == 63) wave_tot[wave] = inc;
         __syncthreads();
-        int pre = base + inc - v;
-        for (int w = 0; w < wave; ++w) pre += wave_tot[w];
+        int pre = off + inc - v;
+#pragma unroll
+        for (int w = 0; w < SLT / 64; ++w) {
+            const int x = wave_tot[w];
+            if (w < wave) pre += x;
+            off += x;
+        }
         if (t < tiles) p.step_off[t] = pre;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            int sum = 0;
-            for (int w = 0; w < GT / 64; ++w) sum += wave_tot[w];
-            base += sum;
-        }
-        __syncthreads();
     }
-    if (threadIdx.x == 0) p.step_off[tiles] = base;
+    if (threadIdx.x == 0) p.step_off[tiles] = off;
 }
+
 inline int round_up(int64_t v, int64_t to) { return (int)(((v + to - 1) / to) * to); }
 
 // digit planes of [E | A'] (the few-row path keeps its k-major copy there instead)
@@ -525,16 +556,11 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
         p.tile_list = list_a;
         if (bm != 128) {
             hipLaunchKernelGGL(tile_list_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, bm,
-                               bm == 64 ? narrow_bn : flat_bn, list_a, (const int*)nullptr, 0,
-                               (int*)nullptr);
+                               bm == 64 ? narrow_bn : flat_bn, list_a, (int*)nullptr, (int*)nullptr);
             COMET_LAUNCH_CHECK(ctx, what);
             return launch(bm);
         }
-        hipLaunchKernelGGL(tile_list_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, 128, 64, list_a,
-                           (const int*)nullptr, 0, (int*)nullptr);
-        COMET_LAUNCH_CHECK(ctx, what);
-        hipLaunchKernelGGL(tile_list_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, 64, narrow_bn,
-                           list_b, (const int*)list_a, 128 * 64, sel);
+        hipLaunchKernelGGL(tile_list_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, 64, narrow_bn, list_a, list_b, sel);
         COMET_LAUNCH_CHECK(ctx, what);
         p.tile_sel = sel;
         p.tile_sel_want = 0;
@@ -554,9 +580,7 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
         p.step_off = base + t32;
         p.step_list = base + 2 * t32 + 1;
         const unsigned tiles_m = (unsigned)((p.m + bm - 1) / bm);
-        hipLaunchKernelGGL(step_list_kernel, dim3(tiles_m), dim3(GT), 0, ctx->stream, p, bm);
-        COMET_LAUNCH_CHECK(ctx, what);
-        hipLaunchKernelGGL(step_offsets_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, bm);
+        hipLaunchKernelGGL(step_list_kernel, dim3(tiles_m), dim3(SLT), 0, ctx->stream, p, bm);
         COMET_LAUNCH_CHECK(ctx, what);
     }
     return launch(bm);
