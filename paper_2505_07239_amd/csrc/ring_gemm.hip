@@ -468,6 +468,7 @@ void place_in_workspace(GemmParams& p, void* ws) {
     p.tile_list = reinterpret_cast<int*>(p.xp + planes_bytes(p.m, p.kc_cap));
     p.mpad = round_up(p.m, 128);
     p.ks_cap = (p.kc_cap + KSTEP - 1) / KSTEP;
+    p.w_nt = 2ll * 8 * p.kc_cap * p.n_cap > (320ll << 20);     // both weight operands (see Loader::load_word)
     p.bs_shift = -1;
     for (int sh = 0; sh < 30; ++sh)
         if (p.bs == (1 << sh)) p.bs_shift = sh;

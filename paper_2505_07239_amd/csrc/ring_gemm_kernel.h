@@ -109,7 +109,7 @@ __device__ __forceinline__ void wait_and_barrier() {
 // beyond the kept width are never written back, and (b) the packed activation
 // planes hold zeros beyond the contraction length, so whatever the weight side
 // reads there is multiplied by zero.
-template <class T, int KIND, int GMODE, bool LISTED>
+template <class T, int KIND, int GMODE, bool LISTED, bool NT>
 struct Loader {
     static constexpr int W = T::WTASK;
     // Where this task's weight words are.  Without a row gather: pointers to (row 0, the task's
@@ -277,6 +277,15 @@ struct Loader {
                      : "memory", "m0");
     }
 
+    // NT: past the caches.  Weight words well beyond the 256 MB memory-side cache only push out what is
+    // still needed there; smaller ones may still lie in it from the call that wrote them.  The line lies
+    // at 320 MB of B_i and F together: 260 MB took 76 -> 72 us with ordinary loads (k = 4096, 16 rows), 400 MB
+    // 97 -> 91 us without (16 rows), 106 -> 92 us (32), 688 MB 175 -> 162 us (32), 390 -> 371 us (128).
+    static __device__ __forceinline__ u64 load_word(const u64* q) {
+        if (NT) return __builtin_nontemporal_load(q);
+        return *q;
+    }
+
     // Word E of task J: split the word that is in the register into digits
     // (it was requested a step ago), then request the word of the step fixed by
     // begin() into the same register.  The choice between the two halves of the
@@ -309,7 +318,7 @@ struct Loader {
         if constexpr (GMODE == GATHER_POW2) {
             const char* rowp = wcur[J];
             wcur[J] += wpitch;
-            wn[J][E] = *reinterpret_cast<const u64*>(rowp + csel[J]);
+            wn[J][E] = load_word(reinterpret_cast<const u64*>(rowp + csel[J]));
             return;
         }
         const int kk = (k0 + E) < kc ? (k0 + E) : kc - 1;
@@ -333,7 +342,7 @@ struct Loader {
             // every operand holds fewer than 2^31 words (host check), so the word offset fits 32 bits
             const u64* src = h2 ? wf[J] : wb[J];
             const unsigned off = (unsigned)row * (unsigned)ld2;
-            wn[J][E] = src[off];
+            wn[J][E] = load_word(src + off);
         }
     }
 
@@ -671,12 +680,12 @@ __device__ __forceinline__ u64 recombine(int s0, int s1, int s2, int s3, int s4,
 
 // One workgroup's share of a product: segment by segment, the main loop and the write-out of the
 // partial sum.
-template <int WAVES_M, int WAVES_N, int WM, int WN, int KIND, int GMODE, bool LISTED>
+template <int WAVES_M, int WAVES_N, int WM, int WN, int KIND, int GMODE, bool LISTED, bool NT>
 __device__ __forceinline__ void gemm_sweep(const GemmParams& p, const Geometry& q, UnitWalk<LISTED, 1>& walk,
                                            const bool own, unsigned char* xs0, unsigned char* xs1,
                                            unsigned char* xs2, unsigned char* wsm) {
     using T = Tile<WAVES_M, WAVES_N, WM, WN>;
-    using LD = Loader<T, KIND, GMODE, LISTED>;
+    using LD = Loader<T, KIND, GMODE, LISTED, NT>;
     const int n_eff = q.n_eff, kc = q.kc, m_eff = q.m_eff;
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -771,7 +780,7 @@ __device__ __forceinline__ int xcd_contiguous(int b, int G) {
 // OWN: the variant for launches planned so that every workgroup gets whole output tiles (see
 // owns_tiles()); it still checks that on the device, where the counts are, and falls back to the
 // shared-tile path.  The other variant never owns: it carries none of that code.
-template <int WAVES_M, int WAVES_N, int WM, int WN, int KIND, int GMODE, bool LISTED, bool OWN = false>
+template <int WAVES_M, int WAVES_N, int WM, int WN, int KIND, int GMODE, bool LISTED, bool OWN = false, bool NT = false>
 __global__ __launch_bounds__(GT, (Tile<WAVES_M, WAVES_N, WM, WN>::WG_PER_CU)) void ring_gemm_kernel(GemmParams p) {
     using T = Tile<WAVES_M, WAVES_N, WM, WN>;
     // three activation stages filled by LDS-DMA two steps ahead, as separate arrays so that the
@@ -789,7 +798,7 @@ __global__ __launch_bounds__(GT, (Tile<WAVES_M, WAVES_N, WM, WN>::WG_PER_CU)) vo
     bool own = false;
     if constexpr (OWN) own = owns_tiles(p, q.m_eff, q.n_eff, q.kc);
     UnitWalk<LISTED, 1> walk(p, q, b, G, own);
-    gemm_sweep<WAVES_M, WAVES_N, WM, WN, KIND, GMODE, LISTED>(p, q, walk, own, xs0, xs1, xs2, wsm);
+    gemm_sweep<WAVES_M, WAVES_N, WM, WN, KIND, GMODE, LISTED, NT>(p, q, walk, own, xs0, xs1, xs2, wsm);
 }
 
 // The kernel variant for a call: the kind of product, how the weight side is addressed, and
@@ -801,27 +810,33 @@ using GemmKernel = void (*)(GemmParams);
 template <int WAVES_M, int WAVES_N, int WM, int WN>
 GemmKernel gemm_own_kernel_for(const GemmParams& p) {
     if (p.kind == KIND_SIMM) {
-        if (!p.b_full) return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, GATHER_NONE, false, true>;
-        if (p.bs_shift >= 3) return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, GATHER_POW2, false, true>;
+        if (!p.b_full) return p.w_nt ? ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, GATHER_NONE, false, true, true>
+                                     : ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, GATHER_NONE, false, true, false>;
+        if (p.bs_shift >= 3) return p.w_nt ? ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, GATHER_POW2, false, true, true>
+                                     : ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, GATHER_POW2, false, true, false>;
         return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, GATHER_ANY, false, true>;
     }
     if (p.w_tr) return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SOMM, WEIGHTS_TR, false, true>;
-    return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SOMM, GATHER_NONE, false, true>;
+    return p.w_nt ? ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SOMM, GATHER_NONE, false, true, true>
+                                     : ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SOMM, GATHER_NONE, false, true, false>;
 }
 extern template GemmKernel gemm_own_kernel_for<2, 2, 2, 1>(const GemmParams&);
 
 template <int WAVES_M, int WAVES_N, int WM, int WN, bool LISTED>
 GemmKernel gemm_kernel_for(const GemmParams& p) {
     if (p.kind == KIND_SIMM) {
-        if (!p.b_full) return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, GATHER_NONE, LISTED>;
-        if (p.bs_shift >= 3) return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, GATHER_POW2, LISTED>;
+        if (!p.b_full) return p.w_nt ? ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, GATHER_NONE, LISTED, false, true>
+                                     : ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, GATHER_NONE, LISTED, false, false>;
+        if (p.bs_shift >= 3) return p.w_nt ? ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, GATHER_POW2, LISTED, false, true>
+                                     : ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, GATHER_POW2, LISTED, false, false>;
         return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SIMM, GATHER_ANY, LISTED>;
     }
     if constexpr (LISTED) {
         return nullptr;      // step lists belong to Protocol 3
     } else {
         if (p.w_tr) return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SOMM, WEIGHTS_TR, false>;
-        return ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SOMM, GATHER_NONE, false>;
+        return p.w_nt ? ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SOMM, GATHER_NONE, false, false, true>
+                                     : ring_gemm_kernel<WAVES_M, WAVES_N, WM, WN, KIND_SOMM, GATHER_NONE, false, false, false>;
     }
 }
 
