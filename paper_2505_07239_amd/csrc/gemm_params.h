@@ -34,6 +34,8 @@ struct GemmParams {
     int mpad;       // rows of xp, multiple of 128
     int chunk;      // contraction units per scheduling slice fixed by the caller, or 0
     int ks_cap;     // contraction steps per half, ceil(kc_cap / 32)
+    int xstep[2];   // first step of a half in xp: 0 and ks_cap, or (group call) where the member's half lies in the common planes
+    int x_shared;   // group call: the planes of E are those of an earlier member
     // general forms of Protocols 2 and 3 (null when unused)
     const int* row_comp;      // SOMM blocks: component number of each listed row
     const int* blk_comp;      // SOMM blocks: component number of each listed block

@@ -143,7 +143,7 @@ struct PlaneStage {
                     n0[g] = (int)(st < 0 ? 0 : st) + (kb - blk * p.bs);
                 }
             }
-            *reinterpret_cast<v4i*>(table + 4 * q) = v4i{h * p.ks_cap + s, n0[0], n0[1], h};
+            *reinterpret_cast<v4i*>(table + 4 * q) = v4i{(h ? p.xstep[1] : p.xstep[0]) + s, n0[0], n0[1], h};
         }
         tab = table;
     }

@@ -126,3 +126,34 @@ def test_compact_chunk_starts(ctx, n_tok, nb, density):
     idx, n = ctx.compact_mask(torch.from_numpy(mask).cuda())
     want = np.nonzero(mask.any(axis=0))[0]
     assert int(n.item()) == len(want) and np.array_equal(idx[:len(want)].cpu().numpy(), want)
+
+
+# Members of a grouped call that name the same opened activations (whole tiles and ragged ones of the packing kernel).
+@pytest.mark.parametrize("kind", ["somm", "simm"])
+@pytest.mark.parametrize("m,k", [(65, 64), (130, 95), (256, 192)])
+@pytest.mark.parametrize("names", [(0, 0), (0, 0, 1, 1), (0, 1, 0, 1, 2), (1, 1, 1, 1, 1, 1, 1, 1)])
+def test_group_members_share_activations(ctx, kind, m, k, names):
+    import paper_2505_07239_amd as comet
+    print("[gpu-kernels] shared activations %s m=%d k=%d %s" % (kind, m, k, names), flush=True)
+    bs, idx = 16, np.array([0, 2, 3, 5, 6, 7], dtype=np.int32)
+    t, nb = len(idx), 9
+    na, nf = t * bs, nb * bs
+    es = {q: u64(300 + q, 1, m, k if kind == "somm" else na) for q in set(names)}
+    es_d = {q: up(e) for q, e in es.items()}
+    members, wants = [], []
+    for j, q in enumerate(names):
+        seed, party = 310 + j, j & 1
+        if kind == "somm":
+            f, a, b, c = u64(seed, 2, k, na), u64(seed, 3, m, k), u64(seed, 4, k, nf), u64(seed, 5, m, na)
+            wants.append(co.beaver_share(party, es[q], f, a, co.index_cols(b, idx, bs), c))
+        else:
+            f, a, b, c = u64(seed, 2, na, k), u64(seed, 3, m, nf), u64(seed, 4, nf, k), u64(seed, 5, m, k)
+            wants.append(co.beaver_share(party, es[q], f, co.index_cols(a, idx, bs), co.index_rows(b, idx, bs), c))
+        members.append((party, es_d[q], ctx.open_weight_planes(up(f)), up(a), ctx.open_weight_planes(up(b)), up(c)))
+    ctx.set_tuning(comet.TUNE_GROUP, 1)
+    try:
+        got = ctx.share_group(kind, bs, torch.from_numpy(idx).cuda(), None, t, members)
+    finally:
+        ctx.set_tuning(comet.TUNE_GROUP, 0)
+    for j, want in enumerate(wants):
+        assert np.array_equal(down(got[j]), want), "member %d" % j
