@@ -397,7 +397,7 @@ int comet_truncate_share(comet_ctx* ctx, int party, const uint64_t* z, uint64_t*
  *                         timed launch costs the stream about ten microseconds
  *                         of idle time around the kernel
  *   COMET_TUNE_GROUP:     comet_share_group normally runs its members as one
- *                         launch when a member alone is a short launch (8 to
+ *                         launch when a member alone is a short launch (up to
  *                         128 contraction steps of 32 words per workgroup);
  *                         1 = whenever the operands allow it, 2 = never,
  *                         3 = as 1 but without teaming the workgroups of a

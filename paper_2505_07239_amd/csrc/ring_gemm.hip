@@ -601,10 +601,11 @@ int run_share_group(comet_ctx* ctx, const char* what, GemmParams* ps, int n, voi
         return comet_fail(ctx, COMET_EALIGN, "%s: workspace must be 256-byte aligned", what);
     unsigned char* base = static_cast<unsigned char*>(ws);
     const GemmParams& p0 = ps[0];
-    // One launch for all members pays when a member alone is a short launch: between 8 and 128
-    // contraction steps per workgroup.  Below that the single calls shrink their grid instead;
-    // above it the fixed cost of a launch is amortised already and one long launch only runs
-    // at a lower sustained clock than the same work in pieces.
+    // One launch for all members pays up to 128 contraction steps per workgroup and member.  Short members
+    // gain most, because what they cost alone is launches, pipeline fill and write-out: two products of
+    // 128 x 768 x 320 39 -> 28 us, four of 65 x 256 x 256 66 -> 22 us, two of 256 x 4096 x 960 142 -> 122 us.
+    // Beyond that the fixed cost is amortised already and one long launch only runs at a lower
+    // sustained clock than the same work in pieces.
     using T = PlaneTile<2, 2, 4, 2>;
     long grid = (ctx->num_cu / 8) * 8;
     if (grid < 8) grid = 8;
@@ -613,7 +614,7 @@ int run_share_group(comet_ctx* ctx, const char* what, GemmParams* ps, int n, voi
     const long steps_each = tiles * 2 * ((p0.kc_cap + KSTEP - 1) / KSTEP) / grid;
     const bool grouped = n > 1 && p0.w_planes && p0.m > 64 && p0.n_cap > 0 && ctx->gemm_tile != 2 &&
                          (ctx->group_mode == 1 || ctx->group_mode == 3 ||
-                          (ctx->group_mode == 0 && steps_each >= 8 && steps_each <= 128));
+                          (ctx->group_mode == 0 && steps_each <= 128));
     if (!grouped) {
         for (int j = 0; j < n; ++j) {
             const int rc = run_share(ctx, what, ps[j], base + (size_t)j * each, each);

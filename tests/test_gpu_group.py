@@ -163,8 +163,8 @@ def test_owned_tiles_follow_the_device_side_block_count(ctx, kept, spare, single
 @pytest.mark.parametrize("kind", ["somm", "simm"])
 @pytest.mark.parametrize("mode", [0, 2])
 def test_share_group_automatic_and_switched_off(ctx, kind, mode):
-    """Mode 0 decides by the size of a member (this one is far too small for a joint launch),
-    mode 2 never groups: both run the members one after the other."""
+    """Mode 0 decides by the size of a member (short ones like this run as one launch), mode 2 never
+    groups: the members run one after the other."""
     import paper_2505_07239_amd as comet
     ctx.set_tuning(comet.TUNE_GROUP, mode)
     try:
