@@ -274,9 +274,9 @@ __device__ __forceinline__ void flat_or(const uint8_t* __restrict__ mask, long t
 }
 
 // One workgroup: whole mask -> index list (nb <= 4096, so one 16-bit word per thread of the first 256).
-// Bound by the trips over the mask, which is why it has sixteen wavefronts: 256 tokens x 344 blocks
-// took 14.5 us with four wavefronts and 11 us with sixteen.
-constexpr int OT = FLAT_WIDE * CT;
+// Bound by the trips over the mask, so a mask that four wavefronts do not read in one trip gets
+// sixteen: 256 tokens x 344 blocks 14.5 -> 9.2 us; 8 x 216 takes 5.4 us with four and 6.1 with sixteen.
+template <int OT>
 __global__ __launch_bounds__(OT) void compact_flat_one_kernel(const uint8_t* __restrict__ mask, long n_tok,
                                                               long nb, int lead, int period,
                                                               int* __restrict__ blk_idx,
@@ -601,8 +601,10 @@ extern "C" int comet_compact_mask(comet_ctx* ctx, const uint8_t* mask, int64_t n
         return COMET_OK;
     }
     if (p.path == PATH_FLAT_ONE) {
-        hipLaunchKernelGGL(compact_flat_one_kernel, dim3(1), dim3(OT), 0, ctx->stream, mask, (long)n_tok,
-                           (long)nb, lead, period, blk_idx, n_blk_dev);
+        const bool many = n_tok * nb > 16l * FLAT_VEC;
+        hipLaunchKernelGGL(many ? compact_flat_one_kernel<FLAT_WIDE * CT> : compact_flat_one_kernel<CT>, dim3(1),
+                           dim3(many ? FLAT_WIDE * CT : CT), 0, ctx->stream, mask, (long)n_tok, (long)nb, lead,
+                           wide && !many ? 0 : period, blk_idx, n_blk_dev);
         COMET_LAUNCH_CHECK(ctx, what);
         return COMET_OK;
     }

@@ -118,7 +118,7 @@ def test_store_rule_of_the_plane_packing(ctx, k, neuron_major):
 # Where a chunk's run of indices starts: from the words of at most three chunks before it (16384 blocks a
 # chunk), from at most 255 counts, or from the scanned counts; and the one-workgroup masks of several tokens.
 @pytest.mark.parametrize("n_tok,nb", [(2, 16384), (2, 16385), (3, 49153), (2, 65536), (2, 65537), (1, 65537),
-                                      (1, 256 * 16384), (1, 256 * 16384 + 1), (31, 4096), (33, 3971), (70, 17)])
+                                      (1, 256 * 16384), (1, 256 * 16384 + 1), (4, 4096), (5, 4096), (31, 4096), (33, 3971), (70, 17)])
 @pytest.mark.parametrize("density", [0.0, 0.3, 1.0])
 def test_compact_chunk_starts(ctx, n_tok, nb, density):
     print("[gpu-kernels] compact %d x %d, %g" % (n_tok, nb, density), flush=True)
