@@ -88,7 +88,7 @@ using namespace comet_gemm;
 // grid: x = chunks of four 16-word groups, y = chunks of 64 rows, z = 0 (E), 1 (A'), 2 (Z := C).
 // A workgroup packs a 64-row x 64-word tile: four adjacent lanes read 512 contiguous bytes of
 // one row, and the sixteen lanes that share a group write sixteen adjacent 16-byte units.
-__device__ __forceinline__ void xpack_body(const GemmParams& p, const int part) {
+__device__ __forceinline__ void xpack_body(const GemmParams& p, const int part, const int xstep) {
     const int nblk = n_blocks(p);
     const int m_eff = n_rows(p);
     if (part == 2) {
@@ -122,7 +122,6 @@ __device__ __forceinline__ void xpack_body(const GemmParams& p, const int part) 
         }
         return;
     }
-    if (part == 0 && p.x_shared) return;
     const int kc = p.kind == KIND_SOMM ? p.kc_cap : nblk * p.bs;
     // Whole tile of 64 rows x 64 contraction words inside the operands: the loads want the lanes
     // along k (a row piece of 512 bytes per half wavefront), the stores want them along the rows (a
@@ -175,7 +174,7 @@ __device__ __forceinline__ void xpack_body(const GemmParams& p, const int part) 
             const int s = half16 >> 1, g = half16 & 1;
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
-                u64x2* dst = reinterpret_cast<u64x2*>(p.xp) + xp_group(0, p.xstep[h] + s, t, g, 0) * p.mpad + trow;
+                u64x2* dst = reinterpret_cast<u64x2*>(p.xp) + xp_group(0, xstep + s, t, g, 0) * p.mpad + trow;
                 *dst = u64x2{plane[0][t], plane[1][t]};
             }
             return;
@@ -255,20 +254,25 @@ __device__ __forceinline__ void xpack_body(const GemmParams& p, const int part) 
     const int s = half16 >> 1, g = half16 & 1;
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-        u64x2* dst = reinterpret_cast<u64x2*>(p.xp) + xp_group(0, p.xstep[h] + s, t, g, 0) * p.mpad + row;
+        u64x2* dst = reinterpret_cast<u64x2*>(p.xp) + xp_group(0, xstep + s, t, g, 0) * p.mpad + row;
         *dst = u64x2{plane[0][t], plane[1][t]};
     }
 }
 
 __global__ __launch_bounds__(GT) void xpack_kernel(GemmParams p) {
-    // (the ticket of step_list_kernel)
+    xpack_body(p, blockIdx.z, blockIdx.z == 1 ? p.ks_cap : 0);
+    // The ticket of step_list_kernel.  Behind the packing: ahead of a store the compiler reads the
+    // parameters and the counts in one batch of scalar loads, behind one word by word through vector loads
+    // (9 rows, 64 x 64 words: 14.9 us a call with this store first, 14.6 with it last).
     if (p.tmask && (blockIdx.x | blockIdx.y | blockIdx.z | threadIdx.x) == 0) p.tile_list[0] = 0;
-    xpack_body(p, blockIdx.z);
 }
 
 // the members of a group (one shape): grid.z = 3 * member + part
 __global__ __launch_bounds__(GT) void xpack_group_kernel(GemmGroup grp) {
-    xpack_body(grp.p[blockIdx.z / 3], blockIdx.z % 3);
+    const GemmParams& p = grp.p[blockIdx.z / 3];
+    const int part = blockIdx.z % 3;
+    if (part == 0 && p.x_shared) return;                       // packed with an earlier member
+    xpack_body(p, part, p.xstep[part == 1]);
 }
 
 // ---------------------------------------------------------------------------

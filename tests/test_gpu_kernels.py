@@ -88,6 +88,68 @@ def test_planes_long_contraction(ctx, m, n):
         ctx.set_tuning(comet.TUNE_GEMM_GRID, 0)
 
 
+def masked_mask(m, nb, per_block, seed=950):
+    """Every block belongs to one token, and to per_block - 1 more at random: most steps of a row tile are
+    there for a single token, and the row tiles list different ones."""
+    mask = np.zeros((m, nb), np.uint8)
+    r = rng.uniform_u64(seed + m, 60, nb * per_block).reshape(nb, per_block)
+    for j in range(nb):
+        mask[(7 * j) % m, j] = 1
+        mask[(r[j, 1:] % np.uint64(m)).astype(np.int64), j] = 1
+    return mask
+
+
+def check_masked(ctx, m, nb, bs, n, fmt, per_block, full=True, replays=0):
+    print("[gpu-kernels] masked m=%d nb=%d bs=%d n=%d %s full=%s" % (m, nb, bs, n, fmt, full), flush=True)
+    k, seed = nb * bs, 940
+    e, a, f, b, c = u64(seed, 1, m, k), u64(seed, 2, m, k), u64(seed, 3, k, n), u64(seed, 4, k, n), u64(seed, 5, m, n)
+    idx = torch.arange(nb, dtype=torch.int32, device="cuda")
+    f_d, b_d = up(f), up(b)
+    if fmt == "planes":
+        f_d, b_d = ctx.open_weight_planes(f_d), ctx.open_weight_planes(b_d)
+    e_d, a_d, c_d = up(e), up(a), up(c)
+    tm, z = torch.zeros((m, nb), dtype=torch.uint8, device="cuda"), torch.zeros((m, n), dtype=torch.int64, device="cuda")
+
+    def call():
+        ctx.simm_share_masked(1, bs, idx, None, nb, tm, e_d, f_d, a_d, b_d, c_d, a_full=full, b_full=full, out=z)
+
+    def inputs(rep):
+        mask = masked_mask(m, nb, per_block, 950 + rep)
+        tm.copy_(torch.from_numpy(mask))
+        return co.beaver_share_sparse_input(1, e, f, a, b, c, np.repeat(mask, bs, axis=1))
+
+    want = inputs(0)
+    call()
+    assert np.array_equal(down(z), want)
+    if not replays:
+        return
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for rep in range(1, replays + 1):
+        want = inputs(rep)
+        z.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(down(z), want), "replay %d" % rep
+        z.zero_()
+        call()
+        assert np.array_equal(down(z), want), "eager after replay %d" % rep
+
+
+# Step lists of more than one chunk (1024 steps of 32 neurons): blocks that end with a chunk, are cut by its
+# end, and single neurons; rows that are no multiple of four.
+@pytest.mark.parametrize("m,nb,bs", [(70, 1056, 32), (70, 702, 48), (67, 1605, 21), (35, 33001, 1), (130, 2064, 16)])
+@pytest.mark.parametrize("fmt", ["words", "planes"])
+def test_masked_step_list_chunks(ctx, m, nb, bs, fmt):
+    check_masked(ctx, m, nb, bs, 40, fmt, 1, fmt == "words" or bs % 16 == 0)
+
+
+# The counter of finished workgroups starts from zero in every call, replayed or not.
+@pytest.mark.parametrize("fmt", ["words", "planes"])
+def test_masked_replays(ctx, fmt):
+    check_masked(ctx, 200, 60, 16, 96, fmt, 2, replays=3)
+
 
 # Results are stored through the caches up to 192 MB (masked shares, opened words) and 112 MB (planes) and
 # past them beyond: just below, at and just above each line.
