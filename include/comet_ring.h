@@ -381,11 +381,11 @@ int comet_truncate_share(comet_ctx* ctx, int party, const uint64_t* z, uint64_t*
  *                         (default: one per compute unit, fewer for tiny work)
  *   COMET_TUNE_GEMM_CHUNK: contraction steps (of 32 words) per scheduling slice,
  *                         clamped to 256
- *   COMET_TUNE_GEMM_TILE: 2 forces the 64 x 64 output tile (two workgroups per
- *                         compute unit) whatever m is
- *   COMET_TUNE_SKINNY:    calls with m <= 8 normally take a vector-ALU kernel
- *                         bound by reading the weights once; 1 sends them to the
- *                         matrix-core kernel like any other call
+ *   COMET_TUNE_GEMM_TILE: 2 forces an output tile of 64 rows whatever m is
+ *                         (64 columns; 128 for large products on weight planes)
+ *   COMET_TUNE_SKINNY:    calls with m <= 8, on weight planes m <= 32, normally
+ *                         take a kernel bound by reading the weights once; 1
+ *                         sends them to the matrix-core kernel like any other
  *   COMET_TUNE_SKINNY_SLICES: pieces the stacked contraction is cut into by
  *                         the vector-ALU kernel (default: about eight
  *                         workgroups per compute unit)

@@ -481,6 +481,25 @@ void place_in_workspace(GemmParams& p, void* ws) {
         if (p.bs == (1 << sh)) p.bs_shift = sh;
 }
 
+// Columns of the 64-row tile on weight planes: 64, or 128 for large products.  A pair of contraction steps takes
+// a workgroup 1.1 us on 64 x 64 and 2.2 us on 64 x 128, which reads half of its operands from LDS less
+// often.  What decides is how many 64 x 64 pairs there are per compute unit: below 32 of them
+// the finer pieces fill the chip better (128 x 768 x 320 19 -> 16 us, 64 x 1664 x 4096 45 -> 38, 192 x
+// 2560 x 640 40 -> 33), from there on the wider tile is ahead (320 x 4096 x 960 101 -> 83, 448 x 4096 x 2560 342 -> 279).
+// Exceptions, as measured: a single row tile reads every weight unit once and stays with 64 (64 x 11008 x
+// 1664 97 -> 94); so does a multiple of 64 tiles, whose workgroup shares line up with the tiles, up to 256 pairs
+// (192 x 1664 x 4096 96 -> 82, 320 x 1664 x 4096 139 -> 133).  With step lists the row tiles do not sweep side by side: 128 columns from 32 pairs
+// on (512 tokens x 344 blocks of 32, n = 1024 334 -> 278), with a single row tile from 24 (33 x 344 of 16, n = 2560 85 -> 75).
+// Result blocks keep 64: the finer tile follows them more closely (129 x 216 of 32, k = 1024 86 -> 68).
+int planes_narrow_bn(const comet_ctx* ctx, const GemmParams& p) {
+    const long tiles = (long)((p.m + 63) / 64) * ((p.n_cap + 63) / 64);
+    const long pairs = tiles * ((p.kc_cap + KSTEP - 1) / KSTEP) / (ctx->num_cu > 0 ? ctx->num_cu : 1);
+    if (p.row_comp) return 64;
+    if (p.tmask) return pairs >= (p.m <= 64 ? 24 : 32) ? 128 : 64;
+    if (p.m <= 64 || pairs < 32 || (tiles % 64 == 0 && pairs < 256)) return 64;
+    return 128;
+}
+
 int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t ws_bytes) {
     const size_t need = gemm_ws_bytes(p.m, p.kc_cap, p.n_cap);
     if (!ws || ws_bytes < need)
@@ -501,9 +520,10 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
         return comet_launch_skinny(ctx, what, p);
     // Tile shape and launch plan first: the packing kernel has to know whether the share kernel
     // will own its tiles (and then initialise Z itself).
-    const int narrow_bn = p.w_planes ? 128 : 64, flat_bn = p.w_planes ? 128 : 256;   // columns of the 64- and 32-row tiles
+    // columns of the 64- and 32-row tiles
+    const int narrow_bn = p.w_planes ? planes_narrow_bn(ctx, p) : 64, flat_bn = p.w_planes ? 128 : 256;
     auto plan = [&](int bm) {
-        if (p.w_planes) plan_gemm(ctx, p, bm, bm == 128 ? 64 : 128, 1, 2);
+        if (p.w_planes) plan_gemm(ctx, p, bm, bm == 128 ? 64 : bm == 64 ? narrow_bn : 128, 1, 2);
         else if (bm == 128) plan_gemm(ctx, p, 128, 64, Tile<2, 2, 2, 1>::WG_PER_CU, 1);
         else if (bm == 64) plan_gemm(ctx, p, 64, 64, Tile<2, 2, 1, 1>::WG_PER_CU, 1);
         else plan_gemm(ctx, p, 32, 256, Tile<1, 4, 1, 2>::WG_PER_CU, 1);
@@ -512,6 +532,7 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
         plan(bm);
         if (p.w_planes) {
             if (bm == 128) return launch_planes<2, 2, 4, 2>(ctx, what, p);
+            if (bm == 64 && narrow_bn == 64) return launch_planes<2, 2, 2, 2>(ctx, what, p);
             if (bm == 64) return launch_planes<1, 4, 4, 2>(ctx, what, p);
             return launch_planes<1, 4, 2, 2>(ctx, what, p);
         }
@@ -526,7 +547,7 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
     else if (p.m <= 32) bm = 32;
     else if (p.m <= 64) bm = 64;
     // a small product (a handful of 128 x 64 tiles) is bound by the fixed cost per workgroup:
-    // the 64 x 64 tile doubles the number of independent tiles
+    // 64 rows double the number of independent tiles
     else if (!p.row_comp && big_tiles * 8 <= ctx->num_cu) bm = 64;
     // a ragged last row tile: 64-row tiles when they pad the rows by clearly less (the smaller
     // tile is about 5 % slower per product)

@@ -36,10 +36,11 @@
 namespace comet_gemm {
 
 constexpr int KPAIR = 2 * KSTEP;          // ring words contracted per matrix instruction
-constexpr int MAX_PAIRS = MAX_SEG / 2;    // pairs an int32 plane can absorb
 
 // Output tile of WAVES_M x WAVES_N wavefronts (four, one per SIMD), each with MT x NT sub-tiles of
-// 16 x 16 outputs in eight digit planes: 4 x 2 sub-tiles fill the 256 accumulator registers.
+// 16 x 16 outputs in eight digit planes: 4 x 2 sub-tiles fill the 256 accumulator registers.  The tile with
+// 2 x 2 of them, 64 x 64, is for small products: a pair of steps takes 1.1 us there and 2.2 us on the others,
+// and that is the least a workgroup can do (see planes_narrow_bn in ring_gemm.hip for where the line lies).
 template <int WAVES_M, int WAVES_N, int MT_, int NT_>
 struct PlaneTile {
     static constexpr int MT = MT_, NT = NT_;
@@ -427,6 +428,8 @@ GemmKernel planes_kernel_for(const GemmParams& p) {
 extern template GemmKernel planes_kernel_for<2, 2, 4, 2, false, false>(const GemmParams&);
 extern template GemmKernel planes_kernel_for<2, 2, 4, 2, false, true>(const GemmParams&);
 extern template GemmKernel planes_kernel_for<1, 4, 4, 2, false, false>(const GemmParams&);
+extern template GemmKernel planes_kernel_for<2, 2, 2, 2, false, false>(const GemmParams&);
+extern template GemmKernel planes_kernel_for<2, 2, 2, 2, true, false>(const GemmParams&);
 extern template GemmKernel planes_kernel_for<1, 4, 4, 2, true, false>(const GemmParams&);
 extern template GemmKernel planes_kernel_for<1, 4, 2, 2, false, false>(const GemmParams&);
 extern template GemmKernel planes_kernel_for<1, 4, 2, 2, true, false>(const GemmParams&);
@@ -435,7 +438,7 @@ template <int WAVES_M, int WAVES_N, int MT, int NT>
 int launch_planes(comet_ctx* ctx, const char* what, const GemmParams& p) {
     using T = PlaneTile<WAVES_M, WAVES_N, MT, NT>;
     GemmKernel kern = nullptr;
-    if constexpr (WAVES_N == 2) {
+    if constexpr (T::BM == 128) {
         if (!p.step_list)
             kern = p.own_try ? planes_kernel_for<WAVES_M, WAVES_N, MT, NT, false, true>(p)
                              : planes_kernel_for<WAVES_M, WAVES_N, MT, NT, false, false>(p);

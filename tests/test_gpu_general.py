@@ -258,7 +258,7 @@ def test_simm_per_token_row_sets(ctx, m, nb, bs, n, groups, per_tok, compact_tri
 # ---------------------------------------------------------------------------
 
 def _somm_blocks_case(ctx, seed, m, k, nb, bs, groups, per_tok, spare_rows=0, spare_blocks=0, b_full=True,
-                      neuron_major=False):
+                      neuron_major=False, planes=False):
     n_full = nb * bs
     mask_blk = grouped_mask(seed, m, nb, groups, per_tok)
     s = np.repeat(mask_blk, bs, axis=1)
@@ -291,8 +291,11 @@ def _somm_blocks_case(ctx, seed, m, k, nb, bs, groups, per_tok, spare_rows=0, sp
         f_arg = f_c
         if neuron_major:                      # the same weights stored one row per neuron
             b_arg, f_arg = np.ascontiguousarray(b_arg.T), np.ascontiguousarray(f_c.T)
+        b_arg, f_arg = up(b_arg), up(f_arg)
+        if planes:
+            b_arg, f_arg = ctx.open_weight_planes(b_arg), ctx.open_weight_planes(f_arg)
         z = ctx.somm_share_blocks(party, bs, comp["blk_idx"], comp["blk_comp"], comp["n_blk"], cap,
-                                  comp["row_comp"], comp["n_row"], up(e_p), up(f_arg), up(a_p), up(b_arg),
+                                  comp["row_comp"], comp["n_row"], up(e_p), f_arg, up(a_p), b_arg,
                                   up(c_p), b_full=b_full, neuron_major=neuron_major)
         torch.cuda.synchronize()
         zz = down(z)
@@ -328,6 +331,19 @@ def test_somm_result_blocks_neuron_major_weights(ctx, m, k, nb, bs, groups, per_
     say("somm blocks, neuron-major weights m=%d k=%d nb=%d bs=%d groups=%d" % (m, k, nb, bs, groups))
     n_comp = _somm_blocks_case(ctx, 430 + m, m, k, nb, bs, groups, per_tok, spare_rows=3,
                                spare_blocks=0 if b_full else 1, b_full=b_full, neuron_major=True)
+    assert n_comp >= 1
+
+
+# Weight planes: the 32 x 128 tile (up to 32 rows), 64 x 64 (up to 64), and beyond that 128 x 64 or 64 x 64, as the
+# result blocks lie (one component, or several of some 50 rows).
+@pytest.mark.parametrize("m,k,nb,bs,groups,per_tok,b_full", [(9, 64, 24, 16, 3, 3, True), (32, 95, 24, 16, 2, 3, False),
+                                                             (40, 70, 20, 32, 4, 2, True), (64, 33, 20, 7, 1, 3, True),
+                                                             (129, 130, 16, 16, 1, 3, True), (260, 64, 40, 32, 5, 2, False),
+                                                             (260, 31, 24, 48, 1, 4, True), (300, 160, 30, 16, 6, 3, True)])
+def test_somm_result_blocks_weight_planes(ctx, m, k, nb, bs, groups, per_tok, b_full):
+    say("somm blocks, weight planes m=%d k=%d nb=%d bs=%d groups=%d" % (m, k, nb, bs, groups))
+    n_comp = _somm_blocks_case(ctx, 460 + m, m, k, nb, bs, groups, per_tok, spare_rows=3,
+                               spare_blocks=0 if b_full else 1, b_full=b_full, planes=True)
     assert n_comp >= 1
 
 

@@ -67,8 +67,7 @@ def check(ctx, kind, m, other, bs, kept, fmt, full, party=1, seed=900):
 
 
 # Contraction of one half in words (steps of 32, stacked and taken in pairs): one step (the only pair
-# takes one step of each half), odd and even step counts, and one that no single run may cover
-# (more than 128 pairs for one workgroup when the tiles are as many as the workgroups).
+# takes one step of each half), odd and even step counts.  Few tiles, so every m takes the 64 x 64 tile.
 @pytest.mark.parametrize("m", [33, 64, 65, 128, 129])
 @pytest.mark.parametrize("k", [1, 31, 33, 64, 95, 160])
 def test_planes_tiles_and_step_pairs(ctx, m, k):
@@ -86,6 +85,68 @@ def test_planes_long_contraction(ctx, m, n):
         check(ctx, "somm", m, 513 * 32, n, (0,), "planes", True)
     finally:
         ctx.set_tuning(comet.TUNE_GEMM_GRID, 0)
+
+
+def check_columns(ctx, kind, m, k, n, fmt, grid=0, seed=920):
+    """One share call too large for the oracle as a whole: the first and last column of every 64, compared
+    in full.  bs = 16; every second block of the indexed axis (n of SOMM, k of SIMM) is kept."""
+    import paper_2505_07239_amd as comet
+    print("[gpu-kernels] columns %s m=%d k=%d n=%d %s grid=%d" % (kind, m, k, n, fmt, grid), flush=True)
+    bs, t = 16, (n if kind == "somm" else k) // 16
+    idx = np.arange(0, 2 * t, 2, dtype=np.int32)
+    e, c = u64(seed, 1, m, k), u64(seed, 5, m, n)
+    f = torch.randint(-2 ** 63, 2 ** 63 - 1, (k, n), dtype=torch.int64, device="cuda")
+    full = (k, 2 * n) if kind == "somm" else (2 * k, n)
+    b = torch.randint(-2 ** 63, 2 ** 63 - 1, full, dtype=torch.int64, device="cuda")
+    a = u64(seed, 2, m, k if kind == "somm" else 2 * k)
+    sel = np.repeat(idx.astype(np.int64), bs) * bs + np.tile(np.arange(bs), t)     # gathered position of a compact one
+    cols = np.unique(np.concatenate([np.arange(0, n, 64), np.minimum(np.arange(63, n + 64, 64), n - 1)]))
+    cols_d = torch.from_numpy(cols).cuda()
+    if kind == "somm":
+        b_sel, a_sel = down(b[:, torch.from_numpy(sel[cols]).cuda()]), a
+    else:
+        b_sel, a_sel = down(b[:, cols_d][torch.from_numpy(sel).cuda()]), np.ascontiguousarray(a[:, sel])
+    want = co.beaver_share(1, e, down(f[:, cols_d]), a_sel, b_sel, np.ascontiguousarray(c[:, cols]))
+    if fmt == "planes":
+        f, b = ctx.open_weight_planes(f), ctx.open_weight_planes(b)
+    ctx.set_tuning(comet.TUNE_GEMM_GRID, grid)
+    try:
+        call = ctx.somm_share if kind == "somm" else ctx.simm_share
+        z = call(1, bs, torch.from_numpy(idx).cuda(), None, t, up(e), f, up(a), b, up(c))
+    finally:
+        ctx.set_tuning(comet.TUNE_GEMM_GRID, 0)
+    assert np.array_equal(down(z[:, cols_d]), want)
+
+
+# The 128 x 64 tile of a single call (more than 32 tiles, rows not ragged): shared tiles; and owned ones
+# (the forced grid divides the tiles), with a contraction of more than 128 pairs that one run may not cover.
+@pytest.mark.parametrize("kind,m,k,n,grid", [("somm", 128, 33, 2112, 0), ("somm", 250, 95, 2112, 0), ("somm", 250, 1, 2112, 0),
+                                             ("simm", 128, 48, 2100, 0), ("simm", 250, 112, 2100, 0),
+                                             ("somm", 128, 33, 2112, 11), ("simm", 128, 48, 2112, 11),
+                                             ("somm", 250, 129 * 32 + 5, 2112, 33), ("simm", 250, 129 * 32 + 16, 2112, 33)])
+def test_planes_128x64_single_calls(ctx, kind, m, k, n, grid):
+    check_columns(ctx, kind, m, k, n, "planes", grid)
+
+
+# The choice between 64 x 64 and 64 x 128: below and from 32 pairs per compute unit on (5 x 15 tiles), a multiple of 64
+# tiles below and from 256 pairs on, a single row tile.
+@pytest.mark.parametrize("kind,m,k,n", [("somm", 320, 3488, 960), ("somm", 320, 3520, 960), ("simm", 300, 3520, 912),
+                                        ("somm", 192, 1664, 4096), ("somm", 192, 10928, 4096), ("simm", 64, 4096, 2560)])
+def test_planes_narrow_tile_choice(ctx, kind, m, k, n):
+    check_columns(ctx, kind, m, k, n, "planes")
+
+
+# The 32 x 128 tile, which plain calls take only with the few-row kernels switched off.
+@pytest.mark.parametrize("kind", ["somm", "simm"])
+@pytest.mark.parametrize("m,other", [(1, 31), (9, 33), (31, 64), (32, 95), (32, 300)])
+def test_planes_32x128_tile(ctx, kind, m, other):
+    import paper_2505_07239_amd as comet
+    ctx.set_tuning(comet.TUNE_SKINNY, 1)
+    try:
+        check(ctx, kind, m, other, 16, (0, 2, 3, 5, 6, 7, 9, 10, 13), "planes", True)
+        check(ctx, kind, m, other, 16, (1, 4), "planes", False)
+    finally:
+        ctx.set_tuning(comet.TUNE_SKINNY, 0)
 
 
 def masked_mask(m, nb, per_block, seed=950):
@@ -135,6 +196,14 @@ def check_masked(ctx, m, nb, bs, n, fmt, per_block, full=True, replays=0):
         z.zero_()
         call()
         assert np.array_equal(down(z), want), "eager after replay %d" % rep
+
+
+# Per-token row sets on weight planes: the 32 x 128, 64 x 64 and (from 32 pairs per compute unit on, 24 with one row tile) 64 x 128 tiles.
+@pytest.mark.parametrize("m,nb,bs,n", [(9, 12, 16, 40), (32, 30, 32, 130), (33, 12, 16, 64), (64, 20, 48, 65),
+                                       (129, 16, 16, 200), (260, 40, 32, 96), (64, 512, 32, 768), (200, 512, 32, 257)])
+@pytest.mark.parametrize("full", [True, False])
+def test_masked_planes(ctx, m, nb, bs, n, full):
+    check_masked(ctx, m, nb, bs, n, "planes", 3, full)
 
 
 # Step lists of more than one chunk (1024 steps of 32 neurons): blocks that end with a chunk, are cut by its

@@ -168,9 +168,8 @@ def _run(ctx, cs, party, b_full):
         assert np.array_equal(down(z), cs["want"][party])
 
 
-# (m, contraction / neurons, other dimension, bs, kept blocks, spare capacity): every tile shape
-# (m <= 32: 32 x 128, m <= 64: 64 x 64, else 128 x 64 or 64 x 64), ragged tails, one and several
-# blocks per contraction step
+# (m, other dimension, bs, kept blocks, spare capacity): the few-row kernel (m <= 32) and the 64 x 64 tile (few
+# tiles; the other shapes are in test_gpu_kernels.py), ragged tails, one and several blocks per contraction step
 SHAPES = [
     (5, 96, 8, (0, 3, 4, 9), 0), (20, 130, 16, (1, 2, 6), 1), (32, 64, 32, (0, 2), 0),
     (50, 200, 16, (0, 5, 6, 7, 11), 2), (64, 96, 48, (1, 3), 0),
