@@ -19,21 +19,13 @@ using namespace comet_gemm;
 constexpr int WT = 128;
 typedef u64 u64x2 __attribute__((ext_vector_type(2)));
 
-// Planes that the 256 MB memory-side cache holds beside the operands they come from are stored through
-// the caches (KEEP), so that the product that follows finds them there: a layer step with 108 MB of
-// planes per operand took 533 -> 519 us, one with 2 MB 154 -> 148 us.  Larger ones stream past: masking
-// both shares and packing them took 129 us either way at 96 MB, 166 -> 181 us with cached stores at
-// 128 MB, 455 -> 517 us at 320 MB.  The line lies in between, at 112 MB.
-constexpr size_t KEEP_BYTES = (size_t)112 << 20;
-template <bool KEEP>
-__device__ __forceinline__ void store_unit(u64x2 v, u64x2* p) {
-    if (KEEP) *p = v;
-    else __builtin_nontemporal_store(v, p);
-}
+// The planes are stored past the caches, whatever their size.  Stored through them, packing alone takes 1 to 4 %
+// longer (18.3 -> 18.7 us at 16 MB of planes, 101 -> 103 at 100 MB, 183 -> 196 at 192 MB), and what the product that
+// follows saves does not make up for it: masking, packing and a product of 64 or 256 rows together take 0 to 3 %
+// longer between 8 and 192 MB, and one of 16 rows gains 1 to 3 % from 16 to 48 MB only (1024, 2048 and 4096 x n words).
 
 // One thread packs sixteen contraction rows of one column: its sixteen loads per operand are
 // coalesced across the wavefront (adjacent columns), and so are its eight 16-byte stores.
-template <bool KEEP>
 __global__ __launch_bounds__(WT) void wpack_kernel(const u64* __restrict__ a, const u64* __restrict__ b,
                                                    u64x2* __restrict__ out, long k, long n, long groups) {
     const long c = (long)blockIdx.x * WT + threadIdx.x;
@@ -68,7 +60,7 @@ __global__ __launch_bounds__(WT) void wpack_kernel(const u64* __restrict__ a, co
         u64x2* dst = out + ((s * nch + (c >> 6)) * 16 + g) * 64 + (c & 63);
 #pragma unroll
         for (int t = 0; t < 8; ++t)
-            store_unit<KEEP>(u64x2{plane[0][t], plane[1][t]}, dst + t * 128);
+            __builtin_nontemporal_store(u64x2{plane[0][t], plane[1][t]}, dst + t * 128);
     }
 }
 
@@ -79,7 +71,6 @@ __global__ __launch_bounds__(WT) void wpack_kernel(const u64* __restrict__ a, co
 // into the tile, then every thread takes the sixteen words of one (column, k-half) from there.
 constexpr int TT = 256;
 constexpr int TPITCH = 33;                       // 16-byte vectors per tile row (32 + 1 of padding)
-template <bool KEEP>
 __global__ __launch_bounds__(TT) void wpack_t_kernel(const u64* __restrict__ a, const u64* __restrict__ b,
                                                      u64x2* __restrict__ out, long k, long n) {
     __shared__ u64x2 tile[64 * TPITCH];
@@ -128,7 +119,7 @@ __global__ __launch_bounds__(TT) void wpack_t_kernel(const u64* __restrict__ a, 
     u64x2* dst = out + ((s * nch + (col >> 6)) * 16 + g) * 64 + (col & 63);
 #pragma unroll
     for (int t = 0; t < 8; ++t)
-        store_unit<KEEP>(u64x2{plane[0][t], plane[1][t]}, dst + t * 128);
+        __builtin_nontemporal_store(u64x2{plane[0][t], plane[1][t]}, dst + t * 128);
 }
 
 }  // namespace
@@ -152,13 +143,12 @@ static int open_planes(comet_ctx* ctx, const char* what, const uint64_t* g_0, co
         return comet_fail(ctx, COMET_EALIGN, "%s: pointers must be 16-byte aligned", what);
     comet_device_guard guard(ctx);
     if (!guard.ok) return comet_fail(ctx, COMET_EDEVICE, "%s: cannot select device", what);
-    const bool keep = comet_weight_planes_bytes(k, n) <= KEEP_BYTES;
     if (neuron_major) {
         // one workgroup per (chunk of 64 columns, 64 contraction rows); the tiles along k of a chunk are
         // dispatched together: they read adjacent pieces of the same 64 operand rows (4 % faster than
         // the tiles of one contraction step together)
         const dim3 grid((unsigned)((k + 63) / 64), (unsigned)((n + 63) / 64));
-        hipLaunchKernelGGL(keep ? wpack_t_kernel<true> : wpack_t_kernel<false>, grid, dim3(TT), 0, ctx->stream, (const u64*)g_0, (const u64*)g_1,
+        hipLaunchKernelGGL(wpack_t_kernel, grid, dim3(TT), 0, ctx->stream, (const u64*)g_0, (const u64*)g_1,
                            (u64x2*)planes, (long)k, (long)n);
         COMET_LAUNCH_CHECK(ctx, what);
         return COMET_OK;
@@ -169,7 +159,7 @@ static int open_planes(comet_ctx* ctx, const char* what, const uint64_t* g_0, co
     long gy = groups;
     if (gy > 65535) gy = 65535;
     if (gy < 1) gy = 1;
-    hipLaunchKernelGGL(keep ? wpack_kernel<true> : wpack_kernel<false>, dim3(gx, (unsigned)gy), dim3(WT), 0, ctx->stream, (const u64*)g_0,
+    hipLaunchKernelGGL(wpack_kernel, dim3(gx, (unsigned)gy), dim3(WT), 0, ctx->stream, (const u64*)g_0,
                        (const u64*)g_1, (u64x2*)planes, (long)k, (long)n, groups);
     COMET_LAUNCH_CHECK(ctx, what);
     return COMET_OK;

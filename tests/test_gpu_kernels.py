@@ -220,8 +220,8 @@ def test_masked_replays(ctx, fmt):
     check_masked(ctx, 200, 60, 16, 96, fmt, 2, replays=3)
 
 
-# Results are stored through the caches up to 192 MB (masked shares, opened words) and 112 MB (planes) and
-# past them beyond: just below, at and just above each line.
+# Masked shares and opened words are stored through the caches up to 192 MB and past them beyond: just below, at
+# and just above the line.
 @pytest.mark.parametrize("words", [(192 << 17) - 512, 192 << 17, (192 << 17) + 512])
 def test_store_rule_of_the_streaming_kernels(ctx, words):
     import paper_2505_07239_amd as comet
@@ -236,7 +236,7 @@ def test_store_rule_of_the_streaming_kernels(ctx, words):
 
 @pytest.mark.parametrize("neuron_major", [False, True])
 @pytest.mark.parametrize("k", [(112 << 17) // 512 - 32, (112 << 17) // 512 + 32])
-def test_store_rule_of_the_plane_packing(ctx, k, neuron_major):
+def test_large_planes(ctx, k, neuron_major):
     """Digit t of word (row, col) sits at byte row % 16 of unit (row / 32, col / 64, t, row / 16 % 2, col % 64)."""
     print("[gpu-kernels] plane stores, k=%d neuron_major=%s" % (k, neuron_major), flush=True)
     w = torch.randint(-2 ** 63, 2 ** 63 - 1, (k, 512), dtype=torch.int64, device="cuda")
