@@ -274,8 +274,19 @@ __device__ __forceinline__ void flat_or(const uint8_t* __restrict__ mask, long t
 }
 
 // One workgroup: whole mask -> index list (nb <= 4096, so one 16-bit word per thread of the first 256).
-// Bound by the trips over the mask, so a mask that four wavefronts do not read in one trip gets
-// sixteen: 256 tokens x 344 blocks 14.5 -> 9.2 us; 8 x 216 takes 5.4 us with four and 6.1 with sixteen.
+// Four wavefronts, or sixteen for masks with many trips: they need fewer, but start and meet later. The line
+// (measured, us with four / sixteen):
+//   * rows of whole vectors: above three trips of four wavefronts, 48 KB (9 x 2048 4.5 / 5.4, 256 x 128 4.8 / 5.6, 52 KB
+//     even, 31 x 4096 9.1 / 7.5); up to 32 blocks, where lanes meet in one or two words of the bitmap, 104 KB (544 x 32
+//     4.7 / 5.5, 2048 x 32 6.2 / 6.8, 4064 x 32 8.2 / 7.9);
+//   * other rows, whose deposits wrap: above 32 KB (48 x 344 5.2 / 5.7, 36 KB even, 256 x 344 7.6 / 7.0); below 72 blocks from
+//     the second trip on (1024 x 17 8.9 / 7.0, 267 x 65 6.4 / 6.0);
+//   * columns that repeat within a trip of sixteen wavefronts only, above 20 KB (5 x 4095 5.2 / 5.4, 24 KB even,
+//     32 x 4095 17 / 8.1).
+constexpr long one_wg_wide_from(long nb, bool wide) {
+    const long kb = nb % 16 == 0 ? (nb <= 32 ? 104 : 48) : wide ? 20 : nb < 72 ? 16 : 32;
+    return kb << 10;
+}
 template <int OT>
 __global__ __launch_bounds__(OT) void compact_flat_one_kernel(const uint8_t* __restrict__ mask, long n_tok,
                                                               long nb, int lead, int period,
@@ -601,7 +612,7 @@ extern "C" int comet_compact_mask(comet_ctx* ctx, const uint8_t* mask, int64_t n
         return COMET_OK;
     }
     if (p.path == PATH_FLAT_ONE) {
-        const bool many = n_tok * nb > 16l * FLAT_VEC;
+        const bool many = n_tok * nb > one_wg_wide_from((long)nb, wide);
         hipLaunchKernelGGL(many ? compact_flat_one_kernel<FLAT_WIDE * CT> : compact_flat_one_kernel<CT>, dim3(1),
                            dim3(many ? FLAT_WIDE * CT : CT), 0, ctx->stream, mask, (long)n_tok, (long)nb, lead,
                            wide && !many ? 0 : period, blk_idx, n_blk_dev);

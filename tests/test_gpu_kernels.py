@@ -259,6 +259,23 @@ def test_compact_chunk_starts(ctx, n_tok, nb, density):
     assert int(n.item()) == len(want) and np.array_equal(idx[:len(want)].cpu().numpy(), want)
 
 
+# One workgroup of four or of sixteen wavefronts, either side of each line between them.
+@pytest.mark.parametrize("n_tok,nb", [(1024, 48), (1025, 48), (12, 4096), (13, 4096), (3328, 32), (3329, 32), (95, 344), (96, 344),
+                                      (20, 1001), (5, 4095), (6, 4095), (5, 1025), (20, 1025), (292, 56), (293, 56), (963, 17), (964, 17),
+                                      (3, 4095), (16385, 1), (131072, 1)])
+@pytest.mark.parametrize("lead", [0, 5])
+def test_compact_one_workgroup(ctx, n_tok, nb, lead):
+    print("[gpu-kernels] compact, one workgroup %d x %d from byte %d" % (n_tok, nb, lead), flush=True)
+    flags = (rng.uniform_u64(9 + nb, 1, n_tok * nb) < np.uint64(2 ** 64 // 100)).astype(np.uint8)
+    flags[-1] = 255
+    buf = torch.full((n_tok * nb + 32,), 7, dtype=torch.uint8, device="cuda")      # flags around the mask count for nothing
+    mask = buf[lead:lead + n_tok * nb].view(n_tok, nb)
+    mask.copy_(torch.from_numpy(flags.reshape(n_tok, nb)))
+    idx, n = ctx.compact_mask(mask)
+    want = np.nonzero(flags.reshape(n_tok, nb).any(axis=0))[0]
+    assert int(n.item()) == len(want) and np.array_equal(idx[:len(want)].cpu().numpy(), want)
+
+
 # Members of a grouped call that name the same opened activations (whole tiles and ragged ones of the packing kernel).
 @pytest.mark.parametrize("kind", ["somm", "simm"])
 @pytest.mark.parametrize("m,k", [(65, 64), (130, 95), (256, 192)])
