@@ -28,7 +28,7 @@ struct GemmParams {
     int w_planes;   // B_i and F are digit planes (comet_open_weight_planes); ldb / ldf = their columns
     const u64* C;
     u64* Z;        long ldz;
-    int w_nt;       // weight words are read past the caches (see Loader::load_word)
+    int w_nt;       // weight words are read past the caches (see words_past_caches)
     // packed digit planes of [E | A']
     unsigned char* xp;
     int mpad;       // rows of xp, multiple of 128

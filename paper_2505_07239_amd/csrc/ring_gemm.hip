@@ -475,7 +475,6 @@ void place_in_workspace(GemmParams& p, void* ws) {
     p.ks_cap = (p.kc_cap + KSTEP - 1) / KSTEP;
     p.xstep[0] = 0;
     p.xstep[1] = p.ks_cap;
-    p.w_nt = 2ll * 8 * p.kc_cap * p.n_cap > (320ll << 20);     // both weight operands (see Loader::load_word)
     p.bs_shift = -1;
     for (int sh = 0; sh < 30; ++sh)
         if (p.bs == (1 << sh)) p.bs_shift = sh;
@@ -498,6 +497,21 @@ int planes_narrow_bn(const comet_ctx* ctx, const GemmParams& p) {
     if (p.tmask) return pairs >= (p.m <= 64 ? 24 : 32) ? 128 : 64;
     if (p.m <= 64 || pairs < 32 || (tiles % 64 == 0 && pairs < 256)) return 64;
     return 128;
+}
+
+// Are weight words read past the caches?  Words well beyond the 256 MB memory-side cache only push out what is
+// still needed there; smaller ones may still lie in it from the call that wrote them.  The line lies
+// at 320 MB of B_i and F together: 260 MB took 76 -> 72 us with ordinary loads (k = 4096, 16 rows), 400 MB
+// 97 -> 91 us without (16 rows), 106 -> 92 us (32), 688 MB 175 -> 162 us (32), 390 -> 371 us (128).
+// Several row tiles read the same words and count on the caches between them.  It does no harm where they sweep
+// side by side and meet in L2 (688 MB: 256 rows 748 -> 737 us past the caches, 320 rows 1065 -> 1034, 512 rows 1475 -> 1456),
+// but three row tiles of 64, out of step with the workgroups of an XCD, go back to memory (129 rows 552 -> 585, 192
+// rows 571 -> 612), tall products gain nothing (1024 rows, gathered, 2636 -> 2734) and with step lists the row tiles go separate ways
+// (256 tokens of one request 737 -> 796, of four 343 -> 342, 512 of one 1458 -> 1558).
+// Neuron-major words and gathered blocks that are no power of two have ordinary loads throughout.
+bool words_past_caches(const GemmParams& p) {
+    if (2ll * 8 * p.kc_cap * p.n_cap <= (320ll << 20)) return false;
+    return p.tmask ? p.m <= 64 : p.m <= 128 || (p.m > 192 && p.m <= 768);
 }
 
 int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t ws_bytes) {
@@ -555,6 +569,7 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
     // per-token row sets: 64-row tiles follow the row sets more closely
     else if (p.tmask) bm = 64;
     plan(bm);
+    p.w_nt = words_past_caches(p);
     // a decoding batch on weight planes: the kernel that streams the planes wavefront by wavefront
     const bool fewrow = p.w_planes && p.m <= COMET_FEWROW_MAX_ROWS && !p.w_tr && !p.row_comp && !p.tmask &&
                         ctx->skinny_mode != 1 && ctx->gemm_tile != 2;
@@ -608,8 +623,7 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
         p.step_cnt = base;
         p.step_off = base + t32;
         p.step_list = base + 2 * t32 + 1;
-        const unsigned tiles_m = (unsigned)((p.m + bm - 1) / bm);
-        hipLaunchKernelGGL(step_list_kernel, dim3(tiles_m), dim3(SLT), 0, ctx->stream, p, bm);
+        hipLaunchKernelGGL(step_list_kernel, dim3((unsigned)((p.m + bm - 1) / bm)), dim3(SLT), 0, ctx->stream, p, bm);
         COMET_LAUNCH_CHECK(ctx, what);
     }
     return launch(bm);

@@ -277,10 +277,7 @@ struct Loader {
                      : "memory", "m0");
     }
 
-    // NT: past the caches.  Weight words well beyond the 256 MB memory-side cache only push out what is
-    // still needed there; smaller ones may still lie in it from the call that wrote them.  The line lies
-    // at 320 MB of B_i and F together: 260 MB took 76 -> 72 us with ordinary loads (k = 4096, 16 rows), 400 MB
-    // 97 -> 91 us without (16 rows), 106 -> 92 us (32), 688 MB 175 -> 162 us (32), 390 -> 371 us (128).
+    // NT: past the caches (words_past_caches() in ring_gemm.hip)
     static __device__ __forceinline__ u64 load_word(const u64* q) {
         if (NT) return __builtin_nontemporal_load(q);
         return *q;
@@ -323,12 +320,7 @@ struct Loader {
         }
         const int kk = (k0 + E) < kc ? (k0 + E) : kc - 1;
         int row = kk;
-        if (GMODE == GATHER_POW2) {
-            // B_i rows are the kept neurons; bs is a power of two >= 8, so an octet of compact
-            // rows lies inside one block (g0 is its first row, set by begin()); F rows are compact
-            const int rg = g0[J] + E;
-            row = rg + ((kk - rg) & -h2);
-        } else if (GMODE == GATHER_ANY) {
+        if (GMODE == GATHER_ANY) {
             const int blk = kk / p.bs;
             const long st = block_start(p, blk);
             row = h2 ? kk : (int)(st < 0 ? 0 : st) + (kk - blk * p.bs);

@@ -136,6 +136,14 @@ def test_planes_narrow_tile_choice(ctx, kind, m, k, n):
     check_columns(ctx, kind, m, k, n, "planes")
 
 
+# Weight words beyond 320 MB, read past the caches up to 128 rows and from 193 to 768.
+@pytest.mark.parametrize("kind", ["somm", "simm"])
+@pytest.mark.parametrize("m", [9, 33, 64, 128, 129, 192, 193, 300, 768, 769])
+def test_words_beyond_the_cache(ctx, kind, m):
+    k, n = (2048, 10512) if kind == "somm" else (10512, 2048)
+    check_columns(ctx, kind, m, k, n, "words")
+
+
 # The 32 x 128 tile, which plain calls take only with the few-row kernels switched off.
 @pytest.mark.parametrize("kind", ["somm", "simm"])
 @pytest.mark.parametrize("m,other", [(1, 31), (9, 33), (31, 64), (32, 95), (32, 300)])
