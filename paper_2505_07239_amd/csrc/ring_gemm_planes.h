@@ -193,11 +193,18 @@ struct PlaneStage {
 // acc += a b.  Written out so that the accumulators stay where they are, in the 256 accumulation
 // registers: from the builtin the compiler builds a three-address form, permutes the accumulators
 // around the loop and spills fragments.  (The same accumulator is not used again for at least four
-// instructions, and mfma_done() stands between the last of them and the first other use.)
+// instructions, and mfma_done() ends the pair: the compiler does not know that these are matrix instructions and adds no
+// wait of its own before another use of their results.)
 __device__ __forceinline__ void mfma_acc(v4i& acc, const v4i& a, const v4i& b) {
     asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
-__device__ __forceinline__ void mfma_done() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+// Wait states from the last matrix instruction to any other access to its result: eight (four passes), BETWEEN of them
+// taken by instructions that follow it. They stand at the end of the loop body and not behind the loop, where a
+// register copy, which is no memory access, could still be placed ahead of them; the matrix pipe is busy meanwhile.
+template <int BETWEEN>
+__device__ __forceinline__ void mfma_done() {
+    asm volatile("s_nop %0" ::"n"(7 - BETWEEN) : "memory");
+}
 
 template <class T, int KIND, int GMODE, bool LISTED, int... Ms>
 __device__ __forceinline__ void plane_pair(std::integer_sequence<int, Ms...>, const GemmParams& p,
@@ -248,6 +255,7 @@ __device__ __forceinline__ void plane_pair(std::integer_sequence<int, Ms...>, co
 #pragma unroll
     for (int i = 0; i < T::MT; ++i) a[0][i] = st.a_load(i);
     __builtin_amdgcn_sched_barrier(0);
+    mfma_done<T::MT>();
 }
 
 // One workgroup's share of a product: segment by segment, the main loop and the write-out of the
@@ -316,7 +324,6 @@ __device__ __forceinline__ void plane_sweep(const GemmParams& p, const Geometry&
         }
         // the transfers requested for pairs beyond the last are redundant; let them land before the
         // stages are reused
-        mfma_done();
         wait_and_barrier<0>();
 
         // The only writer of a tile (own) stores Z = C + sum (Z += sum for a later segment of a long
