@@ -345,7 +345,8 @@ def roofline_of(layer, wname, timing, skinny_forced, probes):
                      "several products)"}
         if probes:
             r["frac_of_measured_mfma_issue"] = ach / probes["mfma_i8_issue_TOPs"]
-            r["frac_of_measured_mfma_issue_random_operands"] = ach / probes["mfma_i8_issue_random_operands_TOPs"]
+            r["frac_of_measured_mfma_issue_random_operands"] = ach / probes[
+                "mfma_i8_issue_random_operands_16x16x64_TOPs" if layer.planes else "mfma_i8_issue_random_operands_TOPs"]
     r.update(common)
     return r
 
@@ -758,6 +759,10 @@ def micro(ctx, layer):
     # the chip clocks down under the extra switching power
     t = timed(lambda: ctx.probe_mfma_i8(1024, 2000, True), reps=10)
     out["mfma_i8_issue_random_operands_TOPs"] = 2.0 * macs / t / 1e12
+    # and through the instruction of the kernel on weight planes (16 x 16 x 64 instead of 32 x 32 x 32)
+    macs = ctx.probe_mfma_i8(1024, 4000, 2)
+    t = timed(lambda: ctx.probe_mfma_i8(1024, 4000, 2), reps=10)
+    out["mfma_i8_issue_random_operands_16x16x64_TOPs"] = 2.0 * macs / t / 1e12
     macs = ctx.probe_valu_mac64(2048, 2000)
     t = timed(lambda: ctx.probe_valu_mac64(2048, 2000), reps=5)
     out["valu_mac64_Gops"] = 2.0 * macs / t / 1e9
@@ -791,7 +796,7 @@ def main():
                     help="time replays of one step captured in a HIP graph instead of eager calls")
     ap.add_argument("--gemm-chunk", type=int, default=0, help="tuning sweep: scheduling slice length")
     ap.add_argument("--gemm-grid", type=int, default=0, help="tuning sweep: workgroups per launch")
-    ap.add_argument("--gemm-tile", type=int, default=0, help="tuning sweep: 2 = 64x64 tile")
+    ap.add_argument("--gemm-tile", type=int, default=0, help="tuning sweep: 2 = a tile of 64 rows")
     ap.add_argument("--skinny", type=int, default=0, help="tuning sweep: 1 = matrix cores even for m <= 8")
     ap.add_argument("--skinny-slices", type=int, default=0, help="tuning sweep: contraction slices of the m <= 8 kernel")
     args = ap.parse_args()

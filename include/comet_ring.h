@@ -423,7 +423,9 @@ int comet_timing_end(comet_ctx* ctx, double* total_ms, int* launches);
  * each.  random_operands = 0: small constant operands; 1: uniformly random
  * operand bytes (the digits of secret shares are uniformly random; the same
  * instruction stream then draws more power and the chip clocks down, so this
- * is the rate a real kernel can approach).  out (device, blocks*256 int32)
+ * is the rate a real kernel can approach); 2: the same random bytes through
+ * the 16 x 16 x 64 instruction, which the share calls on weight planes use (the
+ * others: 32 x 32 x 32).  out (device, blocks*256 int32)
  * keeps the results alive.  Returns the number of int8 multiply-accumulates
  * issued through *macs (host). */
 int comet_probe_mfma_i8(comet_ctx* ctx, int blocks, int iters, int random_operands, int32_t* out,

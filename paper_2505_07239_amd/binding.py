@@ -555,7 +555,7 @@ class Context:
         self._check(self.lib.comet_timing_end(self.h, ctypes.byref(ms), ctypes.byref(n)))
         return ms.value, n.value
 
-    def probe_mfma_i8(self, blocks: int, iters: int, random_operands: bool = False) -> float:
+    def probe_mfma_i8(self, blocks: int, iters: int, random_operands: int = 0) -> float:
         out = torch.empty(blocks * 256, dtype=torch.int32, device="cuda:%d" % self.device)
         macs = ctypes.c_double()
         self._sync_stream()

@@ -6,7 +6,6 @@
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int PROBE_MFMA_PER_ITER = 8;
 
@@ -16,15 +15,17 @@ __device__ __forceinline__ u64 probe_mix(u64 z) {
     return z ^ (z >> 31);
 }
 
-// Eight independent accumulators, one v_mfma_i32_32x32x32_i8 each per iteration, every one
-// with its own operand pair.  RANDOM = false: small constants (most operand bits are zero);
+// Eight independent accumulators, one v_mfma_i32_32x32x32_i8 (SMALL: v_mfma_i32_16x16x64_i8, half the
+// multiply-adds) each per iteration, every one with its own operand pair.  RANDOM = false: small constants (most operand bits are zero);
 // RANDOM = true: uniformly random bytes, which is what the digits of secret shares look like.
 // The instruction stream is the same; the second draws far more power, and the chip lowers
 // its clock accordingly, so the two rates bracket what a real kernel can reach.
-template <bool RANDOM>
+template <bool RANDOM, bool SMALL>
 __global__ __launch_bounds__(256) void probe_mfma_kernel(int iters, int* __restrict__ out) {
+    constexpr int ACC = SMALL ? 4 : 16;
+    typedef int vacc __attribute__((ext_vector_type(ACC)));
     v4i a[PROBE_MFMA_PER_ITER], b[PROBE_MFMA_PER_ITER];
-    v16i acc[PROBE_MFMA_PER_ITER];
+    vacc acc[PROBE_MFMA_PER_ITER];
 #pragma unroll
     for (int j = 0; j < PROBE_MFMA_PER_ITER; ++j) {
         if (RANDOM) {
@@ -37,18 +38,23 @@ __global__ __launch_bounds__(256) void probe_mfma_kernel(int iters, int* __restr
             b[j] = v4i{4, 5, (int)blockIdx.x, 7 + j};
         }
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[j][e] = j;
+        for (int e = 0; e < ACC; ++e) acc[j][e] = j;
     }
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int j = 0; j < PROBE_MFMA_PER_ITER; ++j)
-            acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[j], b[j], acc[j], 0, 0, 0);
+        for (int j = 0; j < PROBE_MFMA_PER_ITER; ++j) {
+            // (written out: from the builtin the compiler moves the accumulators around the loop)
+            if constexpr (SMALL) asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(acc[j]) : "v"(a[j]), "v"(b[j]));
+            else acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[j], b[j], acc[j], 0, 0, 0);
+        }
+        // (the wait before another access to the results; the other wavefronts of the SIMD fill it)
+        if constexpr (SMALL) asm volatile("s_nop 7" ::: "memory");
     }
     int r = 0;
 #pragma unroll
     for (int j = 0; j < PROBE_MFMA_PER_ITER; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) r ^= acc[j][e];
+        for (int e = 0; e < ACC; ++e) r ^= acc[j][e];
     out[blockIdx.x * 256 + threadIdx.x] = r;
 }
 
@@ -82,12 +88,12 @@ int comet_probe_mfma_i8(comet_ctx* ctx, int blocks, int iters, int random_operan
         return comet_fail(ctx, COMET_EINVAL, "comet_probe_mfma_i8: bad argument");
     comet_device_guard guard(ctx);
     if (!guard.ok) return comet_fail(ctx, COMET_EDEVICE, "comet_probe_mfma_i8: cannot select device");
-    if (random_operands)
-        hipLaunchKernelGGL(probe_mfma_kernel<true>, dim3(blocks), dim3(256), 0, ctx->stream, iters, out);
-    else
-        hipLaunchKernelGGL(probe_mfma_kernel<false>, dim3(blocks), dim3(256), 0, ctx->stream, iters, out);
+    const bool small = random_operands == 2;
+    hipLaunchKernelGGL((small ? probe_mfma_kernel<true, true> : random_operands ? probe_mfma_kernel<true, false>
+                                                                                : probe_mfma_kernel<false, false>),
+                       dim3(blocks), dim3(256), 0, ctx->stream, iters, out);
     COMET_LAUNCH_CHECK(ctx, "comet_probe_mfma_i8");
-    if (macs) *macs = (double)blocks * 4.0 * iters * PROBE_MFMA_PER_ITER * 32.0 * 32.0 * 32.0;
+    if (macs) *macs = (double)blocks * 4.0 * iters * PROBE_MFMA_PER_ITER * (small ? 16.0 * 16.0 * 64.0 : 32.0 * 32.0 * 32.0);
     return COMET_OK;
 }
 
