@@ -322,15 +322,16 @@ __device__ int list_tiles(const GemmParams& p, int BM, int BN, int* list) {
 }
 
 // One shape, or (list_b) two of them, 128 x 64 in list and the narrow tile BM x BN in list_b.
-__global__ __launch_bounds__(GT) void tile_list_kernel(GemmParams p, int BM, int BN, int* list, int* list_b, int* sel) {
+__global__ __launch_bounds__(GT) void tile_list_kernel(GemmParams p, int BM, int BN, int* list, int* list_b, int* sel,
+                                                       int percent) {
     if (!list_b) {
         (void)list_tiles(p, BM, BN, list);
         return;
     }
     const long a = list_tiles(p, 128, 64, list), b = list_tiles(p, BM, BN, list_b);
-    // the second shape runs when it computes at most 80 % of the other's area
+    // the second shape runs when it computes less than this share of the other's area
     // (smaller tiles follow the block structure more closely but reuse operands less)
-    if (threadIdx.x == 0) *sel = 5l * b * BM * BN < 4l * a * 128 * 64 ? 1 : 0;
+    if (threadIdx.x == 0) *sel = 100l * b * BM * BN < (long)percent * a * 128 * 64 ? 1 : 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -489,11 +490,13 @@ void place_in_workspace(GemmParams& p, void* ws) {
 // 1664 97 -> 94); so does a multiple of 64 tiles, whose workgroup shares line up with the tiles, up to 256 pairs
 // (192 x 1664 x 4096 96 -> 82, 320 x 1664 x 4096 139 -> 133).  With step lists the row tiles do not sweep side by side: 128 columns from 32 pairs
 // on (512 tokens x 344 blocks of 32, n = 1024 334 -> 278), with a single row tile from 24 (33 x 344 of 16, n = 2560 85 -> 75).
-// Result blocks keep 64: the finer tile follows them more closely (129 x 216 of 32, k = 1024 86 -> 68).
+// Result blocks leave most tiles out, and the finer tile follows them more closely: 128 columns from 144 pairs, counted
+// over all tiles, and 2048 contraction words on only (129 x 400 of 16, k = 4096 209 -> 179, 129 x 563 of 16, k = 4199 572 -> 333; but
+// 512 x 344 of 32, k = 1024 155 -> 119 and 209 x 100 of 16, k = 4096 71 -> 57 with 64).
 int planes_narrow_bn(const comet_ctx* ctx, const GemmParams& p) {
     const long tiles = (long)((p.m + 63) / 64) * ((p.n_cap + 63) / 64);
     const long pairs = tiles * ((p.kc_cap + KSTEP - 1) / KSTEP) / (ctx->num_cu > 0 ? ctx->num_cu : 1);
-    if (p.row_comp) return 64;
+    if (p.row_comp) return pairs >= 144 && p.kc_cap >= 2048 ? 128 : 64;
     if (p.tmask) return pairs >= (p.m <= 64 ? 24 : 32) ? 128 : 64;
     if (p.m <= 64 || pairs < 32 || (tiles % 64 == 0 && pairs < 256)) return 64;
     return 128;
@@ -600,11 +603,14 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
         p.tile_list = list_a;
         if (bm != 128) {
             hipLaunchKernelGGL(tile_list_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, bm,
-                               bm == 64 ? narrow_bn : flat_bn, list_a, (int*)nullptr, (int*)nullptr);
+                               bm == 64 ? narrow_bn : flat_bn, list_a, (int*)nullptr, (int*)nullptr, 0);
             COMET_LAUNCH_CHECK(ctx, what);
             return launch(bm);
         }
-        hipLaunchKernelGGL(tile_list_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, 64, narrow_bn, list_a, list_b, sel);
+        // 80 % of the area; less than three quarters, what 129 to 192 rows of one component come to, for 64 x 64 on planes and
+        // long contractions (129 rows: k = 4199, 300 blocks of 16 479 -> 317 us on 128 x 64; k = 1024, 344 of 32 131 against 160)
+        const int percent = p.w_planes && narrow_bn == 64 && p.kc_cap >= 2048 ? 75 : 80;
+        hipLaunchKernelGGL(tile_list_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, 64, narrow_bn, list_a, list_b, sel, percent);
         COMET_LAUNCH_CHECK(ctx, what);
         p.tile_sel = sel;
         p.tile_sel_want = 0;

@@ -334,12 +334,14 @@ def test_somm_result_blocks_neuron_major_weights(ctx, m, k, nb, bs, groups, per_
     assert n_comp >= 1
 
 
-# Weight planes: the 32 x 128 tile (up to 32 rows), 64 x 64 (up to 64), and beyond that 128 x 64 or 64 x 64, as the
-# result blocks lie (one component, or several of some 50 rows).
+# Weight planes: the 32 x 128 tile (up to 32 rows), 64 x 64 (up to 64), and beyond that 128 x 64 or the narrow tile, as
+# the result blocks lie (one component, or several of some 50 rows).
 @pytest.mark.parametrize("m,k,nb,bs,groups,per_tok,b_full", [(9, 64, 24, 16, 3, 3, True), (32, 95, 24, 16, 2, 3, False),
                                                              (40, 70, 20, 32, 4, 2, True), (64, 33, 20, 7, 1, 3, True),
                                                              (129, 130, 16, 16, 1, 3, True), (260, 64, 40, 32, 5, 2, False),
-                                                             (260, 31, 24, 48, 1, 4, True), (300, 160, 30, 16, 6, 3, True)])
+                                                             (260, 31, 24, 48, 1, 4, True), (300, 160, 30, 16, 6, 3, True),
+                                                             # long contractions: three quarters of the area; 64 x 128
+                                                             (129, 2048, 12, 16, 1, 3, True), (200, 2080, 150, 64, 4, 5, False)])
 def test_somm_result_blocks_weight_planes(ctx, m, k, nb, bs, groups, per_tok, b_full):
     say("somm blocks, weight planes m=%d k=%d nb=%d bs=%d groups=%d" % (m, k, nb, bs, groups))
     n_comp = _somm_blocks_case(ctx, 460 + m, m, k, nb, bs, groups, per_tok, spare_rows=3,
