@@ -8,10 +8,11 @@
 // Paths:
 //   small (one token row, nb <= 4096): one 256-thread workgroup does everything in
 //     one launch; this is the shared FFN mask (a few hundred blocks), latency-bound.
-//   large: three wait-free launches.  (1) each lane ORs 16 adjacent flags over
+//   large: two or three wait-free launches.  (1) each lane ORs 16 adjacent flags over
 //     the tokens into a 16-bit word and each workgroup stores its popcount;
-//     (2) one workgroup scans the workgroup counts; (3) each workgroup scans its
-//     own words with wavefront prefix sums and writes the indices through LDS.
+//     (2) beyond 256 workgroups one scans the counts, up to there each adds up those
+//     ahead of it; (3) each workgroup scans its own words with wavefront prefix
+//     sums and writes the indices through LDS.
 //     The mask bytes are read exactly once; passes 2 and 3 touch only the
 //     bit-packed words (1/8 of a byte per flag) and the outputs.
 //   several token rows: the OR over the tokens is a column-wise reduction of a

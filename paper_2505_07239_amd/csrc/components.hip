@@ -16,9 +16,10 @@
 //     part are sorted by (component, own number) with a stable one-bit-per-pass radix split.
 // It is a chain of LDS accesses and barriers, so what counts is how many there are: two rounds for a batch
 // of requests, one bit word of a token per thread and step, few atomics, and as many splits
-// as the component numbers have bits.  256 tokens x 344 blocks in four requests: 70 -> 40 us,
-// 64 x 96 in one: 34 -> 15 us (label propagation between tokens and blocks, numbering by one thread and a
-// bitonic sort before).  What is left: 5 us of mask reads, 12 us of edges, 8 us of sorting.
+// as the component numbers have bits.  256 tokens x 344 blocks in four requests, 15 % of the blocks: 70 -> 40 us
+// (10 %: 51 -> 26), 64 x 96 in one: 34 -> 15 us (label propagation between tokens and blocks,
+// numbering by one thread and a bitonic sort before).  The mask reads take 5 us and the sorting 8; the rest goes with
+// the number of edges.
 // The result is unique (the partition) up to the order of listing, which is fixed as above.
 //
 // Graphs beyond the one-workgroup limits (element-granular masks at FFN width: hundreds of tokens

@@ -17,7 +17,9 @@ typedef u64 u64x2 __attribute__((ext_vector_type(2)));
 // can hold until then is stored through the caches (KEEP); a larger one would only push out what is
 // still to be read, and streams past them.  Masking both shares of a matrix and opening them took
 // 98 -> 85 us at 64 MB a matrix, 192 -> 174 us at 128 MB, 286 -> 270 us at 192 MB, and 477 -> 515 us
-// at 320 MB with every store cached: the line lies at 192 MB.
+// at 320 MB with every store cached: the line lies at 192 MB.  Small matrices stay in L2 (2 MB 11.5 -> 7.7 us, 6 MB 16.2 ->
+// 13.7).  Between the two caches, 6 to 24 MB, it depends on what follows: masking twice and opening 20.9 -> 22.0 us at
+// 12 MB, gathering twice and packing 24.2 -> 26.6, gathering, opening and a product on words 53.1 -> 48.8.
 constexpr size_t KEEP_BYTES = (size_t)192 << 20;
 template <bool KEEP, class T>
 __device__ __forceinline__ void store_result(T v, T* p) {
