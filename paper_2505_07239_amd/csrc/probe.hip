@@ -16,7 +16,8 @@ __device__ __forceinline__ u64 probe_mix(u64 z) {
 }
 
 // Eight independent accumulators, one v_mfma_i32_32x32x32_i8 (SMALL: v_mfma_i32_16x16x64_i8, half the
-// multiply-adds) each per iteration, every one with its own operand pair.  RANDOM = false: small constants (most operand bits are zero);
+// multiply-adds) each per iteration, every one with its own operand pair.
+// RANDOM = false: small constants (most operand bits are zero);
 // RANDOM = true: uniformly random bytes, which is what the digits of secret shares look like.
 // The instruction stream is the same; the second draws far more power, and the chip lowers
 // its clock accordingly, so the two rates bracket what a real kernel can reach.

@@ -481,18 +481,18 @@ void place_in_workspace(GemmParams& p, void* ws) {
         if (p.bs == (1 << sh)) p.bs_shift = sh;
 }
 
-// Columns of the 64-row tile on weight planes: 64, or 128 for large products.  A pair of contraction steps takes
-// a workgroup 1.1 us on 64 x 64 and 2.2 us on 64 x 128, which reads half of its operands from LDS less
-// often.  What decides is how many 64 x 64 pairs there are per compute unit: below 32 of them
-// the finer pieces fill the chip better (128 x 768 x 320 19 -> 16 us, 64 x 1664 x 4096 45 -> 38, 192 x
-// 2560 x 640 40 -> 33), from there on the wider tile is ahead (320 x 4096 x 960 101 -> 83, 448 x 4096 x 2560 342 -> 279).
-// Exceptions, as measured: a single row tile reads every weight unit once and stays with 64 (64 x 11008 x
-// 1664 97 -> 94); so does a multiple of 64 tiles, whose workgroup shares line up with the tiles, up to 256 pairs
-// (192 x 1664 x 4096 96 -> 82, 320 x 1664 x 4096 139 -> 133).  With step lists the row tiles do not sweep side by side: 128 columns from 32 pairs
-// on (512 tokens x 344 blocks of 32, n = 1024 334 -> 278), with a single row tile from 24 (33 x 344 of 16, n = 2560 85 -> 75).
-// Result blocks leave most tiles out, and the finer tile follows them more closely: 128 columns from 144 pairs, counted
-// over all tiles, and 2048 contraction words on only (129 x 400 of 16, k = 4096 209 -> 179, 129 x 563 of 16, k = 4199 572 -> 333; but
-// 512 x 344 of 32, k = 1024 155 -> 119 and 209 x 100 of 16, k = 4096 71 -> 57 with 64).
+// Columns of the 64-row tile on weight planes: 64, or 128 for large products.  A pair of contraction steps takes a
+// workgroup 1.1 us on 64 x 64 and 2.2 us on 64 x 128, which reads half of its operands from LDS less often.  What
+// decides is how many 64 x 64 pairs there are per compute unit: below 32 of them the finer pieces fill the chip
+// better (128 x 768 x 320 19 -> 16 us, 64 x 1664 x 4096 45 -> 38, 192 x 2560 x 640 40 -> 33), from there on the wider
+// tile is ahead (320 x 4096 x 960 101 -> 83, 448 x 4096 x 2560 342 -> 279). Exceptions, as measured: a single row
+// tile reads every weight unit once and stays with 64 (64 x 11008 x 1664 97 -> 94); so does a multiple of 64 tiles,
+// whose workgroup shares line up with the tiles, up to 256 pairs (192 x 1664 x 4096 96 -> 82, 320 x 1664 x 4096 139
+// -> 133).  With step lists the row tiles do not sweep side by side: 128 columns from 32 pairs on (512 tokens x 344
+// blocks of 32, n = 1024 334 -> 278), with a single row tile from 24 (33 x 344 of 16, n = 2560 85 -> 75). Result
+// blocks leave most tiles out, and the finer tile follows them more closely: 128 columns from 144 pairs, counted over
+// all tiles, and 2048 contraction words on only (129 x 400 of 16, k = 4096 209 -> 179, 129 x 563 of 16, k = 4199 572
+// -> 333; but 512 x 344 of 32, k = 1024 155 -> 119 and 209 x 100 of 16, k = 4096 71 -> 57 with 64).
 int planes_narrow_bn(const comet_ctx* ctx, const GemmParams& p) {
     const long tiles = (long)((p.m + 63) / 64) * ((p.n_cap + 63) / 64);
     const long pairs = tiles * ((p.kc_cap + KSTEP - 1) / KSTEP) / (ctx->num_cu > 0 ? ctx->num_cu : 1);
@@ -502,16 +502,16 @@ int planes_narrow_bn(const comet_ctx* ctx, const GemmParams& p) {
     return 128;
 }
 
-// Are weight words read past the caches?  Words well beyond the 256 MB memory-side cache only push out what is
-// still needed there; smaller ones may still lie in it from the call that wrote them.  The line lies
-// at 320 MB of B_i and F together: 260 MB took 76 -> 72 us with ordinary loads (k = 4096, 16 rows), 400 MB
-// 97 -> 91 us without (16 rows), 106 -> 92 us (32), 688 MB 175 -> 162 us (32), 390 -> 371 us (128).
-// Several row tiles read the same words and count on the caches between them.  It does no harm where they sweep
-// side by side and meet in L2 (688 MB: 256 rows 748 -> 737 us past the caches, 320 rows 1065 -> 1034, 512 rows 1475 -> 1456),
-// but three row tiles of 64, out of step with the workgroups of an XCD, go back to memory (129 rows 552 -> 585, 192
-// rows 571 -> 612), tall products gain nothing (1024 rows, gathered, 2636 -> 2734) and with step lists the row tiles go separate ways
-// (256 tokens of one request 737 -> 796, of four 343 -> 342, 512 of one 1458 -> 1558).
-// Neuron-major words and gathered blocks that are no power of two have ordinary loads throughout.
+// Are weight words read past the caches?  Words well beyond the 256 MB memory-side cache only push out what is still
+// needed there; smaller ones may still lie in it from the call that wrote them.  The line lies at 320 MB of B_i and F
+// together: 260 MB took 76 -> 72 us with ordinary loads (k = 4096, 16 rows), 400 MB 97 -> 91 us without (16 rows),
+// 106 -> 92 us (32), 688 MB 175 -> 162 us (32), 390 -> 371 us (128). Several row tiles read the same words and count
+// on the caches between them.  It does no harm where they sweep side by side and meet in L2 (688 MB: 256 rows 748 ->
+// 737 us past the caches, 320 rows 1065 -> 1034, 512 rows 1475 -> 1456), but three row tiles of 64, out of step with
+// the workgroups of an XCD, go back to memory (129 rows 552 -> 585, 192 rows 571 -> 612), tall products gain nothing
+// (1024 rows, gathered, 2636 -> 2734) and with step lists the row tiles go separate ways (256 tokens of one request
+// 737 -> 796, of four 343 -> 342, 512 of one 1458 -> 1558). Neuron-major words and gathered blocks that are no power
+// of two have ordinary loads throughout.
 bool words_past_caches(const GemmParams& p) {
     if (2ll * 8 * p.kc_cap * p.n_cap <= (320ll << 20)) return false;
     return p.tmask ? p.m <= 64 : p.m <= 128 || (p.m > 192 && p.m <= 768);
@@ -607,10 +607,12 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
             COMET_LAUNCH_CHECK(ctx, what);
             return launch(bm);
         }
-        // 80 % of the area; less than three quarters, what 129 to 192 rows of one component come to, for 64 x 64 on planes and
-        // long contractions (129 rows: k = 4199, 300 blocks of 16 479 -> 317 us on 128 x 64; k = 1024, 344 of 32 131 against 160)
+        // 80 % of the area; less than three quarters, what 129 to 192 rows of one component come to, for 64 x 64 on
+        // planes and long contractions (129 rows: k = 4199, 300 blocks of 16 479 -> 317 us on 128 x 64; k = 1024, 344 of 32
+        // 131 against 160)
         const int percent = p.w_planes && narrow_bn == 64 && p.kc_cap >= 2048 ? 75 : 80;
-        hipLaunchKernelGGL(tile_list_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, 64, narrow_bn, list_a, list_b, sel, percent);
+        hipLaunchKernelGGL(tile_list_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, 64, narrow_bn, list_a, list_b, sel,
+                           percent);
         COMET_LAUNCH_CHECK(ctx, what);
         p.tile_sel = sel;
         p.tile_sel_want = 0;

@@ -9,8 +9,9 @@
 //
 // What bounds it is power.  Secret shares are uniformly random words, and on random operands the chip
 // lowers its clock: in a register-resident loop (comet_probe_mfma_i8) 32x32x32 sustains 3.3 POP/s and
-// 16x16x64 sustains 3.8 POP/s (32x32x32 on constants: 4.2 to 4.8), so the smaller instruction is used although it reads its operands from
-// registers twice as often.  The second lever is the data movement beside the multipliers:
+// 16x16x64 sustains 3.8 POP/s (32x32x32 on constants: 4.2 to 4.8), so the smaller instruction is used
+// although it reads its operands from registers twice as often.  The second lever is the data movement
+// beside the multipliers:
 //   * activation units go from memory (L2, for the most part) straight into the registers of the
 //     wavefront that multiplies them.  The digit pairs are walked with the activation digit
 //     descending, so a digit's fragments are used in one run of instructions and then dead: its
@@ -25,10 +26,10 @@
 //     reads are older; the transfers for pair n + 2 then overwrite it.  No instruction waits for
 //     something requested shortly before.
 // Measured against 32x32x32 with both operands staged in LDS (three stages, one barrier per 32 words):
-// 512 x 11008 x 4096 dense 1213 -> 1057 us (3.1 POP/s, matrix pipe busy 81 % of the cycles at 1.87
-// GHz: profiles/bench_c5_d100_mfma_counters.md), four products of 256 x 4096 x 1664 in one launch 413 -> 365 us, one of them 128 -> 111 us a
-// call.  The order of the digit pairs and of the two operands does not matter to the power (twelve
-// orders in a register-resident loop agree within 3 %).
+// 512 x 11008 x 4096 dense 1213 -> 1057 us (3.1 POP/s, matrix pipe busy 81 % of the cycles at 1.87 GHz:
+// profiles/bench_c5_d100_mfma_counters.md), four products of 256 x 4096 x 1664 in one launch 413 -> 365
+// us, one of them 128 -> 111 us a call.  The order of the digit pairs and of the two operands does not
+// matter to the power (twelve orders in a register-resident loop agree within 3 %).
 #pragma once
 
 #include "ring_gemm_kernel.h"

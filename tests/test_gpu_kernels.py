@@ -206,7 +206,8 @@ def check_masked(ctx, m, nb, bs, n, fmt, per_block, full=True, replays=0):
         assert np.array_equal(down(z), want), "eager after replay %d" % rep
 
 
-# Per-token row sets on weight planes: the 32 x 128, 64 x 64 and (from 32 pairs per compute unit on, 24 with one row tile) 64 x 128 tiles.
+# Per-token row sets on weight planes: the 32 x 128, 64 x 64 and (from 32 pairs per compute unit on, 24 with one
+# row tile) 64 x 128 tiles.
 @pytest.mark.parametrize("m,nb,bs,n", [(9, 12, 16, 40), (32, 30, 32, 130), (33, 12, 16, 64), (64, 20, 48, 65),
                                        (129, 16, 16, 200), (260, 40, 32, 96), (64, 512, 32, 768), (200, 512, 32, 257)])
 @pytest.mark.parametrize("full", [True, False])
@@ -268,9 +269,9 @@ def test_compact_chunk_starts(ctx, n_tok, nb, density):
 
 
 # One workgroup of four or of sixteen wavefronts, either side of each line between them.
-@pytest.mark.parametrize("n_tok,nb", [(1024, 48), (1025, 48), (12, 4096), (13, 4096), (3328, 32), (3329, 32), (95, 344), (96, 344),
-                                      (20, 1001), (5, 4095), (6, 4095), (5, 1025), (20, 1025), (292, 56), (293, 56), (963, 17), (964, 17),
-                                      (3, 4095), (16385, 1), (131072, 1)])
+@pytest.mark.parametrize("n_tok,nb", [(1024, 48), (1025, 48), (12, 4096), (13, 4096), (3328, 32), (3329, 32),
+                                      (95, 344), (96, 344), (20, 1001), (5, 4095), (6, 4095), (5, 1025), (20, 1025),
+                                      (292, 56), (293, 56), (963, 17), (964, 17), (3, 4095), (16385, 1), (131072, 1)])
 @pytest.mark.parametrize("lead", [0, 5])
 def test_compact_one_workgroup(ctx, n_tok, nb, lead):
     print("[gpu-kernels] compact, one workgroup %d x %d from byte %d" % (n_tok, nb, lead), flush=True)
