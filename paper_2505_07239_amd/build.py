@@ -10,14 +10,14 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcomet_ring.so")
-# the variants of the matrix-core kernel come first: they take longest to compile
-SOURCES = ["ring_gemm_tile_128x64_own.hip", "ring_gemm_planes_128x64_own.hip",
-           "ring_gemm_group_128x64.hip", "ring_gemm_group_128x64_own.hip", "ring_gemm_tile_32x256.hip", "ring_gemm_tile_32x256_listed.hip", "ring_gemm_tile_128x64.hip",
-           "ring_gemm_tile_64x64.hip", "ring_gemm_tile_64x64_listed.hip",
+# the variants of the matrix-core kernels come first: they take longest to compile
+SOURCES = ["ring_gemm_planes_128x64_own.hip", "ring_gemm_group_128x64.hip", "ring_gemm_group_128x64_own.hip",
            "ring_gemm_planes_128x64.hip", "ring_gemm_planes_64x128.hip", "ring_gemm_planes_64x128_listed.hip",
            "ring_gemm_planes_64x64.hip", "ring_gemm_planes_64x64_listed.hip",
-           "ring_gemm_planes_32x128.hip", "ring_gemm_planes_32x128_listed.hip", "ring_gemm.hip", "wplanes.hip",
-           "ring_skinny.hip", "ring_fewrow.hip", "ctx.hip", "elementwise.hip", "compact.hip", "components.hip", "glue.hip", "probe.hip"]
+           "ring_gemm_planes_32x128.hip", "ring_gemm_planes_32x128_listed.hip",
+           "ring_words_64x64.hip", "ring_words_64x64_listed.hip", "ring_tile_32x256.hip", "ring_tile_32x256_listed.hip",
+           "ring_gemm.hip", "wplanes.hip", "ring_skinny.hip", "ring_fewrow.hip", "ctx.hip", "elementwise.hip", "compact.hip",
+           "components.hip", "glue.hip", "probe.hip"]
 FLAGS = ["-O3", "-std=c++20", "--offload-arch=gfx950", "-fPIC", "-fvisibility=default",
          # the LDS-DMA helper names M0 as clobbered, which clang flags as a reserved register
          "-Wno-inline-asm",

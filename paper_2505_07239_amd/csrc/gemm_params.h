@@ -56,7 +56,6 @@ struct GemmParams {
     int grid;                 // workgroups
     int tile_bm, tile_bn;     // output tile
     int own_try;              // plain product (no result blocks, no step lists, default slicing)
-    int k_rotate;             // units tile by tile; the parts of a tile take its steps in reverse order (see UnitWalk::next)
     int team;                 // group launch: workgroups form teams over the row tiles (see ring_planes_group_kernel)
     int group_n;              // members of the group launch this product is part of (0 or 1: on its own)
 };
@@ -112,6 +111,15 @@ static __device__ __forceinline__ long block_start(const GemmParams& p, int blk)
 // traffic and the matrix-core kernel's 32-row tile is faster.
 static const int COMET_SKINNY_MAX_ROWS = 8;
 int comet_launch_skinny(comet_ctx* ctx, const char* what, const GemmParams& p);
+
+// The members of a group call (one shape, one index list).
+constexpr int GROUP_MAX = COMET_SHARE_GROUP_MAX;
+struct GemmGroup {
+    int n;
+    GemmParams p[GROUP_MAX];
+};
+using GemmKernel = void (*)(GemmParams);
+using GemmGroupKernel = void (*)(GemmGroup);
 
 // Matrix-core path for at most COMET_FEWROW_MAX_ROWS activation rows with the weight side in digit
 // planes (plain products only: no result blocks, no per-token row sets): every wavefront streams

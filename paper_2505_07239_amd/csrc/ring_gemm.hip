@@ -39,14 +39,17 @@
 //                  out so that a tile is a linear copy into LDS (small operand).
 //   gemm kernel  : weight-side WORDS are loaded once as uint64 (with the block
 //                  gather folded into the addressing), split into digits and
-//                  byte-transposed in registers, staged through LDS, and fed
-//                  to v_mfma_i32_32x32x32_i8; they are never re-written to
+//                  byte-transposed in registers, and fed to the matrix
+//                  instructions through LDS (ring_words.h, ring_tile.h) or directly
+//                  (ring_fewrow.hip); they are never re-written to
 //                  memory.  Weight-side PLANES (COMET_WEIGHT_PLANES: F opened in
 //                  that format, B_i packed offline, see wplanes.hip) go to LDS
 //                  by LDS-DMA, activation planes straight into registers: a step
 //                  then holds nothing but matrix instructions and their fragment
 //                  reads (ring_gemm_planes.h).
 #include "ring_gemm_planes.h"
+#include "ring_tile.h"
+#include "ring_words.h"
 
 #include <mutex>
 
@@ -504,18 +507,12 @@ int planes_narrow_bn(const comet_ctx* ctx, const GemmParams& p) {
 
 // Are weight words read past the caches?  Words well beyond the 256 MB memory-side cache only push out what is still
 // needed there; smaller ones may still lie in it from the call that wrote them.  The line lies at 320 MB of B_i and F
-// together: 260 MB took 76 -> 72 us with ordinary loads (k = 4096, 16 rows), 400 MB 97 -> 91 us without (16 rows),
-// 106 -> 92 us (32), 688 MB 175 -> 162 us (32), 390 -> 371 us (128). Several row tiles read the same words and count
-// on the caches between them.  It does no harm where they sweep side by side and meet in L2 (688 MB: 256 rows 748 ->
-// 737 us past the caches, 320 rows 1065 -> 1034, 512 rows 1475 -> 1456), but three row tiles of 64, out of step with
-// the workgroups of an XCD, go back to memory (129 rows 552 -> 585, 192 rows 571 -> 612), tall products gain nothing
-// (1024 rows, gathered, 2636 -> 2734) and with step lists the row tiles go separate ways (256 tokens of one request
-// 737 -> 796, of four 343 -> 342, 512 of one 1458 -> 1558). Neuron-major words and gathered blocks that are no power
-// of two have ordinary loads throughout.
-bool words_past_caches(const GemmParams& p) {
-    if (2ll * 8 * p.kc_cap * p.n_cap <= (320ll << 20)) return false;
-    return p.tmask ? p.m <= 64 : p.m <= 128 || (p.m > 192 && p.m <= 768);
-}
+// together: 260 MB took 76 -> 72 us with ordinary loads (k = 4096, 16 rows), 400 MB 107 -> 98 us without (16 rows),
+// 115 -> 103 us (32), 147 -> 137 us (64). Several row tiles read the same words and count on the caches between them:
+// 722 MB take 583 -> 601 us past the caches (150 rows), 605 -> 618 (192), 1415 -> 1433 (512), 2751 -> 2840 (1024), one
+// request of 256 tokens with a step list 697 -> 745. Neuron-major words and blocks that are gathered row by row have
+// ordinary loads throughout.
+bool words_past_caches(const GemmParams& p) { return p.m <= 64 && 2ll * 8 * p.kc_cap * p.n_cap > (320ll << 20); }
 
 int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t ws_bytes) {
     const size_t need = gemm_ws_bytes(p.m, p.kc_cap, p.n_cap);
@@ -539,30 +536,21 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
     // will own its tiles (and then initialise Z itself).
     // columns of the 64- and 32-row tiles
     const int narrow_bn = p.w_planes ? planes_narrow_bn(ctx, p) : 64, flat_bn = p.w_planes ? 128 : 256;
-    auto plan = [&](int bm) {
-        if (p.w_planes) plan_gemm(ctx, p, bm, bm == 128 ? 64 : bm == 64 ? narrow_bn : 128, 1, 2);
-        else if (bm == 128) plan_gemm(ctx, p, 128, 64, Tile<2, 2, 2, 1>::WG_PER_CU, 1);
-        else if (bm == 64) plan_gemm(ctx, p, 64, 64, Tile<2, 2, 1, 1>::WG_PER_CU, 1);
-        else plan_gemm(ctx, p, 32, 256, Tile<1, 4, 1, 2>::WG_PER_CU, 1);
-    };
+    auto plan = [&](int bm) { plan_gemm(ctx, p, bm, bm == 128 ? 64 : bm == 64 ? narrow_bn : flat_bn, bm == 32 && !p.w_planes ? 1 : 2); };
     auto launch = [&](int bm) {
         plan(bm);
-        if (p.w_planes) {
-            if (bm == 128) return launch_planes<2, 2, 4, 2>(ctx, what, p);
-            if (bm == 64 && narrow_bn == 64) return launch_planes<2, 2, 2, 2>(ctx, what, p);
-            if (bm == 64) return launch_planes<1, 4, 4, 2>(ctx, what, p);
-            return launch_planes<1, 4, 2, 2>(ctx, what, p);
-        }
-        if (bm == 128) return launch_gemm<2, 2, 2, 1>(ctx, what, p);
-        if (bm == 64) return launch_gemm<2, 2, 1, 1>(ctx, what, p);
-        return launch_gemm<1, 4, 1, 2>(ctx, what, p);
+        if (!p.w_planes) return bm == 64 ? launch_words(ctx, what, p) : launch_gemm<1, 4, 1, 2>(ctx, what, p);
+        if (bm == 128) return launch_planes<2, 2, 4, 2>(ctx, what, p);
+        if (bm == 64 && narrow_bn == 64) return launch_planes<2, 2, 2, 2>(ctx, what, p);
+        if (bm == 64) return launch_planes<1, 4, 4, 2>(ctx, what, p);
+        return launch_planes<1, 4, 2, 2>(ctx, what, p);
     };
-    // rows per workgroup tile: 128, 64 or 32
+    // rows per workgroup tile: 128, 64 or 32 (words: 64 or 32)
     int bm = 128;
     const long big_tiles = (long)((p.m + 127) / 128) * ((p.n_cap + 63) / 64);
     if (ctx->gemm_tile == 2) bm = 64;
     else if (p.m <= 32) bm = 32;
-    else if (p.m <= 64) bm = 64;
+    else if (p.m <= 64 || !p.w_planes) bm = 64;
     // a small product (a handful of 128 x 64 tiles) is bound by the fixed cost per workgroup:
     // 64 rows double the number of independent tiles
     else if (!p.row_comp && big_tiles * 8 <= ctx->num_cu) bm = 64;
@@ -574,11 +562,11 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
     plan(bm);
     p.w_nt = words_past_caches(p);
     // a decoding batch on weight planes: the kernel that streams the planes wavefront by wavefront
-    const bool fewrow = p.w_planes && p.m <= COMET_FEWROW_MAX_ROWS && !p.w_tr && !p.row_comp && !p.tmask &&
-                        ctx->skinny_mode != 1 && ctx->gemm_tile != 2;
+    const bool fewrow = p.w_planes && p.m <= COMET_FEWROW_MAX_ROWS && !p.row_comp && !p.tmask && ctx->skinny_mode != 1 &&
+                        ctx->gemm_tile != 2;
     if (fewrow) {
         p.own_try = 0;                                         // Z := C comes from the packing kernel
-        p.mpad = 32;                                           // one row tile: a digit group is 512 bytes
+        if (p.m <= 32) p.mpad = 32;                            // one row tile: a digit group is 512 bytes
     }
 
     // digit planes of [E | A'] and Z := C, one launch
@@ -610,7 +598,7 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
         // 80 % of the area; less than three quarters, what 129 to 192 rows of one component come to, for 64 x 64 on
         // planes and long contractions (129 rows: k = 4199, 300 blocks of 16 479 -> 317 us on 128 x 64; k = 1024, 344 of 32
         // 131 against 160)
-        const int percent = p.w_planes && narrow_bn == 64 && p.kc_cap >= 2048 ? 75 : 80;
+        const int percent = narrow_bn == 64 && p.kc_cap >= 2048 ? 75 : 80;
         hipLaunchKernelGGL(tile_list_kernel, dim3(1), dim3(GT), 0, ctx->stream, p, 64, narrow_bn, list_a, list_b, sel,
                            percent);
         COMET_LAUNCH_CHECK(ctx, what);
@@ -659,9 +647,9 @@ int run_share_group(comet_ctx* ctx, const char* what, GemmParams* ps, int n, voi
     if (ctx->gemm_grid > 0) grid = ctx->gemm_grid;
     const long tiles = (long)((p0.m + T::BM - 1) / T::BM) * ((p0.n_cap + T::BN - 1) / T::BN);
     const long steps_each = tiles * 2 * ((p0.kc_cap + KSTEP - 1) / KSTEP) / grid;
-    const bool grouped = n > 1 && p0.w_planes && p0.m > 64 && p0.n_cap > 0 && ctx->gemm_tile != 2 &&
-                         (ctx->group_mode == 1 || ctx->group_mode == 3 ||
-                          (ctx->group_mode == 0 && steps_each <= 128));
+    const bool grouped = (n > 1 && p0.w_planes && p0.m > 64 && p0.n_cap > 0 && ctx->gemm_tile != 2 &&
+                                 (ctx->group_mode == 1 || ctx->group_mode == 3 ||
+                                  (ctx->group_mode == 0 && steps_each <= 128)));
     if (!grouped) {
         for (int j = 0; j < n; ++j) {
             const int rc = run_share(ctx, what, ps[j], base + (size_t)j * each, each);
@@ -694,17 +682,16 @@ int run_share_group(comet_ctx* ctx, const char* what, GemmParams* ps, int n, voi
         p.tile_bn = T::BN;
         p.group_n = n;
         p.own_try = (tiles * n % grid == 0) ? 1 : 0;
-        p.k_rotate = 1;
         p.team = ctx->group_mode != 3;      // (3: one launch without teams, for comparison)
     }
     {
         const GemmParams& p = grp.p[0];
         unsigned gx = (unsigned)((p.ks_cap * 2 + 3) / 4);
         if (gx < 1) gx = 1;
-        const long zgx = ((long)p.m * p.n_cap / (2l * 4 * GT) + p.mpad / 64 - 1) / (p.mpad / 64);
+        const int slabs = (p.mpad + 63) / 64;
+        const long zgx = ((long)p.m * p.n_cap / (2l * 4 * GT) + slabs - 1) / slabs;
         if (zgx > gx) gx = (unsigned)(zgx > 4096 ? 4096 : zgx);
-        hipLaunchKernelGGL(xpack_group_kernel, dim3(gx, (unsigned)(p.mpad / 64), 3u * (unsigned)n), dim3(GT), 0,
-                           ctx->stream, grp);
+        hipLaunchKernelGGL(xpack_group_kernel, dim3(gx, (unsigned)slabs, 3u * (unsigned)n), dim3(GT), 0, ctx->stream, grp);
         COMET_LAUNCH_CHECK(ctx, what);
     }
     return launch_planes_group<2, 2, 4, 2>(ctx, what, grp);

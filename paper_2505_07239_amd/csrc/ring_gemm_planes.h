@@ -36,8 +36,6 @@
 
 namespace comet_gemm {
 
-constexpr int KPAIR = 2 * KSTEP;          // ring words contracted per matrix instruction
-
 // Output tile of WAVES_M x WAVES_N wavefronts (four, one per SIMD), each with MT x NT sub-tiles of
 // 16 x 16 outputs in eight digit planes: 4 x 2 sub-tiles fill the 256 accumulator registers.  The tile with
 // 2 x 2 of them, 64 x 64, is for small products: a pair of steps takes 1.1 us there and 2.2 us on the others,
@@ -262,7 +260,7 @@ __device__ __forceinline__ void plane_pair(std::integer_sequence<int, Ms...>, co
 // One workgroup's share of a product: segment by segment, the main loop and the write-out of the
 // partial sum.
 template <class T, int WAVES_M, int KIND, int GMODE, bool LISTED>
-__device__ __forceinline__ void plane_sweep(const GemmParams& p, const Geometry& q, UnitWalk<LISTED, 2>& walk,
+__device__ __forceinline__ void plane_sweep(const GemmParams& p, const Geometry& q, UnitWalk<LISTED>& walk,
                                             const bool own, unsigned char* wsm, int* steptab) {
     using PM = PairMap<T>;
     constexpr int MT = T::MT, NT = T::NT;
@@ -373,30 +371,24 @@ __global__ __launch_bounds__(GT, 1) void ring_planes_kernel(GemmParams p) {
     using T = PlaneTile<WAVES_M, WAVES_N, MT, NT>;
     COMET_PLANES_LDS(T);
     if (p.tile_sel && *p.tile_sel != p.tile_sel_want) return;   // the other tile shape was chosen
-    const Geometry q = gemm_geometry<T::BM, T::BN, KIND, LISTED, 2>(p);
+    const Geometry q = gemm_geometry<T::BM, T::BN, KIND, LISTED>(p);
     if (q.units == 0) return;
     const int G = gridDim.x;
     const int b = xcd_contiguous(blockIdx.x, G);
     bool own = false;
     if constexpr (OWN) own = owns_tiles(p, q.m_eff, q.n_eff, q.kc);
-    UnitWalk<LISTED, 2> walk(p, q, b, G, own);
+    UnitWalk<LISTED> walk(p, q, b, G, own);
     plane_sweep<T, WAVES_M, KIND, GMODE, LISTED>(p, q, walk, own, wsm, steptab);
 }
 
 // Several products of one shape and one index list (so: one geometry) in one launch: the work
 // units of the members follow each other, tile by tile inside a member, and the workgroups share
 // out the whole sequence.  A workgroup's range may run across members.
-constexpr int GROUP_MAX = COMET_SHARE_GROUP_MAX;
-struct GemmGroup {
-    int n;
-    GemmParams p[GROUP_MAX];
-};
-
 template <int WAVES_M, int WAVES_N, int MT, int NT, int KIND, int GMODE, bool OWN>
 __global__ __launch_bounds__(GT, 1) void ring_planes_group_kernel(GemmGroup grp) {
     using T = PlaneTile<WAVES_M, WAVES_N, MT, NT>;
     COMET_PLANES_LDS(T);
-    const Geometry q = gemm_geometry<T::BM, T::BN, KIND, false, 2>(grp.p[0]);
+    const Geometry q = gemm_geometry<T::BM, T::BN, KIND, false>(grp.p[0]);
     if (q.units == 0) return;
     const int G = gridDim.x;
     const int b = xcd_contiguous(blockIdx.x, G);
@@ -415,7 +407,7 @@ __global__ __launch_bounds__(GT, 1) void ring_planes_group_kernel(GemmGroup grp)
     for (int j = (int)(u / units); u < u_end; ++j) {
         const long base = (long)j * units;
         const long hi = u_end - base < units ? u_end - base : units;
-        UnitWalk<false, 2> walk(grp.p[j], q, u - base, hi, team ? b % q.tiles_m : -1);
+        UnitWalk<false> walk(grp.p[j], q, u - base, hi, team ? b % q.tiles_m : -1);
         plane_sweep<T, WAVES_M, KIND, GMODE, false>(grp.p[j], q, walk, own, wsm, steptab);
         u = base + units;
     }
@@ -458,10 +450,8 @@ int launch_planes(comet_ctx* ctx, const char* what, const GemmParams& p) {
     if (!kern || !p.w_planes) return comet_fail(ctx, COMET_EINVAL, "%s: no kernel variant for this call", what);
     if (p.tile_bm != T::BM || p.tile_bn != T::BN || p.grid < 1)
         return comet_fail(ctx, COMET_EINVAL, "%s: launch plan does not match the kernel", what);
-    return launch_share_kernel(ctx, what, kern, p.grid, p);
+    return launch_share_kernel(ctx, what, kern, dim3((unsigned)p.grid), p);
 }
-
-using GemmGroupKernel = void (*)(GemmGroup);
 
 template <int WAVES_M, int WAVES_N, int MT, int NT, bool OWN>
 GemmGroupKernel planes_group_kernel_for(const GemmParams& p) {
@@ -482,7 +472,7 @@ int launch_planes_group(comet_ctx* ctx, const char* what, const GemmGroup& grp) 
         return comet_fail(ctx, COMET_EINVAL, "%s: launch plan does not match the grouped kernel", what);
     return launch_share_kernel(ctx, what, p.own_try ? planes_group_kernel_for<WAVES_M, WAVES_N, MT, NT, true>(p)
                                                     : planes_group_kernel_for<WAVES_M, WAVES_N, MT, NT, false>(p),
-                               p.grid, grp);
+                               dim3((unsigned)p.grid), grp);
 }
 
 }  // namespace comet_gemm
