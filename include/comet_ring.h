@@ -257,12 +257,13 @@ int comet_simm_share_unopened(comet_ctx* ctx, int party, int64_t m, int64_t k_fu
  * operands; shape, block size, index list and flags are common to all and mean
  * what they mean for comet_somm_share (op = COMET_OP_SOMM: m, k, n = n_full) or
  * comet_simm_share (op = COMET_OP_SIMM: m, k = k_full, n).  The result is, bit
- * for bit, that of the n_members single calls.  With COMET_WEIGHT_PLANES and
- * m > 64, members that are short launches on their own (see COMET_TUNE_GROUP)
- * run as one operand-packing launch and one matrix-core launch over the union
- * of their work units: the fixed cost of a launch is paid once and the tail of
- * one product is filled by the next.  Otherwise they run one after the other.  No Z_i may alias another member's Z_i or any
- * input.  Workspace: n_members * comet_workspace_bytes(op, ...) bytes.
+ * for bit, that of the n_members single calls.  With COMET_WEIGHT_PLANES, members
+ * of m <= 32, small ones of any m, and members of m > 64 that are short launches
+ * on their own (see COMET_TUNE_GROUP) run as one operand-packing launch and one
+ * matrix-core launch over the union of their work units: the fixed cost of a
+ * launch is paid once and the tail of one product is filled by the next.
+ * Otherwise they run one after the other.  No Z_i may alias another member's Z_i
+ * or any input.  Workspace: n_members * comet_workspace_bytes(op, ...) bytes.
  * 1 <= n_members <= COMET_SHARE_GROUP_MAX; other limits as for the single
  * calls. */
 enum { COMET_SHARE_GROUP_MAX = 8 };
@@ -398,8 +399,8 @@ int comet_truncate_share(comet_ctx* ctx, int party, const uint64_t* z, uint64_t*
  *                         of idle time around the kernel
  *   COMET_TUNE_GROUP:     comet_share_group normally runs its members as one
  *                         launch when a member alone is a short launch (up to
- *                         128 contraction steps of 32 words per workgroup);
- *                         1 = whenever the operands allow it, 2 = never,
+ *                         128 contraction steps of 32 words per workgroup, and
+ *                         m > 64 or few or small products); 1 = whenever the operands allow it, 2 = never,
  *                         3 = as 1 but without teaming the workgroups of a
  *                         column of tiles (a measurement aid) */
 enum { COMET_TUNE_GEMM_GRID = 0, COMET_TUNE_GEMM_CHUNK = 1, COMET_TUNE_GEMM_TILE = 2,

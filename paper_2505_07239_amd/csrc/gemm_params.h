@@ -121,9 +121,13 @@ struct GemmGroup {
 using GemmKernel = void (*)(GemmParams);
 using GemmGroupKernel = void (*)(GemmGroup);
 
-// Matrix-core path for at most COMET_FEWROW_MAX_ROWS activation rows with the weight side in digit
-// planes (plain products only: no result blocks, no per-token row sets): every wavefront streams
-// its own weight fragments from memory into registers.  Runs after the packing kernel (digit
-// planes of [E | A'] in p.xp, Z := C).
+// Matrix-core path whose wavefronts stream their weight fragments from memory into registers (plain products only: no
+// result blocks, no per-token row sets): up to COMET_FEWROW_MAX_ROWS activation rows on weight planes, and small
+// products (see small_product() in ring_gemm.hip).  Runs after the packing kernel (digit planes of
+// [E | A'] in p.xp, Z := C).
 static const int COMET_FEWROW_MAX_ROWS = 32;
 int comet_launch_fewrow(comet_ctx* ctx, const char* what, const GemmParams& p);
+int comet_launch_fewrow_group(comet_ctx* ctx, const char* what, const GemmGroup& grp);
+// The smallest products, whole share in one launch: no packing kernel, no workspace.
+static const int COMET_DIRECT_MAX_K = 128;
+int comet_launch_direct(comet_ctx* ctx, const char* what, const GemmParams& p);

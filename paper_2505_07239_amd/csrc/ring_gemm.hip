@@ -514,6 +514,46 @@ int planes_narrow_bn(const comet_ctx* ctx, const GemmParams& p) {
 // ordinary loads throughout.
 bool words_past_caches(const GemmParams& p) { return p.m <= 64 && 2ll * 8 * p.kc_cap * p.n_cap > (320ll << 20); }
 
+// ---------------------------------------------------------------------------
+// which kernel
+// ---------------------------------------------------------------------------
+// What the few-row kernel deals out: (32-row tile, 128 columns, contraction step) units of all members.
+long few_units(const GemmParams& p, int members) {
+    return (long)((p.m + 31) / 32) * ((p.n_cap + 127) / 128) * 2 * ((p.kc_cap + KSTEP - 1) / KSTEP) * members;
+}
+
+// Does a product take the kernel whose wavefronts stream by themselves (ring_fewrow.hip)?  Up to 32 rows on planes
+// always; on words up to 16 units per compute unit (13: 9 and 32 rows, k = 4096, n = 1664 33 and 41 us with the
+// 32 x 256 tile, 31 and 36 here; 32 rows, 819 gathered row by row x 1001 46 against 21; but 27: 9 rows, 5120 x 2752 49
+// against 53); of more rows the smallest products, up to half a unit (128 x 256 x 256 13.2 against 12.7, 64 x 64 x 64 11.3
+// against 8.8; but one unit: 256 x 256 x 256 13.1 against 15.1).
+bool takes_few_rows(const comet_ctx* ctx, const GemmParams& p) {
+    if (p.row_comp || p.tmask || ctx->gemm_tile == 2 || ctx->gemm_chunk > 0) return false;
+    if (p.w_planes && p.m <= COMET_FEWROW_MAX_ROWS) return ctx->skinny_mode != 1;
+    return 2 * few_units(p, 1) <= (p.m <= COMET_FEWROW_MAX_ROWS ? 32l : 1l) * ctx->num_cu;
+}
+
+// A group on planes there: up to 32 rows always, because the members then share one packing and one share launch; more rows up to
+// twenty units per compute unit (two products of 128 x 768 x 320 26.4 -> 21.7 us, four of 256 x 320 x 768 47 -> 36, two of
+// 65 x 640 x 2560 44.0 -> 41.7 at 19 units; at 24 units four of 65 x 640 x 1664 50 -> 55).
+bool group_takes_few_rows(const comet_ctx* ctx, const GemmParams& p, int members) {
+    if (members < 2 || !p.w_planes || p.n_cap < 1 || p.kc_cap < 1 || ctx->group_mode != 0 || ctx->gemm_tile == 2 ||
+        ctx->gemm_chunk > 0)
+        return false;
+    if (p.m <= COMET_FEWROW_MAX_ROWS) return ctx->skinny_mode != 1;
+    return few_units(p, members) <= 20l * ctx->num_cu;
+}
+
+// The smallest products take one launch: up to 100 contraction words and a 32 x 32 tile per compute unit. 64 x 64 x 64 9.0
+// us packed, multiplied by the few-row kernel -> 7.9 us, 16 x 64 x 3072 8.3 -> 6.5, 256 x 64 x 1024 13.7 -> 8.9, 256 x
+// 100 x 64 11.0 -> 9.0, and 2.5 us less of the host's time; but 64 x 128 x 256 9.5 -> 10.5, 128 x 64 x 3072 (384 tiles)
+// 14.6 -> 15.7.
+bool takes_direct(const comet_ctx* ctx, const GemmParams& p) {
+    if (p.row_comp || p.tmask || ctx->gemm_tile == 2 || ctx->gemm_chunk > 0 || ctx->gemm_grid > 0) return false;
+    const long tiles = (long)((p.m + 31) / 32) * ((p.n_cap + 31) / 32);
+    return p.kc_cap >= 1 && p.kc_cap <= 100 && tiles <= ctx->num_cu;
+}
+
 int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t ws_bytes) {
     const size_t need = gemm_ws_bytes(p.m, p.kc_cap, p.n_cap);
     if (!ws || ws_bytes < need)
@@ -532,6 +572,7 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
     // (the few-row kernel reads the weights along the output columns: row-major words only)
     if (p.m <= COMET_SKINNY_MAX_ROWS && ctx->skinny_mode != 1 && !p.w_tr && !p.w_planes)
         return comet_launch_skinny(ctx, what, p);
+    if (takes_direct(ctx, p)) return comet_launch_direct(ctx, what, p);
     // Tile shape and launch plan first: the packing kernel has to know whether the share kernel
     // will own its tiles (and then initialise Z itself).
     // columns of the 64- and 32-row tiles
@@ -561,9 +602,8 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
     else if (p.tmask) bm = 64;
     plan(bm);
     p.w_nt = words_past_caches(p);
-    // a decoding batch on weight planes: the kernel that streams the planes wavefront by wavefront
-    const bool fewrow = p.w_planes && p.m <= COMET_FEWROW_MAX_ROWS && !p.row_comp && !p.tmask && ctx->skinny_mode != 1 &&
-                        ctx->gemm_tile != 2;
+    // a decoding batch on weight planes, or a small product: the kernel that streams wavefront by wavefront
+    const bool fewrow = takes_few_rows(ctx, p);
     if (fewrow) {
         p.own_try = 0;                                         // Z := C comes from the packing kernel
         if (p.m <= 32) p.mpad = 32;                            // one row tile: a digit group is 512 bytes
@@ -626,7 +666,7 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
 }
 
 // Several products of one shape, one index list and one operand format.  When they suit the
-// grouped matrix-core kernel (weight planes, more than 64 rows, no few-row path) they run as one
+// grouped kernels (weight planes; few rows or small, or more than 64 rows) they run as one
 // packing launch and one share launch over the union of their work units; otherwise one by one.
 int run_share_group(comet_ctx* ctx, const char* what, GemmParams* ps, int n, void* ws, size_t ws_bytes) {
     const size_t each = gemm_ws_bytes(ps[0].m, ps[0].kc_cap, ps[0].n_cap);
@@ -647,7 +687,8 @@ int run_share_group(comet_ctx* ctx, const char* what, GemmParams* ps, int n, voi
     if (ctx->gemm_grid > 0) grid = ctx->gemm_grid;
     const long tiles = (long)((p0.m + T::BM - 1) / T::BM) * ((p0.n_cap + T::BN - 1) / T::BN);
     const long steps_each = tiles * 2 * ((p0.kc_cap + KSTEP - 1) / KSTEP) / grid;
-    const bool grouped = (n > 1 && p0.w_planes && p0.m > 64 && p0.n_cap > 0 && ctx->gemm_tile != 2 &&
+    const bool few = group_takes_few_rows(ctx, p0, n);
+    const bool grouped = few || (n > 1 && p0.w_planes && p0.m > 64 && p0.n_cap > 0 && ctx->gemm_tile != 2 &&
                                  (ctx->group_mode == 1 || ctx->group_mode == 3 ||
                                   (ctx->group_mode == 0 && steps_each <= 128)));
     if (!grouped) {
@@ -681,7 +722,8 @@ int run_share_group(comet_ctx* ctx, const char* what, GemmParams* ps, int n, voi
         p.tile_bm = T::BM;
         p.tile_bn = T::BN;
         p.group_n = n;
-        p.own_try = (tiles * n % grid == 0) ? 1 : 0;
+        p.own_try = (tiles * n % grid == 0 && !few) ? 1 : 0;          // (few: Z := C comes from the packing kernel)
+        if (few && p.m <= 32) p.mpad = 32;
         p.team = ctx->group_mode != 3;      // (3: one launch without teams, for comparison)
     }
     {
@@ -694,6 +736,7 @@ int run_share_group(comet_ctx* ctx, const char* what, GemmParams* ps, int n, voi
         hipLaunchKernelGGL(xpack_group_kernel, dim3(gx, (unsigned)slabs, 3u * (unsigned)n), dim3(GT), 0, ctx->stream, grp);
         COMET_LAUNCH_CHECK(ctx, what);
     }
+    if (few) return comet_launch_fewrow_group(ctx, what, grp);
     return launch_planes_group<2, 2, 4, 2>(ctx, what, grp);
 }
 
