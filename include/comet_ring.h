@@ -388,8 +388,8 @@ int comet_truncate_share(comet_ctx* ctx, int party, const uint64_t* z, uint64_t*
  *                         take a kernel bound by reading the weights once; 1
  *                         sends them to the matrix-core kernel like any other
  *   COMET_TUNE_SKINNY_SLICES: pieces the stacked contraction is cut into by
- *                         the vector-ALU kernel (default: about eight
- *                         workgroups per compute unit)
+ *                         the vector-ALU kernel (default: as many as
+ *                         fill the places on the chip a few times over)
  *   COMET_TUNE_COMPONENTS: 1 sends every comet_components call to the
  *                         multi-workgroup search (small graphs normally take a
  *                         one-workgroup kernel)

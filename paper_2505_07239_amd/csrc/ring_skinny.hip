@@ -238,6 +238,14 @@ void (*pick_kernel(int kind, bool unopened))(GemmParams, const u64*, int) {
 
 }  // namespace
 
+// Workgroups of a variant that share a compute unit (by its registers: accumulators of MR rows and eight weight rows in
+// flight, twelve loads of them unopened).
+static int per_cu(int mr, bool vec2, bool unopened) {
+    if (!vec2) return mr <= 4 ? 7 : 6;
+    if (unopened) return mr == 2 ? 5 : mr == 8 ? 3 : 4;
+    return mr == 2 ? 8 : mr == 4 ? 7 : mr == 6 ? 5 : 4;
+}
+
 int comet_launch_skinny(comet_ctx* ctx, const char* what, const GemmParams& p) {
     if (p.m < 1 || p.m > COMET_SKINNY_MAX_ROWS)
         return comet_fail(ctx, COMET_EINVAL, "%s: row count outside the vector-ALU path", what);
@@ -263,16 +271,30 @@ int comet_launch_skinny(comet_ctx* ctx, const char* what, const GemmParams& p) {
     const bool vec2 = (p.ldb & 1) == 0 && (p.ldf & 1) == 0 && (p.n_cap & 1) == 0 && (p.bs & 1) == 0;
     const int cols = vec2 ? 128 : 64;
     const long tiles = (p.n_cap + cols - 1) / cols;
-    // about sixteen workgroups per compute unit, each wavefront with at least one full batch of
-    // rows in flight
-    long slices = (16l * ctx->num_cu + tiles - 1) / tiles;
+    const bool un = p.F2 != nullptr;
+    // As many slices as fill the places on the chip (per_cu() workgroups a compute unit) a whole number of times: the first
+    // of four rounds that leaves at most 8 % of the places empty, or the one that leaves fewest.  A last round
+    // that is nearly empty costs as much as a full one, and every slice adds its partial sums onto Z. 8 rows, both
+    // shares of F (768 places), 90 tiles: 271 us with 46 slices (sixteen workgroups a unit), 233 with 8 (720
+    // workgroups), 270 with 11 (990); 13 tiles, k = 4096, 43 -> 38; opened (1024 places) 32 tiles, k = 4096, 67 -> 64;
+    // 6 rows, 300 x 20000 33 -> 24; 8 rows, 6000 x 1001 word by word 38 -> 32.  Two rows have little to add onto Z and
+    // wait for memory alone: they take about sixteen workgroups a unit (4096 x 4096 50 us, 52 in one round).
+    // Every wavefront keeps at least one full batch of rows.
+    const long places = (long)per_cu(MR, vec2, un) * ctx->num_cu;
+    long slices = 1;
+    double filled = 0.0;
+    const int first = MR > 2 || !vec2 ? 1 : un ? 3 : 2;
+    for (int rounds = first; rounds < first + 4 && filled < 0.92; ++rounds) {
+        const long s = rounds * places / tiles;
+        const double f = (double)(s * tiles) / (double)(rounds * places);
+        if (s >= 1 && f > filled) { slices = s; filled = f; }
+    }
     const long max_slices = (2l * p.kc_cap) / (SW * UNROLL);
     if (slices > max_slices) slices = max_slices;
     if (ctx->skinny_slices > 0) slices = ctx->skinny_slices;
     if (slices > 65535) slices = 65535;
     if (slices < 1) slices = 1;
     void (*kern)(GemmParams, const u64*, int);
-    const bool un = p.F2 != nullptr;
     if (MR == 2) kern = vec2 ? pick_kernel<2, 2>(p.kind, un) : pick_kernel<2, 1>(p.kind, un);
     else if (MR == 4) kern = vec2 ? pick_kernel<4, 2>(p.kind, un) : pick_kernel<4, 1>(p.kind, un);
     else if (MR == 6) kern = vec2 ? pick_kernel<6, 2>(p.kind, un) : pick_kernel<6, 1>(p.kind, un);
