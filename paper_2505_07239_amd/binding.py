@@ -5,6 +5,10 @@ kernels.  Tensors are ``torch.int64`` CUDA(-HIP) tensors whose bits are the
 ring elements mod 2^64; torch is used for device memory and streams, nothing
 else.  There is no CPU fallback: if the library is missing or a call fails, an
 exception is raised.
+
+The calls a layer makes over and over go through the native module ``_host`` (csrc/host.cpp), which makes the
+same checks on tensors in one call and declines (None) whatever is not plain; the methods below then take their own way,
+and the messages of what they refuse come from there.
 """
 from __future__ import annotations
 
@@ -51,6 +55,8 @@ def load_library() -> ctypes.CDLL:
     if not os.path.exists(LIB_PATH):
         raise FileNotFoundError(
             "%s not found: run `python -m paper_2505_07239_amd.build` (needs hipcc)" % LIB_PATH)
+    if not os.path.exists(os.path.join(_HERE, "_host.so")):
+        raise FileNotFoundError("_host.so not found beside the library: run `python -m paper_2505_07239_amd.build` (needs g++)")
     lib = ctypes.CDLL(LIB_PATH)
     vp, i32, i64, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t
     lib.comet_create.argtypes = [ctypes.POINTER(vp), i32]
@@ -92,6 +98,8 @@ def load_library() -> ctypes.CDLL:
     lib.comet_set_tuning.argtypes = [vp, i32, i32]
     lib.comet_timing_begin.argtypes = [vp, i32]
     lib.comet_timing_end.argtypes = [vp, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int)]
+    from . import _host
+    _host.bind({name: ctypes.cast(getattr(lib, name), vp).value for name in EXPORTS}, WeightPlanes)
     _lib = lib
     return lib
 
@@ -186,8 +194,12 @@ class Context:
             raise CometError(rc, "comet_create failed (is device %d an MI355X?)" % device)
         self.h = h
         self._ws = None
+        from . import _host
+        self._host = _host.Host(h.value, device)
 
     def close(self):
+        if getattr(self, "_host", None):
+            self._host.close()
         if getattr(self, "h", None):
             self.lib.comet_destroy(self.h)
             self.h = None
@@ -201,6 +213,12 @@ class Context:
     def _check(self, rc: int):
         if rc != 0:
             raise CometError(rc, self.lib.comet_last_error(self.h).decode())
+
+    def _made(self, r):
+        """The result of a call that ``_host`` made: an int is an error code."""
+        if type(r) is int:
+            self._check(r)
+        return r
 
     def _sync_stream(self):
         # (the handle itself: torch.cuda.current_stream builds a stream object around it on every call)
@@ -216,6 +234,9 @@ class Context:
 
     # ---- (1) mask / open ----
     def mask_share(self, x_i, a_i, out=None):
+        r = self._host.elementwise(False, x_i, a_i, out)
+        if r is not None:
+            return self._made(r)
         _words(x_i, "x_i"), _words(a_i, "a_i")
         out = torch.empty_like(x_i) if out is None else _words(out, "out")
         if a_i.numel() != x_i.numel() or out.numel() != x_i.numel():
@@ -225,6 +246,9 @@ class Context:
         return out
 
     def open(self, d_0, d_1, out=None):
+        r = self._host.elementwise(True, d_0, d_1, out)
+        if r is not None:
+            return self._made(r)
         _words(d_0, "d_0"), _words(d_1, "d_1")
         out = torch.empty_like(d_0) if out is None else _words(out, "out")
         if d_1.numel() != d_0.numel() or out.numel() != d_0.numel():
@@ -236,6 +260,10 @@ class Context:
     def open_weight_planes(self, g_0, g_1=None, out=None, neuron_major=False) -> WeightPlanes:
         """F = g_0 + g_1 (or g_0 alone: offline packing of a triple share) as digit planes.
         ``neuron_major``: the operands are stored one row per column of the matrix (n x k)."""
+        r = self._host.open_planes(g_0, g_1, out, neuron_major)
+        if r is not None:
+            n, k = g_0.shape if neuron_major else g_0.shape[::-1]
+            return WeightPlanes(self._made(r), k, n)
         _words(g_0, "g_0")
         k, n = (g_0.shape[1], g_0.shape[0]) if neuron_major else g_0.shape
         if g_1 is not None:
@@ -252,6 +280,9 @@ class Context:
         return WeightPlanes(out, k, n)
 
     def mask_share_gather(self, w_i, b_i, axis, bs, blk_idx, n_blk_dev, n_blk_cap, out=None):
+        r = self._host.gather(w_i, b_i, axis, bs, blk_idx, n_blk_dev, n_blk_cap, out)
+        if r is not None:
+            return self._made(r)
         _words(w_i, "w_i"), _words(b_i, "b_i")
         rows, cols = w_i.shape
         ld = n_blk_cap * bs
@@ -267,6 +298,10 @@ class Context:
 
     # ---- (2) compact ----
     def compact_mask(self, mask, blk_idx=None, n_blk_dev=None):
+        r = self._host.compact(self._ws, mask, blk_idx, n_blk_dev)
+        if r is not None:
+            self._made(r)
+            return blk_idx, n_blk_dev
         if mask.dtype != torch.uint8 or not mask.is_cuda or not mask.is_contiguous():
             raise TypeError("mask must be a contiguous uint8 tensor on the GPU")
         if mask.dim() == 1:
@@ -287,6 +322,10 @@ class Context:
     def somm_share(self, party, bs, blk_idx, n_blk_dev, n_blk_cap, e, f, a_i, b_i, c_i,
                    b_full=True, neuron_major=False, out=None):
         """``neuron_major``: ``f`` and ``b_i`` are stored one row per neuron (n x k)."""
+        r = self._host.share(self._ws, True, party, bs, blk_idx, n_blk_dev, n_blk_cap, e, f, None, a_i, b_i, c_i,
+                             False, b_full, neuron_major, out)
+        if r is not None:
+            return self._made(r)
         planes = _operands(e, f, a_i, b_i, c_i)
         m, k = e.shape
         n_full = b_i.shape[0 if neuron_major else 1] if b_full else 0
@@ -320,6 +359,10 @@ class Context:
 
     def simm_share(self, party, bs, blk_idx, n_blk_dev, n_blk_cap, e, f, a_i, b_i, c_i,
                    a_full=True, b_full=True, out=None):
+        r = self._host.share(self._ws, False, party, bs, blk_idx, n_blk_dev, n_blk_cap, e, f, None, a_i, b_i, c_i,
+                             a_full, b_full, False, out)
+        if r is not None:
+            return self._made(r)
         planes = _operands(e, f, a_i, b_i, c_i)
         m = e.shape[0]
         n = f.shape[1]
@@ -342,6 +385,11 @@ class Context:
                             b_full=True, out=None):
         """``somm_share`` for at most 8 rows with the opening folded in: ``g_0``, ``g_1`` are the
         two masked shares of the indexed weights (k x ld words), F = g_0 + g_1 is never stored."""
+        if g_1 is not None:
+            r = self._host.share(self._ws, True, party, bs, blk_idx, n_blk_dev, n_blk_cap, e, g_0, g_1, a_i, b_i, c_i,
+                                 False, b_full, False, out)
+            if r is not None:
+                return self._made(r)
         if _operands(e, g_0, a_i, b_i, c_i) or isinstance(g_1, WeightPlanes):
             raise TypeError("the unopened form takes words, not weight planes")
         m, k = e.shape
@@ -363,6 +411,11 @@ class Context:
     def simm_share_unopened(self, party, bs, blk_idx, n_blk_dev, n_blk_cap, e, g_0, g_1, a_i, b_i, c_i,
                             a_full=True, b_full=True, out=None):
         """``simm_share`` for at most 8 rows with the opening folded in (``g_0``, ``g_1``: ld x n)."""
+        if g_1 is not None:
+            r = self._host.share(self._ws, False, party, bs, blk_idx, n_blk_dev, n_blk_cap, e, g_0, g_1, a_i, b_i, c_i,
+                                 a_full, b_full, False, out)
+            if r is not None:
+                return self._made(r)
         if _operands(e, g_0, a_i, b_i, c_i) or isinstance(g_1, WeightPlanes):
             raise TypeError("the unopened form takes words, not weight planes")
         m = e.shape[0]
@@ -389,6 +442,9 @@ class Context:
         of output tensors, one per member, or None.  Returns the list of outputs."""
         if kind not in ("somm", "simm"):
             raise ValueError("kind must be 'somm' or 'simm'")
+        r = self._host.group(self._ws, kind == "somm", bs, blk_idx, n_blk_dev, n_blk_cap, members, a_full, b_full, out)
+        if r is not None:
+            return self._made(r)
         if not 1 <= len(members) <= SHARE_GROUP_MAX:
             raise ValueError("1 to %d members" % SHARE_GROUP_MAX)
         somm = kind == "somm"

@@ -1,4 +1,5 @@
-"""Builds ``libcomet_ring.so`` (hipcc, gfx950 only) next to this file."""
+"""Builds ``libcomet_ring.so`` (hipcc, gfx950 only) and the native part of the binding, ``_host.so`` (g++ against
+torch's headers), next to this file."""
 from __future__ import annotations
 
 import os
@@ -10,6 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcomet_ring.so")
+HOST = os.path.join(HERE, "_host.so")
 # the variants of the matrix-core kernels come first: they take longest to compile
 SOURCES = ["ring_gemm_planes_128x64_own.hip", "ring_gemm_group_128x64.hip", "ring_gemm_group_128x64_own.hip",
            "ring_gemm_planes_128x64.hip", "ring_gemm_planes_64x128.hip", "ring_gemm_planes_64x128_listed.hip",
@@ -24,6 +26,19 @@ FLAGS = ["-O3", "-std=c++20", "--offload-arch=gfx950", "-fPIC", "-fvisibility=de
          # packed-FP32 instruction selection is switched off for every device pass
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+
+
+def host_command():
+    """The command that builds ``_host.so``: the CPython and torch of the interpreter that runs this."""
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    include = [os.path.join(base, "include"), os.path.join(base, "include", "torch", "csrc", "api", "include"),
+               sysconfig.get_paths()["include"], "/opt/rocm/include", os.path.join(ROOT, "include")]
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+             "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1"] + ["-I" + i for i in include] +
+            [os.path.join(CSRC, "host.cpp"), "-o", HOST, "-L" + os.path.join(base, "lib"),
+             "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"])
 
 
 def build(verbose: bool = False, incremental: bool = False) -> str:
@@ -53,10 +68,20 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
             print(err, file=sys.stderr)
         return obj
 
-    # translation units compile side by side (hipcc is a subprocess: threads are enough)
+    def compile_host():
+        if incremental and os.path.exists(HOST) and os.path.getmtime(HOST) > max(
+                newest_header, os.path.getmtime(os.path.join(CSRC, "host.cpp"))):
+            return
+        res = subprocess.run(host_command(), capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("g++ failed on host.cpp:\n" + res.stderr)
+
+    # translation units compile side by side (the compilers are subprocesses: threads are enough)
     jobs = max(1, min(len(SOURCES), int(os.environ.get("MAX_JOBS", "0")) or (os.cpu_count() or 1), 8))
     with ThreadPoolExecutor(max_workers=jobs) as pool:
+        host = pool.submit(compile_host)
         objs = list(pool.map(compile_one, SOURCES))
+        host.result()
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
