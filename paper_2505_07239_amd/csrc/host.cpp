@@ -13,6 +13,7 @@
 // the error code of the library.
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/object_ptr.h>
 
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
@@ -116,34 +117,32 @@ struct Weights {
             rows = t->size(0); cols = t->size(1); data = u64(*t);
             return true;
         }
-        PyObject* buf = PyObject_GetAttr(o, name_buf);
-        PyObject* shape = PyObject_GetAttr(o, name_shape);
-        bool ok = buf && shape && PyTuple_CheckExact(shape) && PyTuple_GET_SIZE(shape) == 2;
+        THPObjectPtr buf(PyObject_GetAttr(o, name_buf)), shape(PyObject_GetAttr(o, name_shape));
+        bool ok = buf && shape && PyTuple_CheckExact(shape.get()) && PyTuple_GET_SIZE(shape.get()) == 2;
         long long r = 0, c = 0;
-        ok = ok && integer(PyTuple_GET_ITEM(shape, 0), 0, 1ll << 40, &r) && integer(PyTuple_GET_ITEM(shape, 1), 0, 1ll << 40, &c);
+        ok = ok && integer(PyTuple_GET_ITEM(shape.get(), 0), 0, 1ll << 40, &r) &&
+             integer(PyTuple_GET_ITEM(shape.get(), 1), 0, 1ll << 40, &c);
         const Tensor* t = ok ? plain(buf) : nullptr;
         if (t) data = u64(*t);             // (the planes object holds the buffer)
         rows = r; cols = c;
-        Py_XDECREF(buf);
-        Py_XDECREF(shape);
         PyErr_Clear();
         return t != nullptr;
     }
     bool is(int64_t r, int64_t c) const { return rows == r && cols == c; }
 };
 
-// The result: the caller's tensor of this shape, or a new one.  Returns a new reference, or null to decline.
-PyObject* result(PyObject* o, int64_t rows, int64_t cols, const Tensor& like, uint64_t** data) {
+// The result: the caller's tensor of this shape, or a new one; null to decline.  (References that a call owns are
+// THPObjectPtr throughout: an allocation or a stream lookup that throws gives them back.)
+THPObjectPtr result(PyObject* o, int64_t rows, int64_t cols, const Tensor& like, uint64_t** data) {
     if (o == Py_None) {
         Tensor t = at::empty({rows, cols}, like.options().requires_grad(false));
         *data = u64(t);
-        return THPVariable_Wrap(std::move(t));
+        return THPObjectPtr(THPVariable_Wrap(std::move(t)));
     }
     const Tensor* t = words(o);
-    if (!t || !shaped(*t, rows, cols)) return nullptr;
+    if (!t || !shaped(*t, rows, cols)) return THPObjectPtr();
     *data = u64(*t);
-    Py_INCREF(o);
-    return o;
+    return THPObjectPtr::dup(o);
 }
 
 // a workspace of at least `need` bytes: the context's, or decline
@@ -156,18 +155,16 @@ bool scratch(PyObject* o, size_t need, void** ws) {
     return true;
 }
 
-// On torch's current stream, without the interpreter lock (as ctypes calls).  Takes the reference to `out`.
+// On torch's current stream, without the interpreter lock (as ctypes calls).  `out` is what the call returns.
 template <class F>
-PyObject* call(Host* self, PyObject* out, F&& f) {
+PyObject* call(Host* self, THPObjectPtr out, F&& f) {
     void* stream = c10::hip::getCurrentHIPStream((c10::DeviceIndex)self->device).stream();
     int rc;
     Py_BEGIN_ALLOW_THREADS
     rc = lib.set_stream(self->ctx, stream);
     if (rc == 0) rc = f();
     Py_END_ALLOW_THREADS
-    if (rc == 0) return out;
-    Py_DECREF(out);
-    return PyLong_FromLong(rc);
+    return rc == 0 ? out.release() : PyLong_FromLong(rc);
 }
 
 #define DECLINE Py_RETURN_NONE
@@ -180,7 +177,7 @@ PyObject* elementwise(Host* self, PyObject* const* arg, Py_ssize_t nargs) {
     bool open;
     const Tensor *a = words(arg[1]), *b = words(arg[2]);
     if (!flag(arg[0], &open) || !a || !b || a->numel() != b->numel()) DECLINE;
-    PyObject* out;
+    THPObjectPtr out;
     uint64_t* o;
     if (arg[3] == Py_None) {
         Tensor t = at::empty(a->sizes(), a->options().requires_grad(false));
@@ -190,12 +187,11 @@ PyObject* elementwise(Host* self, PyObject* const* arg, Py_ssize_t nargs) {
         const Tensor* t = words(arg[3]);
         if (!t || t->numel() != a->numel()) DECLINE;
         o = u64(*t);
-        out = arg[3];
-        Py_INCREF(out);
+        out = THPObjectPtr::dup(arg[3]);
     }
     const uint64_t *pa = u64(*a), *pb = u64(*b);
     const size_t n = (size_t)a->numel();
-    return call(self, out, [&] { return open ? lib.open(self->ctx, pa, pb, o, n) : lib.mask_share(self->ctx, pa, pb, o, n); });
+    return call(self, std::move(out), [&] { return open ? lib.open(self->ctx, pa, pb, o, n) : lib.mask_share(self->ctx, pa, pb, o, n); });
     END_HANDLE_TH_ERRORS
 }
 
@@ -211,10 +207,10 @@ PyObject* gather(Host* self, PyObject* const* arg, Py_ssize_t nargs) {
         DECLINE;
     const int64_t rows = w->size(0), cols = w->size(1);
     uint64_t* o;
-    PyObject* out = axis == COMET_AXIS_COLS ? result(arg[7], rows, ix.ld(), *w, &o) : result(arg[7], ix.ld(), cols, *w, &o);
+    THPObjectPtr out = axis == COMET_AXIS_COLS ? result(arg[7], rows, ix.ld(), *w, &o) : result(arg[7], ix.ld(), cols, *w, &o);
     if (!out) DECLINE;
     const uint64_t *pw = u64(*w), *pb = u64(*b);
-    return call(self, out, [&] {
+    return call(self, std::move(out), [&] {
         return lib.mask_share_gather(self->ctx, pw, pb, o, rows, cols, (int)axis, (int)ix.bs, ix.idx, ix.n, (int)ix.cap);
     });
     END_HANDLE_TH_ERRORS
@@ -230,7 +226,7 @@ PyObject* open_planes(Host* self, PyObject* const* arg, Py_ssize_t nargs) {
     if (!g0 || g0->dim() != 2 || !flag(arg[3], &nm) || (arg[1] != Py_None && (!g1 || !g1->sizes().equals(g0->sizes())))) DECLINE;
     const int64_t k = g0->size(nm ? 1 : 0), n = g0->size(nm ? 0 : 1);
     const size_t need = lib.weight_planes_bytes(k, n);
-    PyObject* out;
+    THPObjectPtr out;
     void* o;
     if (arg[2] == Py_None) {
         Tensor t = at::empty({(int64_t)(need < 16 ? 16 : need)}, g0->options().dtype(c10::kByte).requires_grad(false));
@@ -240,11 +236,10 @@ PyObject* open_planes(Host* self, PyObject* const* arg, Py_ssize_t nargs) {
         const Tensor* t = plain(arg[2]);
         if (!t || t->scalar_type() != c10::kByte || (size_t)t->numel() < need) DECLINE;
         o = t->data_ptr();
-        out = arg[2];
-        Py_INCREF(out);
+        out = THPObjectPtr::dup(arg[2]);
     }
     const uint64_t *p0 = u64(*g0), *p1 = g1 ? u64(*g1) : nullptr;
-    return call(self, out, [&] {
+    return call(self, std::move(out), [&] {
         return nm ? lib.open_weight_planes_neuron_major(self->ctx, p0, p1, k, n, o) : lib.open_weight_planes(self->ctx, p0, p1, k, n, o);
     });
     END_HANDLE_TH_ERRORS
@@ -262,8 +257,7 @@ PyObject* compact(Host* self, PyObject* const* arg, Py_ssize_t nargs) {
     if (!scratch(arg[0], need, &ws)) DECLINE;
     auto* m = static_cast<const uint8_t*>(mask->data_ptr());
     auto *pi = static_cast<int32_t*>(idx->data_ptr()), *pn = static_cast<int32_t*>(n->data_ptr());
-    Py_INCREF(Py_True);
-    return call(self, Py_True, [&] { return lib.compact_mask(self->ctx, m, n_tok, nb, pi, pn, ws, need); });
+    return call(self, THPObjectPtr::dup(Py_True), [&] { return lib.compact_mask(self->ctx, m, n_tok, nb, pi, pn, ws, need); });
     END_HANDLE_TH_ERRORS
 }
 
@@ -331,9 +325,9 @@ PyObject* share(Host* self, PyObject* const* arg, Py_ssize_t nargs) {
     void* ws;
     if (!scratch(arg[0], need, &ws)) DECLINE;
     uint64_t* z;
-    PyObject* out = result(arg[16], p.zr, p.zc, *p.like, &z);
+    THPObjectPtr out = result(arg[16], p.zr, p.zc, *p.like, &z);
     if (!out) DECLINE;
-    return call(self, out, [&] {
+    return call(self, std::move(out), [&] {
         const int bs = (int)ix.bs, cap = (int)ix.cap;
         if (g1 && somm)
             return lib.somm_share_unopened(self->ctx, (int)party, p.m, p.k, p.n, bs, ix.idx, ix.n, cap, p.flags, p.e, p.f, g1, p.a, p.b, p.c, z, ws, need);
@@ -376,17 +370,14 @@ PyObject* group(Host* self, PyObject* const* arg, Py_ssize_t nargs) {
     const size_t need = p0.workspace(ix) * (size_t)count;
     void* ws;
     if (!scratch(arg[0], need, &ws)) DECLINE;
-    PyObject* outs = PyList_New(count);
+    THPObjectPtr outs(PyList_New(count));
     if (!outs) return nullptr;
     for (Py_ssize_t j = 0; j < count; ++j) {
-        PyObject* z = result(given == Py_None ? Py_None : PyList_GET_ITEM(given, j), p0.zr, p0.zc, *p0.like, &ops[j].Z_i);
-        if (!z) {
-            Py_DECREF(outs);
-            DECLINE;
-        }
-        PyList_SET_ITEM(outs, j, z);
+        THPObjectPtr z = result(given == Py_None ? Py_None : PyList_GET_ITEM(given, j), p0.zr, p0.zc, *p0.like, &ops[j].Z_i);
+        if (!z) DECLINE;
+        PyList_SET_ITEM(outs.get(), j, z.release());
     }
-    return call(self, outs, [&] {
+    return call(self, std::move(outs), [&] {
         return lib.share_group(self->ctx, somm ? COMET_OP_SOMM : COMET_OP_SIMM, (int)count, ops, p0.m, p0.k, p0.n, (int)ix.bs, ix.idx,
                                ix.n, (int)ix.cap, p0.flags, ws, need);
     });

@@ -162,3 +162,23 @@ def test_current_stream_and_capture(both):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want)
+
+
+def test_an_allocation_that_fails_leaves_nothing_behind(both):
+    """The second result of a group does not fit: the exception is torch's, and the first one is given back."""
+    import gc
+    m, k, bs, t = 8192, 2, 16, 64                             # results of 64 MB
+    idx, e, a, c_i = i32(*range(t)), words(m, k), words(m, k), words(m, t * bs)
+    f, b = words(k, t * bs), words(k, t * bs)
+    both[0].workspace(1 << 26)
+    gc.collect()
+    torch.cuda.empty_cache()
+    before, total = torch.cuda.memory_allocated(), torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (100 << 20)) / total)
+    try:
+        with pytest.raises(torch.OutOfMemoryError):
+            both[0].share_group("somm", bs, idx, None, t, [(j, e, f, a, b, c_i) for j in (0, 1)])
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    gc.collect()
+    assert torch.cuda.memory_allocated() == before
