@@ -373,6 +373,7 @@ PyObject* group(Host* self, PyObject* const* arg, Py_ssize_t nargs) {
     THPObjectPtr outs(PyList_New(count));
     if (!outs) return nullptr;
     for (Py_ssize_t j = 0; j < count; ++j) {
+        if (given != Py_None && PyList_GET_ITEM(given, j) == Py_None) DECLINE;   // (no result of its own for one member of a list)
         THPObjectPtr z = result(given == Py_None ? Py_None : PyList_GET_ITEM(given, j), p0.zr, p0.zc, *p0.like, &ops[j].Z_i);
         if (!z) DECLINE;
         PyList_SET_ITEM(outs.get(), j, z.release());

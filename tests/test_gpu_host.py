@@ -112,6 +112,9 @@ def test_share_calls(both, kind, fmt):
                                                     **more)
         assert same(both, lambda c: group(c, members))
         assert same(both, lambda c: group(c, members[:1], out=[torch.empty_like(c_i)]))
+        assert same(both, lambda c: group(c, members, out=(torch.empty_like(c_i), torch.empty_like(c_i))))
+        for bad in ([None, None], [torch.empty_like(c_i), None], [torch.empty_like(c_i)], [torch.empty_like(c_i), 3]):
+            assert not same(both, lambda c: group(c, members, out=list(bad)))
         assert not same(both, lambda c: group(c, []))
         assert not same(both, lambda c: group(c, members * 5))
         assert not same(both, lambda c: group(c, [members[0], (1, e[:4].contiguous(), f, a[:4].contiguous(), b, c_i[:4].contiguous())]))
