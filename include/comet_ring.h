@@ -384,9 +384,10 @@ int comet_truncate_share(comet_ctx* ctx, int party, const uint64_t* z, uint64_t*
  *                         clamped to 256
  *   COMET_TUNE_GEMM_TILE: 2 forces an output tile of 64 rows whatever m is
  *                         (64 columns; 128 for large products on weight planes)
- *   COMET_TUNE_SKINNY:    calls with m <= 8, on weight planes m <= 32, normally
- *                         take a kernel bound by reading the weights once; 1
- *                         sends them to the matrix-core kernel like any other
+ *   COMET_TUNE_SKINNY:    calls with m <= 8, on weight planes and small ones
+ *                         on words m <= 32, normally take a kernel that streams the
+ *                         weights without staging them; 1 sends every call of up to
+ *                         32 rows to the matrix-core kernel with staged tiles
  *   COMET_TUNE_SKINNY_SLICES: pieces the stacked contraction is cut into by
  *                         the vector-ALU kernel (default: as many as
  *                         fill the places on the chip a few times over)

@@ -488,14 +488,17 @@ long few_units(const GemmParams& p, int members) {
     return (long)((p.m + 31) / 32) * ((p.n_cap + 127) / 128) * 2 * ((p.kc_cap + KSTEP - 1) / KSTEP) * members;
 }
 
+// COMET_TUNE_SKINNY = 1: up to 32 rows go to the tiles
+bool rows_to_tiles(const comet_ctx* ctx, const GemmParams& p) { return ctx->skinny_mode == 1 && p.m <= COMET_FEWROW_MAX_ROWS; }
+
 // Does a product take the kernel whose wavefronts stream by themselves (ring_fewrow.hip)?  Up to 32 rows on planes
 // always; on words up to 16 units per compute unit (13: 9 and 32 rows, k = 4096, n = 1664 33 and 41 us with the
 // 32 x 256 tile, 31 and 36 here; 32 rows, 819 gathered row by row x 1001 46 against 21; but 27: 9 rows, 5120 x 2752 49
 // against 53); of more rows the smallest products, up to half a unit (128 x 256 x 256 13.2 against 12.7, 64 x 64 x 64 11.3
 // against 8.8; but one unit: 256 x 256 x 256 13.1 against 15.1).
 bool takes_few_rows(const comet_ctx* ctx, const GemmParams& p) {
-    if (p.row_comp || p.tmask || ctx->gemm_tile == 2 || ctx->gemm_chunk > 0) return false;
-    if (p.w_planes && p.m <= COMET_FEWROW_MAX_ROWS) return ctx->skinny_mode != 1;
+    if (p.row_comp || p.tmask || ctx->gemm_tile == 2 || ctx->gemm_chunk > 0 || rows_to_tiles(ctx, p)) return false;
+    if (p.w_planes && p.m <= COMET_FEWROW_MAX_ROWS) return true;
     return 2 * few_units(p, 1) <= (p.m <= COMET_FEWROW_MAX_ROWS ? 32l : 1l) * ctx->num_cu;
 }
 
@@ -504,9 +507,9 @@ bool takes_few_rows(const comet_ctx* ctx, const GemmParams& p) {
 // 65 x 640 x 2560 44.0 -> 41.7 at 19 units; at 24 units four of 65 x 640 x 1664 50 -> 55).
 bool group_takes_few_rows(const comet_ctx* ctx, const GemmParams& p, int members) {
     if (members < 2 || !p.w_planes || p.n_cap < 1 || p.kc_cap < 1 || ctx->group_mode != 0 || ctx->gemm_tile == 2 ||
-        ctx->gemm_chunk > 0)
+        ctx->gemm_chunk > 0 || rows_to_tiles(ctx, p))
         return false;
-    if (p.m <= COMET_FEWROW_MAX_ROWS) return ctx->skinny_mode != 1;
+    if (p.m <= COMET_FEWROW_MAX_ROWS) return true;
     return few_units(p, members) <= 20l * ctx->num_cu;
 }
 
@@ -515,7 +518,7 @@ bool group_takes_few_rows(const comet_ctx* ctx, const GemmParams& p, int members
 // 100 x 64 11.0 -> 9.0, and 2.5 us less of the host's time; but 64 x 128 x 256 9.5 -> 10.5, 128 x 64 x 3072 (384 tiles)
 // 14.6 -> 15.7.
 bool takes_direct(const comet_ctx* ctx, const GemmParams& p) {
-    if (p.row_comp || p.tmask || ctx->gemm_tile == 2 || ctx->gemm_chunk > 0 || ctx->gemm_grid > 0) return false;
+    if (p.row_comp || p.tmask || ctx->gemm_tile == 2 || ctx->gemm_chunk > 0 || ctx->gemm_grid > 0 || rows_to_tiles(ctx, p)) return false;
     const long tiles = (long)((p.m + 31) / 32) * ((p.n_cap + 31) / 32);
     return p.kc_cap >= 1 && p.kc_cap <= 100 && tiles <= ctx->num_cu;
 }

@@ -11,6 +11,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 import oracle as co                                   # noqa: E402
+from kernel_names import kernels                      # noqa: E402
 from workloads import rng                             # noqa: E402
 
 
@@ -36,8 +37,9 @@ def u64(seed, stream, *shape):
     return rng.uniform_u64(seed, stream, int(np.prod(shape))).reshape(shape)
 
 
-def check(ctx, kind, m, other, bs, kept, fmt, full, party=1, seed=900):
-    """One share call: ``other`` is the axis that is not indexed (k of SOMM, n of SIMM)."""
+def check(ctx, kind, m, other, bs, kept, fmt, full, party=1, seed=900, kernel=None):
+    """One share call: ``other`` is the axis that is not indexed (k of SOMM, n of SIMM).  ``kernel``: how the name of the
+    kernel that has to take the call begins."""
     print("[gpu-kernels] %s m=%d other=%d bs=%d blocks=%d %s full=%s" % (kind, m, other, bs, len(kept), fmt, full),
           flush=True)
     sys.stdout.flush()
@@ -54,16 +56,23 @@ def check(ctx, kind, m, other, bs, kept, fmt, full, party=1, seed=900):
         a_sel, b_sel = co.index_cols(a, idx, bs), co.index_rows(b, idx, bs)
     want = co.beaver_share(party, e, f, a_sel, b_sel, c)
     gi = torch.from_numpy(idx).cuda()
-    f_d, b_d = up(f), up(b if full else b_sel)
+    b = b if full else b_sel
+    tr = fmt == "neuron_major"
+    e_d, a_d, f_d, b_d, c_d = up(e), up(a if full else a_sel), up(f.T if tr else f), up(b.T if tr else b), up(c)
     if fmt == "planes":
         f_d, b_d = ctx.open_weight_planes(f_d), ctx.open_weight_planes(b_d)
-    if kind == "somm":
-        z = ctx.somm_share(party, bs, gi, None, t, up(e), f_d, up(a), b_d, up(c), b_full=full)
-    else:
-        z = ctx.simm_share(party, bs, gi, None, t, up(e), f_d, up(a if full else a_sel), b_d, up(c), a_full=full,
-                           b_full=full)
+
+    def call():
+        if kind == "somm":
+            return ctx.somm_share(party, bs, gi, None, t, e_d, f_d, a_d, b_d, c_d, b_full=full, neuron_major=tr)
+        return ctx.simm_share(party, bs, gi, None, t, e_d, f_d, a_d, b_d, c_d, a_full=full, b_full=full)
+
+    z = call()
     torch.cuda.synchronize()
     assert np.array_equal(down(z), want)
+    if kernel:
+        ran = kernels(call)
+        assert len([name for name in ran if name.startswith(kernel)]) == 1, ran
 
 
 # Contraction of one half in words (steps of 32, stacked and taken in pairs): one step (the only pair
@@ -144,15 +153,24 @@ def test_words_beyond_the_cache(ctx, kind, m):
     check_columns(ctx, kind, m, k, n, "words")
 
 
-# The 32 x 128 tile, which plain calls take only with the few-row kernels switched off.
+# The 32 x 128 tile on planes and the 32 x 256 tile on words, whatever the size, with the few-row kernels switched off:
+# remainders of the contraction and of the columns, rows of B_i as they come, gathered by blocks of a power of two and of
+# any other length, neuron-major weights.
 @pytest.mark.parametrize("kind", ["somm", "simm"])
 @pytest.mark.parametrize("m,other", [(1, 31), (9, 33), (31, 64), (32, 95), (32, 300)])
-def test_planes_32x128_tile(ctx, kind, m, other):
+@pytest.mark.parametrize("fmt,bs", [("planes", 16), ("planes", 48), ("words", 32), ("words", 21), ("words", 8), ("words", 5),
+                                    ("neuron_major", 16)])
+def test_32_row_tiles(ctx, kind, m, other, fmt, bs):
     import paper_2505_07239_amd as comet
+    if fmt == "neuron_major":
+        if kind == "simm":
+            pytest.skip("neuron-major weights belong to SOMM")
+        other += other % 2
+    kernel = "ring_planes_kernel<1, 4, 2, 2," if fmt == "planes" else "ring_gemm_kernel<1, 4, 1, 2,"
     ctx.set_tuning(comet.TUNE_SKINNY, 1)
     try:
-        check(ctx, kind, m, other, 16, (0, 2, 3, 5, 6, 7, 9, 10, 13), "planes", True)
-        check(ctx, kind, m, other, 16, (1, 4), "planes", False)
+        check(ctx, kind, m, other, bs, (0, 2, 3, 5, 6, 7, 9, 10, 13), fmt, True, kernel=kernel)
+        check(ctx, kind, m, other, bs, (1, 4), fmt, False, kernel=kernel)
     finally:
         ctx.set_tuning(comet.TUNE_SKINNY, 0)
 
