@@ -506,10 +506,12 @@ bool takes_few_rows(const comet_ctx* ctx, const GemmParams& p) {
 // twenty units per compute unit (two products of 128 x 768 x 320 26.4 -> 21.7 us, four of 256 x 320 x 768 47 -> 36, two of
 // 65 x 640 x 2560 44.0 -> 41.7 at 19 units; at 24 units four of 65 x 640 x 1664 50 -> 55).
 bool group_takes_few_rows(const comet_ctx* ctx, const GemmParams& p, int members) {
-    if (members < 2 || !p.w_planes || p.n_cap < 1 || p.kc_cap < 1 || ctx->group_mode != 0 || ctx->gemm_tile == 2 ||
+    if (members < 2 || !p.w_planes || p.n_cap < 1 || p.kc_cap < 1 || ctx->group_mode == 2 || ctx->gemm_tile == 2 ||
         ctx->gemm_chunk > 0 || rows_to_tiles(ctx, p))
         return false;
     if (p.m <= COMET_FEWROW_MAX_ROWS) return true;
+    // (the grouped launch of tiles starts at 65 rows)
+    if (ctx->group_mode != 0) return p.m <= 64;
     return few_units(p, members) <= 20l * ctx->num_cu;
 }
 

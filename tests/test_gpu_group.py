@@ -5,7 +5,7 @@ The grouped matrix-core launch is forced (``COMET_TUNE_GROUP`` = 1) on shapes th
 quickly; the cases cover a workgroup range that runs across members, whole owned tiles (the grid
 divides the tile count) and shared ones, contractions longer than one accumulation segment, a
 device-side block count below the capacity, the most members a group takes, and the fallbacks
-(word operands, few rows, grouping switched off), which must give the same result."""
+(word operands, grouping switched off), which must give the same result."""
 import ctypes
 import sys
 
@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 import oracle as co                                   # noqa: E402
+from kernel_names import kernels                      # noqa: E402
 from workloads import rng                             # noqa: E402
 
 SENTINEL = np.uint64(0x0123456789ABCDEF)
@@ -67,8 +68,9 @@ def _member(seed, kind, party, m, k, n, bs, idx, cap):
     return dict(party=party, e=e, f=f, a=a, b=b, c=c, want=want)
 
 
-def _run_group(ctx, kind, m, k, n, bs, kept, spare, parties, planes=True, seed=0, single=False):
-    """``single``: the members through one ``somm_share`` / ``simm_share`` call each instead."""
+def _run_group(ctx, kind, m, k, n, bs, kept, spare, parties, planes=True, seed=0, single=False, names=None):
+    """``single``: the members through one ``somm_share`` / ``simm_share`` call each instead.  ``names``: how the names of
+    the kernels that have to run begin."""
     idx = np.array(sorted(kept), dtype=np.int32)
     t, cap = len(idx), len(idx) + spare
     kc = t * bs
@@ -83,11 +85,13 @@ def _run_group(ctx, kind, m, k, n, bs, kept, spare, parties, planes=True, seed=0
         zshape = (m, cap * bs) if kind == "somm" else (m, n)
         outs.append(torch.full(zshape, int(SENTINEL.view(np.int64)), dtype=torch.int64, device="cuda"))
         wants.append(mb["want"])
-    if single:
-        call = ctx.somm_share if kind == "somm" else ctx.simm_share
-        got = [call(mb[0], bs, gi, n_dev, cap, *mb[1:], out=o) for mb, o in zip(members, outs)]
-    else:
-        got = ctx.share_group(kind, bs, gi, n_dev, cap, members, out=outs)
+    def run():
+        if single:
+            call = ctx.somm_share if kind == "somm" else ctx.simm_share
+            return [call(mb[0], bs, gi, n_dev, cap, *mb[1:], out=o) for mb, o in zip(members, outs)]
+        return ctx.share_group(kind, bs, gi, n_dev, cap, members, out=outs)
+
+    got = run()
     torch.cuda.synchronize()
     for j, (z, want) in enumerate(zip(got, wants)):
         z = down(z)
@@ -96,6 +100,9 @@ def _run_group(ctx, kind, m, k, n, bs, kept, spare, parties, planes=True, seed=0
             assert np.all(z[:, kc:] == SENTINEL), "member %d wrote beyond the kept columns" % j
         else:
             assert np.array_equal(z, want), "member %d" % j
+    if names:
+        ran = kernels(run)
+        assert len(ran) == len(names) and all(r.startswith(w) for r, w in zip(ran, names)), ran
 
 
 # (kind, m, k, n, bs, kept blocks, spare capacity, parties of the members, forced grid)
@@ -175,17 +182,19 @@ def test_share_group_automatic_and_switched_off(ctx, kind, mode):
 
 
 @pytest.mark.parametrize("kind", ["somm", "simm"])
-def test_share_group_fallbacks(ctx, kind):
-    """Word operands and activations of at most 64 rows are not grouped even when asked to."""
+@pytest.mark.parametrize("mode", [1, 3])
+def test_share_group_forced(ctx, kind, mode):
+    """Every group on weight planes runs as one packing and one share launch when asked to, up to 64 rows in the few-row
+    kernel; word operands never do."""
     import paper_2505_07239_amd as comet
-    ctx.set_tuning(comet.TUNE_GROUP, 1)
+    ctx.set_tuning(comet.TUNE_GROUP, mode)
     try:
         dims = (150, 64, 8 * 16) if kind == "somm" else (150, 8 * 16, 64)
         say("%s group of word operands" % kind)
         _run_group(ctx, kind, *dims, 16, (1, 2, 6), 0, (0, 1), planes=False, seed=960)
-        for m in (5, 64):
+        for m, kernel in ((5, "ring_fewrow_group_kernel"), (64, "ring_fewrow_group_kernel"), (65, "ring_planes_group_kernel")):
             say("%s group with m=%d" % (kind, m))
-            _run_group(ctx, kind, m, *dims[1:], 16, (1, 2, 6), 0, (1, 0, 1), seed=970 + m)
+            _run_group(ctx, kind, m, *dims[1:], 16, (1, 2, 6), 0, (1, 0, 1), seed=970 + m, names=["xpack_group_kernel", kernel])
     finally:
         ctx.set_tuning(comet.TUNE_GROUP, 0)
 
