@@ -382,8 +382,10 @@ int comet_truncate_share(comet_ctx* ctx, int party, const uint64_t* z, uint64_t*
  *                         (default: one per compute unit, fewer for tiny work)
  *   COMET_TUNE_GEMM_CHUNK: contraction steps (of 32 words) per scheduling slice,
  *                         clamped to 256
- *   COMET_TUNE_GEMM_TILE: 2 forces an output tile of 64 rows whatever m is
- *                         (64 columns; 128 for large products on weight planes)
+ *   COMET_TUNE_GEMM_TILE: 2 and 3 force an output tile of 64 rows whatever m is
+ *                         (64 columns; 128 for large products on weight planes);
+ *                         on weight words 2 takes the kernel with feeding and
+ *                         multiplying wavefronts, 3 the one whose wavefronts do both
  *   COMET_TUNE_SKINNY:    calls with m <= 8, on weight planes and small ones
  *                         on words m <= 32, normally take a kernel that streams the
  *                         weights without staging them; 1 sends every call of up to

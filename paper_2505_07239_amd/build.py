@@ -17,7 +17,7 @@ SOURCES = ["ring_gemm_planes_128x64_own.hip", "ring_gemm_group_128x64.hip", "rin
            "ring_gemm_planes_128x64.hip", "ring_gemm_planes_64x128.hip", "ring_gemm_planes_64x128_listed.hip",
            "ring_gemm_planes_64x64.hip", "ring_gemm_planes_64x64_listed.hip",
            "ring_gemm_planes_32x128.hip", "ring_gemm_planes_32x128_listed.hip",
-           "ring_words_64x64.hip", "ring_words_64x64_listed.hip", "ring_tile_32x256.hip", "ring_tile_32x256_listed.hip",
+           "ring_words_64x64.hip", "ring_words_64x64_listed.hip", "ring_tile_32x256.hip", "ring_tile_32x256_listed.hip", "ring_tile_64x64.hip", "ring_tile_64x64_listed.hip",
            "ring_gemm.hip", "wplanes.hip", "ring_skinny.hip", "ring_fewrow.hip", "ctx.hip", "elementwise.hip", "compact.hip",
            "components.hip", "glue.hip", "probe.hip"]
 FLAGS = ["-O3", "-std=c++20", "--offload-arch=gfx950", "-fPIC", "-fvisibility=default",

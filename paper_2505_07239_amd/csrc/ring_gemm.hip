@@ -497,7 +497,7 @@ bool rows_to_tiles(const comet_ctx* ctx, const GemmParams& p) { return ctx->skin
 // against 53); of more rows the smallest products, up to half a unit (128 x 256 x 256 13.2 against 12.7, 64 x 64 x 64 11.3
 // against 8.8; but one unit: 256 x 256 x 256 13.1 against 15.1).
 bool takes_few_rows(const comet_ctx* ctx, const GemmParams& p) {
-    if (p.row_comp || p.tmask || ctx->gemm_tile == 2 || ctx->gemm_chunk > 0 || rows_to_tiles(ctx, p)) return false;
+    if (p.row_comp || p.tmask || ctx->gemm_tile >= 2 || ctx->gemm_chunk > 0 || rows_to_tiles(ctx, p)) return false;
     if (p.w_planes && p.m <= COMET_FEWROW_MAX_ROWS) return true;
     return 2 * few_units(p, 1) <= (p.m <= COMET_FEWROW_MAX_ROWS ? 32l : 1l) * ctx->num_cu;
 }
@@ -506,7 +506,7 @@ bool takes_few_rows(const comet_ctx* ctx, const GemmParams& p) {
 // twenty units per compute unit (two products of 128 x 768 x 320 26.4 -> 21.7 us, four of 256 x 320 x 768 47 -> 36, two of
 // 65 x 640 x 2560 44.0 -> 41.7 at 19 units; at 24 units four of 65 x 640 x 1664 50 -> 55).
 bool group_takes_few_rows(const comet_ctx* ctx, const GemmParams& p, int members) {
-    if (members < 2 || !p.w_planes || p.n_cap < 1 || p.kc_cap < 1 || ctx->group_mode == 2 || ctx->gemm_tile == 2 ||
+    if (members < 2 || !p.w_planes || p.n_cap < 1 || p.kc_cap < 1 || ctx->group_mode == 2 || ctx->gemm_tile >= 2 ||
         ctx->gemm_chunk > 0 || rows_to_tiles(ctx, p))
         return false;
     if (p.m <= COMET_FEWROW_MAX_ROWS) return true;
@@ -520,9 +520,50 @@ bool group_takes_few_rows(const comet_ctx* ctx, const GemmParams& p, int members
 // 100 x 64 11.0 -> 9.0, and 2.5 us less of the host's time; but 64 x 128 x 256 9.5 -> 10.5, 128 x 64 x 3072 (384 tiles)
 // 14.6 -> 15.7.
 bool takes_direct(const comet_ctx* ctx, const GemmParams& p) {
-    if (p.row_comp || p.tmask || ctx->gemm_tile == 2 || ctx->gemm_chunk > 0 || ctx->gemm_grid > 0 || rows_to_tiles(ctx, p)) return false;
+    if (p.row_comp || p.tmask || ctx->gemm_tile >= 2 || ctx->gemm_chunk > 0 || ctx->gemm_grid > 0 || rows_to_tiles(ctx, p)) return false;
     const long tiles = (long)((p.m + 31) / 32) * ((p.n_cap + 31) / 32);
     return p.kc_cap >= 1 && p.kc_cap <= 100 && tiles <= ctx->num_cu;
+}
+
+// Products on words of more than 32 rows: the 64 x 64 tile whose four wavefronts load, split, stage and multiply in one
+// instruction stream, two workgroups per compute unit (ring_tile.h), or the one with four feeding and four multiplying
+// wavefronts (ring_words.h)?  The second is ahead once its workgroups have a few pairs of steps each (512 x 3000 x 2560 254
+// -> 227 us, 96 x 384 x 2048 25 -> 18), the first
+//   * up to one pair of steps per compute unit, where what counts is how soon the first step is multiplied: 64 x 768 x 320
+//     12.4 against 13.4 us, 40 x 160 x 1024 10.9 against 12.4, 129 x 384 x 320 13.2 against 14.7 (but from there on
+//     64 x 1024 x 768, 1.5 pairs, 18.6 against 15.9);
+//   * where the second has to share the units out evenly, without teams of row tiles (three, five, six of them ..: see
+//     UnitWalk), or reads neuron-major weights in such shares, and twice as many workgroups give slices that are hardly longer:
+//     400 x 2560 x 640 60 against 67 us, 150 x 4096 x 1664 92 against 101, neuron-major 150 x 4096 x 960 59 against 71.
+//     Not where the slices are a tenth longer (400 x 2560 x 1024 91 against 82) or a tile has one to four of them and more
+//     than eight pairs each (320 x 1664 x 2048 82 against 77).
+// Row sets: up to 64 rows and one pair per unit (33 rows, 60 blocks of 16, n = 96 18.9 against 20.7; more rows are a draw),
+// and with a ragged last row tile, which lists fewer steps than the others and so reads the weights at times of its own,
+// where the lists are long and the columns few (77 rows, 800 blocks of 16, n = 500 86 against 98, 130 rows 105 against 114,
+// 400 rows 256 against 266; but n = 1024 100 rows 110 against 102, 40 blocks of 32 28 against 24).
+// Result blocks: up to 64 rows and sixteen pairs per unit (33 rows, 344 blocks of 32, k = 512 36 against 47; 64 rows, 100
+// blocks, k = 1024 31 against 34; but 344 blocks, k = 1024, 21 pairs, 71 against 69).
+// Rows looked up one by one always take the second (256 rows x 819 x 1001 39 against 50).
+bool takes_staged_tile(const comet_ctx* ctx, const GemmParams& p) {
+    if (ctx->gemm_tile >= 2) return ctx->gemm_tile == 3;
+    if (p.w_planes || ctx->gemm_chunk > 0 || (p.kind == KIND_SIMM && p.b_full && p.bs_shift < 3)) return false;
+    const long cu = (ctx->num_cu / 8) * 8, tiles_m = (p.m + 63) / 64, tiles = tiles_m * ((p.n_cap + 63) / 64);
+    if (p.row_comp) return p.m <= 64 && tiles * p.ks_cap <= 16 * cu;
+    if (p.tmask)
+        return (p.m <= 64 && tiles * p.ks_cap <= cu) || (p.m > 64 && p.m % 64 != 0 && p.n_cap <= 512 && p.kc_cap >= 8192);
+    if (tiles * p.ks_cap <= cu) return true;
+    // the longest run of a workgroup: in pairs when the second kernel shares the units out evenly, in steps when the first
+    // cuts a tile into slices (see UnitWalk)
+    const long even = (tiles * p.ks_cap + cu - 1) / cu;
+    if (tiles <= cu) {
+        const long slices = cu / tiles < p.ks_cap ? cu / tiles : p.ks_cap;
+        if ((p.ks_cap + slices - 1) / slices <= tiles * p.ks_cap / cu + UnitWalk<false>::SPLIT_COST) return false;
+    }
+    if (tiles > 2 * cu) return false;
+    const long slices = 2 * cu / tiles < 2l * p.ks_cap ? 2 * cu / tiles : 2l * p.ks_cap;
+    const long sliced = (2l * p.ks_cap + slices - 1) / slices;
+    if (sliced > tiles * p.ks_cap / cu + UnitWalk<false, 1>::SPLIT_COST) return false;
+    return p.w_tr || (cu % tiles_m != 0 && 10 * sliced <= 11 * even + 10 && (slices >= 5 || even <= 8));
 }
 
 int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t ws_bytes) {
@@ -548,10 +589,17 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
     // will own its tiles (and then initialise Z itself).
     // columns of the 64- and 32-row tiles
     const int narrow_bn = p.w_planes ? planes_narrow_bn(ctx, p) : 64, flat_bn = p.w_planes ? 128 : 256;
-    auto plan = [&](int bm) { plan_gemm(ctx, p, bm, bm == 128 ? 64 : bm == 64 ? narrow_bn : flat_bn, bm == 32 && !p.w_planes ? 1 : 2); };
+    const bool staged = !p.w_planes && takes_staged_tile(ctx, p);
+    auto plan = [&](int bm) {
+        if (p.w_planes) plan_gemm(ctx, p, bm, bm == 128 ? 64 : bm == 64 ? narrow_bn : flat_bn, bm == 128);
+        else if (bm == 32) plan_gemm(ctx, p, 32, flat_bn, false, 1);
+        else if (staged) plan_gemm(ctx, p, 64, 64, false, 1, Tile<2, 2, 1, 1>::WG_PER_CU);
+        else plan_gemm(ctx, p, 64, 64, true);
+    };
     auto launch = [&](int bm) {
         plan(bm);
-        if (!p.w_planes) return bm == 64 ? launch_words(ctx, what, p) : launch_gemm<1, 4, 1, 2>(ctx, what, p);
+        if (!p.w_planes && bm == 32) return launch_gemm<1, 4, 1, 2>(ctx, what, p);
+        if (!p.w_planes) return staged ? launch_gemm<2, 2, 1, 1>(ctx, what, p) : launch_words(ctx, what, p);
         if (bm == 128) return launch_planes<2, 2, 4, 2>(ctx, what, p);
         if (bm == 64 && narrow_bn == 64) return launch_planes<2, 2, 2, 2>(ctx, what, p);
         if (bm == 64) return launch_planes<1, 4, 4, 2>(ctx, what, p);
@@ -560,7 +608,7 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
     // rows per workgroup tile: 128, 64 or 32 (words: 64 or 32)
     int bm = 128;
     const long big_tiles = (long)((p.m + 127) / 128) * ((p.n_cap + 63) / 64);
-    if (ctx->gemm_tile == 2) bm = 64;
+    if (ctx->gemm_tile >= 2) bm = 64;
     else if (p.m <= 32) bm = 32;
     else if (p.m <= 64 || !p.w_planes) bm = 64;
     // a small product (a handful of 128 x 64 tiles) is bound by the fixed cost per workgroup:
@@ -659,7 +707,7 @@ int run_share_group(comet_ctx* ctx, const char* what, GemmParams* ps, int n, voi
     const long tiles = (long)((p0.m + T::BM - 1) / T::BM) * ((p0.n_cap + T::BN - 1) / T::BN);
     const long steps_each = tiles * 2 * ((p0.kc_cap + KSTEP - 1) / KSTEP) / grid;
     const bool few = group_takes_few_rows(ctx, p0, n);
-    const bool grouped = few || (n > 1 && p0.w_planes && p0.m > 64 && p0.n_cap > 0 && ctx->gemm_tile != 2 &&
+    const bool grouped = few || (n > 1 && p0.w_planes && p0.m > 64 && p0.n_cap > 0 && ctx->gemm_tile < 2 &&
                                  (ctx->group_mode == 1 || ctx->group_mode == 3 ||
                                   (ctx->group_mode == 0 && steps_each <= 128)));
     if (!grouped) {

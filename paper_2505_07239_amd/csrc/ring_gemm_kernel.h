@@ -248,13 +248,13 @@ __device__ __forceinline__ int xcd_contiguous(int b, int G) {
 
 
 // Launch plan of the matrix-core kernels for an output tile BM x BN: the grid and whether the launch may turn out to
-// own its tiles.  Fixed before the packing kernel is launched, which has to know whether the share
-// kernel will initialise Z itself.
-inline void plan_gemm(const comet_ctx* ctx, GemmParams& p, int BM, int BN, int per = 2) {
+// own its tiles (owner: the kernel can).  Fixed before the packing kernel is launched, which has to know whether the
+// share kernel will initialise Z itself.
+inline void plan_gemm(const comet_ctx* ctx, GemmParams& p, int BM, int BN, bool owner, int per = 2, int wg_per_cu = 1) {
     const long tiles = (long)((p.m + BM - 1) / BM) * ((p.n_cap + BN - 1) / BN);
     const long pairs_cap = tiles * p.ks_cap;
-    // one workgroup per compute unit, fewer when there are fewer pairs of contraction steps
-    long grid = (ctx->num_cu / 8) * 8;
+    // as many workgroups as the chip holds, fewer when there are fewer pairs of contraction steps
+    long grid = (ctx->num_cu / 8) * 8 * wg_per_cu;
     if (grid < 8) grid = 8;
     if (pairs_cap < grid) grid = pairs_cap < 8 ? (pairs_cap < 1 ? 1 : pairs_cap) : (pairs_cap / 8) * 8;
     if (ctx->gemm_grid > 0) grid = ctx->gemm_grid;
@@ -265,8 +265,8 @@ inline void plan_gemm(const comet_ctx* ctx, GemmParams& p, int BM, int BN, int p
     p.tile_bm = BM;
     p.tile_bn = BN;
     // Owned tiles: plain product, default slicing, a tile count (at full capacity; the kernel checks the
-    // device-resident counts) that the grid divides, and on planes the 128 x 64, on words the 64 x 64 tile
-    p.own_try = (!p.row_comp && !p.tmask && ctx->gemm_chunk == 0 && (BM == 128 || (BM == 64 && !p.w_planes)) && tiles % grid == 0) ? 1 : 0;
+    // device-resident counts) that the grid divides
+    p.own_try = (owner && !p.row_comp && !p.tmask && ctx->gemm_chunk == 0 && tiles % grid == 0) ? 1 : 0;
 }
 
 // Launches a share kernel; when this launch is a timed one the event pair rides on the dispatch

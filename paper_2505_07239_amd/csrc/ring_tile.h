@@ -1,7 +1,9 @@
-// The 32 x 256 output tile of the int8 matrix-core kernel on weight WORDS (see ring_gemm.hip for the
-// formulation): up to 32 rows, where the product is bound by reading the weights and 2 KB of every weight row in one
-// piece count for more than the matrix instructions.  The loader that stages both operands, one contraction
-// step, the stream-K kernel and its launcher.  More rows: ring_words.h, small products: ring_fewrow.hip.
+// The int8 matrix-core kernel on weight WORDS whose wavefronts load, split, stage and multiply in one instruction stream
+// (see ring_gemm.hip for the formulation), with two output tiles: 32 x 256 up to 32 rows, where the product is bound by
+// reading the weights and 2 KB of every weight row in one piece count for more than the matrix instructions; 64 x 64, two
+// workgroups per compute unit, for products of few steps (takes_staged_tile() in ring_gemm.hip).  The loader that stages
+// both operands, one contraction step, the stream-K kernel and its launcher.  More rows: ring_words.h, the smallest
+// products: ring_fewrow.hip.
 #pragma once
 
 #include "ring_gemm_kernel.h"
@@ -546,7 +548,6 @@ __global__ __launch_bounds__(GT, (Tile<WAVES_M, WAVES_N, WM, WN>::WG_PER_CU)) vo
     __shared__ __align__(16) unsigned char xs1[T::XBYTES];
     __shared__ __align__(16) unsigned char xs2[T::XBYTES];
     __shared__ __align__(16) unsigned char wsm[T::WSTAGES * T::WBYTES];
-    if (p.tile_sel && *p.tile_sel != p.tile_sel_want) return;   // the other tile shape was chosen
     const Geometry q = gemm_geometry<T::BM, T::BN, KIND, LISTED, 1>(p);
     if (q.units == 0) return;
     const int G = gridDim.x;
@@ -574,6 +575,8 @@ GemmKernel gemm_kernel_for(const GemmParams& p) {
     }
 }
 
+extern template GemmKernel gemm_kernel_for<2, 2, 1, 1, false>(const GemmParams&);
+extern template GemmKernel gemm_kernel_for<2, 2, 1, 1, true>(const GemmParams&);
 extern template GemmKernel gemm_kernel_for<1, 4, 1, 2, false>(const GemmParams&);
 extern template GemmKernel gemm_kernel_for<1, 4, 1, 2, true>(const GemmParams&);
 

@@ -1,0 +1,5 @@
+// The 64 x 64 output tile on weight words: the variants that walk a step list (Protocol 3
+// with per-token row sets) (see ring_tile.h).
+#include "ring_tile.h"
+
+template comet_gemm::GemmKernel comet_gemm::gemm_kernel_for<2, 2, 1, 1, true>(const GemmParams&);

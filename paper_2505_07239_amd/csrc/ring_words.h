@@ -21,14 +21,15 @@
 //
 // Why two kinds of wavefront: the vector work of the digit split and the waits for memory stay out of
 // the instruction stream of the matrix instructions, and the two share the SIMD's issue slots without
-// waiting for each other.  Kernels that did both in every wavefront (32x32x32, operands of both sides staged in LDS,
-// 64 x 64 and 128 x 64 tiles) took, for 64 rows, k = 4096, n = 11008 (722 MB of words), 220 us, of which 180
+// waiting for each other.  Kernels that do both in every wavefront (32x32x32, operands of both sides staged in LDS,
+// 64 x 64 and 128 x 64 tiles) take, for 64 rows, k = 4096, n = 11008 (722 MB of words), 220 us, of which 180
 // remained when every load hit the cache and 160 when eight of nine matrix instructions were left out.  What bounds this
 // one is power, as for the kernel on planes (ring_gemm_planes.h): 185 us for the same product from a cool chip, 245
 // in a long run of them, and the planes kernel 172 and 220; without the digit split it is no faster.
 // Against those kernels, whole calls: 192 x 1664 x 4096 106 -> 91 us, 512 x 4096 x 1664 238 -> 212, 512 x 4096 x 11008
 // 1486 -> 1361, 64 x 11008 x 4096 235 -> 216; rows gathered in blocks that are no multiple of 16 (256 x 819 x 1001) 50 -> 39.
-// A pair is the least a workgroup can do: calls of 11 to 16 us (128 x 768 x 320) take up to 1 us longer.
+// A pair is the least a workgroup can do; where a workgroup has one or two the 64 x 64 tile of ring_tile.h is ahead
+// (takes_staged_tile() in ring_gemm.hip).
 #pragma once
 
 #include "ring_gemm_kernel.h"
