@@ -91,6 +91,8 @@ using namespace comet_gemm;
 // grid: x = chunks of four 16-word groups, y = chunks of 64 rows, z = 0 (E), 1 (A'), 2 (Z := C).
 // A workgroup packs a 64-row x 64-word tile: the lanes of a wavefront read along the rows, and write adjacent 16-byte
 // units of 64 rows.
+// SETS: with per-token row sets (a variant of its own: their code in the other one cost it 0.1 us a call).
+template <bool SETS>
 __device__ __forceinline__ void xpack_body(const GemmParams& p, const int part, const int xstep) {
     const int nblk = n_blocks(p);
     const int m_eff = n_rows(p);
@@ -127,7 +129,7 @@ __device__ __forceinline__ void xpack_body(const GemmParams& p, const int part, 
     }
     const int kc = p.kind == KIND_SOMM ? p.kc_cap : nblk * p.bs;
     // The loads want the lanes along k (512 bytes of a row per wavefront or half of one), the stores want them along the
-    // rows (a digit group is one run of rows), so the tile passes through LDS in between.
+    // rows (a digit group is one run of rows), so the tile passes through LDS in between (row sets aside, see below).
     typedef u64 u64x2 __attribute__((ext_vector_type(2)));
     constexpr int PITCH = 33;                                  // 16-byte vectors per tile row (32 + padding)
     __shared__ u64x2 tile[64 * PITCH];
@@ -135,105 +137,153 @@ __device__ __forceinline__ void xpack_body(const GemmParams& p, const int part, 
     const int kw = blockIdx.x * 64;                            // first word of the workgroup's four groups
     if (kw >= p.ks_cap * KSTEP) return;                        // uniform over the workgroup
     const bool e_too = h == 0 || p.party;                      // party 0's A' is A_i itself
-    if (!p.tmask && !p.a_full && (p.lde & 1) == 0 && (p.lda & 1) == 0 && kw + 64 <= kc) {
-        // Whole tile, rows as they come and on 16 bytes: two words per lane, all eight rows in flight (a row past the last
-        // one reads the last one's words and packs zeros).  Two members of 128 rows x 768 words 8.5 us with a
-        // branch and a wait per row, 6.4 with four in flight, 5.8 with eight; 64 rows x 12288 words 9.8 -> 9.0.
-        u64x2 e[8], a[8];
+    const int live = m_eff - (int)blockIdx.y * 64;             // rows of the tile that exist (the others pack zeros)
+    const bool pairs = ((p.lde | p.lda) & 1) == 0;             // rows start on 16 bytes
+    // sixteen words of one row -> their units of the eight digits
+    auto store = [&](int trow, int half16, const u64x2 (&w)[8]) {
+        u64 plane[2][8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int v = i * GT + threadIdx.x;                // vector of the tile: row v / 32, words 2 (v % 32) ..
-            const int trow = blockIdx.y * 64 + (v >> 5), kk = kw + 2 * (v & 31);
-            const int row = trow < m_eff ? trow : m_eff > 0 ? m_eff - 1 : 0;
-            e[i] = a[i] = u64x2{0, 0};
-            if (e_too) e[i] = *reinterpret_cast<const u64x2*>(p.E + (size_t)row * p.lde + kk);
-            if (h) a[i] = *reinterpret_cast<const u64x2*>(p.A + (size_t)row * p.lda + kk);
+        for (int o = 0; o < 2; ++o) {
+            u64 v[8];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                v[2 * j] = to_digits(w[4 * o + j].x);
+                v[2 * j + 1] = to_digits(w[4 * o + j].y);
+            }
+            digits_to_planes(v, plane[o]);
+        }
+        const int s = half16 >> 1, g = half16 & 1;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            u64x2* dst = reinterpret_cast<u64x2*>(p.xp) + xp_group(0, xstep + s, t, g, 0) * p.mpad + trow;
+            *dst = u64x2{plane[0][t], plane[1][t]};
+        }
+    };
+    if (SETS && pairs && p.bs % 16 == 0) {
+        // Row sets, sixteen words in one block: a thread packs sixteen words of one row, so that one flag decides about all
+        // of them and nothing else is fetched where it is not set (entries a token does not use take no part, and
+        // their values are not read).  Against the way over LDS below, with one flag per word and with one per sixteen: 33 rows
+        // x 960 words 5.3 and 5.0 us, 4.6 here; 200 rows, 1 % of the flags set, 5.8, 5.5 and 5.0; 256 x 11008, 15 % set,
+        // 15.4, 15.3 and 15.9.
+        const int r = threadIdx.x >> 2, half16 = blockIdx.x * 4 + (threadIdx.x & 3);
+        const int trow = blockIdx.y * 64 + r, k0 = half16 * 16;
+        if (trow >= p.mpad || half16 >= p.ks_cap * 2) return;
+        u64x2 w[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) w[j] = u64x2{0, 0};
+        const int blk = k0 / p.bs;
+        if (r < live && k0 < kc && token_uses(p, trow, blk)) {
+            if (e_too) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) w[j] = *reinterpret_cast<const u64x2*>(p.E + (size_t)trow * p.lde + k0 + 2 * j);
+            }
+            if (h) {
+                const long st = p.a_full ? block_start(p, blk) : 0;
+                const long col = p.a_full ? (st < 0 ? 0 : st) + (k0 - (long)blk * p.bs) : k0;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) w[j] += *reinterpret_cast<const u64x2*>(p.A + (size_t)trow * p.lda + col + 2 * j);
+            }
+        }
+        store(trow, half16, w);
+        return;
+    }
+    if (!SETS && pairs && kw + 64 <= kc && (!p.a_full || p.bs % 16 == 0)) {
+        // Whole tile on 16 bytes: two words per lane, all eight rows in flight.  Two members of 128 rows x 768 words 8.5 us
+        // with a branch and a wait per row, 6.4 with four in flight, 5.8 with eight; 64 rows x 12288 words 9.8 -> 9.0.
+        // A row past the last one reads the last one's words and packs zeros; half a tile that lies behind it as a whole reads
+        // nothing (150 rows x 4096 words, 256 padded, 11.8 us when it did, 7.1 without).
+        // A_i indexed by blocks of 16 or a multiple too: 256 rows x 1664 gathered words 10.0 us word by word, 8.9 here.
+        const int kv = threadIdx.x & 31, r0 = threadIdx.x >> 5;
+        long col = kw + 2 * kv;
+        if (p.a_full && h) {
+            const int blk = (int)col / p.bs;
+            const long st = block_start(p, blk);
+            col = (st < 0 ? 0 : st) + (col - (long)blk * p.bs);
+        }
+        const u64* const first = e_too ? p.E + kw + 2 * kv : p.A + col;
+        const long ld = e_too ? p.lde : p.lda;
+        const size_t row0 = (size_t)blockIdx.y * 64;
+        u64x2 x[8], a[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = a[i] = u64x2{0, 0};
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            if (live <= 32 * half) continue;                   // uniform over the workgroup
+#pragma unroll
+            for (int i = 4 * half; i < 4 * half + 4; ++i) {
+                const int r = 8 * i + r0;
+                x[i] = *reinterpret_cast<const u64x2*>(first + (row0 + (r < live ? r : live - 1)) * ld);
+            }
+            if (h && e_too) {
+#pragma unroll
+                for (int i = 4 * half; i < 4 * half + 4; ++i) {
+                    const int r = 8 * i + r0;
+                    a[i] = *reinterpret_cast<const u64x2*>(p.A + col + (row0 + (r < live ? r : live - 1)) * p.lda);
+                }
+            }
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int v = i * GT + threadIdx.x;
-            const bool on = (int)blockIdx.y * 64 + (v >> 5) < m_eff;
-            tile[(v >> 5) * PITCH + (v & 31)] = on ? e[i] + a[i] : u64x2{0, 0};
-        }
+        for (int i = 0; i < 8; ++i) tile[(8 * i + r0) * PITCH + kv] = 8 * i + r0 < live ? x[i] + a[i] : u64x2{0, 0};
     } else {
         // Word by word, a wavefront along 64 words of a row: what bounds it is the latency of these loads, so a lane keeps
         // its contraction index, looks the block it lies in (indexed A_i, row sets) up once and has sixteen rows in flight.
         // Against a thread that packed sixteen words of one row: 77 rows x 1001 words 13.7 -> 6.2 us, x 819 gathered words
-        // 16.2 -> 5.6; 256 rows x 11008 gathered words with row sets 22.4 -> 20.0; 500 x 11008 gathered 40 -> 36.5.
+        // 16.2 -> 5.6.
         const int kk = kw + (threadIdx.x & 63), r0 = threadIdx.x >> 6;
-        const bool live = kk < kc && m_eff > 0;
         const int k = kk < kc ? kk : kc - 1;
-        long col = k, flag = 0;
-        bool used = live;
-        if (live && (p.a_full || p.tmask)) {
+        const size_t row0 = (size_t)blockIdx.y * 64;
+        long col = k;
+        unsigned uses = kk < kc ? 0xffff : 0;                  // of the sixteen rows
+        if (kc > 0 && live > 0 && (p.a_full || SETS)) {
             const int blk = k / p.bs;
             const long st = block_start(p, blk);
             if (p.a_full) col = (st < 0 ? 0 : st) + (k - blk * p.bs);
-            if (p.tmask) {
-                flag = p.blk_idx[blk];
-                used = flag >= 0 && flag < p.tmask_nb;         // (see token_uses)
-            }
-        }
-        // The uses of the sixteen rows first, all in flight, then their values: entries a token does not use take no part,
-        // and their values are not read.
-        unsigned uses = 0;
-        if (p.tmask) {
-            if (used) {
+            if (SETS) {
+                // The uses of the rows first, all in flight, then their values (entries a token does not use take no part).
+                const long flag = p.blk_idx[blk];
+                const bool listed = flag >= 0 && flag < p.tmask_nb;    // (see token_uses)
                 unsigned char on[16];
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const int trow = blockIdx.y * 64 + r0 + 4 * i;
-                    on[i] = p.tmask[(long)(trow < m_eff ? trow : m_eff - 1) * p.tmask_nb + flag];
+                    const int r = r0 + 4 * i;
+                    on[i] = p.tmask[(long)(row0 + (r < live ? r : live - 1)) * p.tmask_nb + (listed ? flag : 0)];
                 }
+                unsigned set = 0;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) uses |= (on[i] != 0 ? 1u : 0u) << i;
+                for (int i = 0; i < 16; ++i) set |= (on[i] != 0 ? 1u : 0u) << i;
+                uses &= listed ? set : 0;
             }
-        } else if (used) {
-            uses = 0xffff;
         }
-        u64 e[16], a[16];
+        u64 x[16], a[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const int trow = blockIdx.y * 64 + r0 + 4 * i;
-            const bool on = (uses >> i & 1) && trow < m_eff;
-            e[i] = a[i] = 0;
-            if (on && e_too) e[i] = p.E[(size_t)trow * p.lde + k];
-            if (on && h) a[i] = p.A[(size_t)trow * p.lda + col];
+            const int r = r0 + 4 * i;
+            x[i] = a[i] = 0;
+            if (r >= live || !(uses >> i & 1)) continue;
+            if (e_too) x[i] = p.E[(row0 + r) * p.lde + k];
+            if (h) a[i] = p.A[(row0 + r) * p.lda + col];
         }
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-            reinterpret_cast<u64*>(tile)[(r0 + 4 * i) * 2 * PITCH + (threadIdx.x & 63)] = e[i] + a[i];
+            reinterpret_cast<u64*>(tile)[(r0 + 4 * i) * 2 * PITCH + (threadIdx.x & 63)] = x[i] + a[i];
     }
     __syncthreads();
     const int r = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int trow = blockIdx.y * 64 + r, half16 = blockIdx.x * 4 + q;
     if (trow >= p.mpad || half16 >= p.ks_cap * 2) return;      // (the few-row kernel packs 32 rows)
-    u64 plane[2][8];
+    u64x2 w[8];
 #pragma unroll
-    for (int o = 0; o < 2; ++o) {
-        u64 v[8];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const u64x2 t = tile[r * PITCH + 8 * q + 4 * o + j];
-            v[2 * j] = to_digits(t.x);
-            v[2 * j + 1] = to_digits(t.y);
-        }
-        digits_to_planes(v, plane[o]);
-    }
-    const int s = half16 >> 1, g = half16 & 1;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        u64x2* dst = reinterpret_cast<u64x2*>(p.xp) + xp_group(0, xstep + s, t, g, 0) * p.mpad + trow;
-        *dst = u64x2{plane[0][t], plane[1][t]};
-    }
+    for (int j = 0; j < 8; ++j) w[j] = tile[r * PITCH + 8 * q + j];
+    store(trow, half16, w);
 }
 
+template <bool SETS>
 __global__ __launch_bounds__(GT) void xpack_kernel(GemmParams p) {
-    xpack_body(p, blockIdx.z, blockIdx.z == 1 ? p.ks_cap : 0);
+    xpack_body<SETS>(p, blockIdx.z, blockIdx.z == 1 ? p.ks_cap : 0);
     // The ticket of step_list_kernel.  Behind the packing: ahead of a store the compiler reads the
     // parameters and the counts in one batch of scalar loads, behind one word by word through vector loads
     // (9 rows, 64 x 64 words: 14.9 us a call with this store first, 14.6 with it last).
-    if (p.tmask && (blockIdx.x | blockIdx.y | blockIdx.z | threadIdx.x) == 0) p.tile_list[0] = 0;
+    if (SETS && (blockIdx.x | blockIdx.y | blockIdx.z | threadIdx.x) == 0) p.tile_list[0] = 0;
 }
 
 // the members of a group (one shape): grid.z = 3 * member + part
@@ -241,7 +291,7 @@ __global__ __launch_bounds__(GT) void xpack_group_kernel(GemmGroup grp) {
     const GemmParams& p = grp.p[blockIdx.z / 3];
     const int part = blockIdx.z % 3;
     if (part == 0 && p.x_shared) return;                       // packed with an earlier member
-    xpack_body(p, part, p.xstep[part == 1]);
+    xpack_body<false>(p, part, p.xstep[part == 1]);
 }
 
 // ---------------------------------------------------------------------------
@@ -637,7 +687,7 @@ int run_share(comet_ctx* ctx, const char* what, GemmParams p, void* ws, size_t w
         const int slabs = (p.mpad + 63) / 64;
         const long zgx = ((long)p.m * p.n_cap / (2l * 4 * GT) + slabs - 1) / slabs;
         if (zgx > gx) gx = (unsigned)(zgx > 4096 ? 4096 : zgx);
-        hipLaunchKernelGGL(xpack_kernel, dim3(gx, (unsigned)slabs, 3), dim3(GT), 0, ctx->stream, p);
+        hipLaunchKernelGGL(p.tmask ? xpack_kernel<true> : xpack_kernel<false>, dim3(gx, (unsigned)slabs, 3), dim3(GT), 0, ctx->stream, p);
         COMET_LAUNCH_CHECK(ctx, what);
     }
     if (p.ks_cap == 0) return COMET_OK;

@@ -33,7 +33,7 @@ def u64(seed, stream, *shape):
 # the end of the contraction; blocks that divide 64 and blocks that straddle it.
 @pytest.mark.parametrize("row_sets", [False, True])
 @pytest.mark.parametrize("m", [9, 32, 33, 64, 65, 130])
-@pytest.mark.parametrize("bs,t", [(1, 127), (3, 64), (21, 7), (24, 8), (32, 7), (65, 3)])
+@pytest.mark.parametrize("bs,t", [(1, 127), (3, 64), (16, 9), (21, 7), (24, 8), (32, 7), (48, 5), (65, 3)])
 def test_word_by_word(ctx, bs, t, m, row_sets):
     print("[gpu-pack] m=%d bs=%d blocks=%d row_sets=%s" % (m, bs, t, row_sets), flush=True)
     n, party = 40, t & 1
