@@ -238,10 +238,13 @@ void (*pick_kernel(int kind, bool unopened))(GemmParams, const u64*, int) {
 
 }  // namespace
 
-// Workgroups of a variant that share a compute unit (by its registers: accumulators of MR rows and eight weight rows in
-// flight, twelve loads of them unopened).
+// Workgroups per compute unit that one round of the launch is planned for.  Two columns per lane: what the registers of
+// the variant allow (accumulators of MR rows and eight weight rows in flight, twelve loads of them unopened).
+// Word by word fewer than the registers allow (seven or eight): 8 rows, 6000 x 1001 31.6 us with six, 33.4 with eight; 4 rows,
+// 5001 gathered rows x 1001 23.8 with six, 29.0 with seven, 26.4 with eight; 2 rows there 21.3, 22.3 and 22.9, but 1001 x
+// 6001 25.3 with six, 23.4 with seven.
 static int per_cu(int mr, bool vec2, bool unopened) {
-    if (!vec2) return mr <= 4 ? 7 : 6;
+    if (!vec2) return mr == 2 ? 7 : 6;
     if (unopened) return mr == 2 ? 5 : mr == 8 ? 3 : 4;
     return mr == 2 ? 8 : mr == 4 ? 7 : mr == 6 ? 5 : 4;
 }
@@ -277,13 +280,19 @@ int comet_launch_skinny(comet_ctx* ctx, const char* what, const GemmParams& p) {
     // that is nearly empty costs as much as a full one, and every slice adds its partial sums onto Z. 8 rows, both
     // shares of F (768 places), 90 tiles: 271 us with 46 slices (sixteen workgroups a unit), 233 with 8 (720
     // workgroups), 270 with 11 (990); 13 tiles, k = 4096, 43 -> 38; opened (1024 places) 32 tiles, k = 4096, 67 -> 64;
-    // 6 rows, 300 x 20000 33 -> 24; 8 rows, 6000 x 1001 word by word 38 -> 32.  Two rows have little to add onto Z and
-    // wait for memory alone: they take about sixteen workgroups a unit (4096 x 4096 50 us, 52 in one round).
+    // 6 rows, 300 x 20000 33 -> 24; 8 rows, 6000 x 1001 word by word 38 -> 32.  About sixteen workgroups a unit instead
+    //   * for two rows, which have little to add onto Z and wait for memory alone (4096 x 4096 50 us, 52 in one round);
+    //   * opened, where one round would leave a workgroup more than 512 rows of the contraction: beside runs of that
+    //     length the partial sums are little, and shorter ones end closer together (8 rows, 5120 x 11520 189 us in one
+    //     round of 990 rows, 181 in four; 11520 x 5120 210 and 199; 4 rows 161 and 155; 6 rows 171 and 168 where rows are
+    //     gathered, else 160 and 162; 256 rows, 4096 x 4096, 59 and 63; unopened no difference).
     // Every wavefront keeps at least one full batch of rows.
-    const long places = (long)per_cu(MR, vec2, un) * ctx->num_cu;
+    const int per = per_cu(MR, vec2, un);
+    const long places = (long)per * ctx->num_cu;
     long slices = 1;
     double filled = 0.0;
-    const int first = MR > 2 || !vec2 ? 1 : un ? 3 : 2;
+    const bool long_runs = vec2 && !un && (MR != 6 || p.kind == KIND_SIMM) && 2l * p.kc_cap * tiles > 512 * places;
+    const int first = MR == 2 && vec2 ? (un ? 3 : 2) : long_runs ? 16 / per : 1;
     for (int rounds = first; rounds < first + 4 && filled < 0.92; ++rounds) {
         const long s = rounds * places / tiles;
         const double f = (double)(s * tiles) / (double)(rounds * places);

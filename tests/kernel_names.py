@@ -18,8 +18,8 @@ def _libraries():
     return hip, cxx
 
 
-def launches(call):
-    """[(kernel with its template arguments, workgroups)] of one call, in the order of the launches."""
+def _nodes(call):
+    """(kernel with its template arguments, workgroups, threads, function) of the launches of one call, in their order."""
     hip, cxx = _libraries()
     call()                                                    # (workspace and first-launch work outside the capture)
     torch.cuda.synchronize()
@@ -38,9 +38,23 @@ def launches(call):
         name = hip.hipKernelNameRefByPtr(ctypes.c_void_p(params.func), None)
         name = cxx.__cxa_demangle(name, None, None, None).decode()
         name = re.sub(r"\(anonymous namespace\)::|comet_gemm::|^void ", "", name)
-        out.append((re.sub(r"\((GemmParams|GemmGroup|comet|unsigned|int|void).*", "", name), params.grid[0] * params.grid[1] * params.grid[2]))
+        out.append((re.sub(r"\((GemmParams|GemmGroup|comet|unsigned|int|void).*", "", name),
+                    params.grid[0] * params.grid[1] * params.grid[2], params.block[0], params.func))
     return out
 
 
 def kernels(call):
-    return [name for name, _ in launches(call)]
+    """The names of the kernels that one call launches, in the order of the launches."""
+    return [node[0] for node in _nodes(call)]
+
+
+def places(call, kernel):
+    """Workgroups of the launch whose kernel's name begins with ``kernel``, and how many share a compute unit by the
+    kernel's registers and LDS."""
+    hip, _ = _libraries()
+    found = [(grid, threads, func) for name, grid, threads, func in _nodes(call) if name.startswith(kernel)]
+    assert len(found) == 1
+    grid, threads, func = found[0]
+    count = ctypes.c_int(0)
+    assert hip.hipOccupancyMaxActiveBlocksPerMultiprocessor(ctypes.byref(count), ctypes.c_void_p(func), threads, ctypes.c_size_t(0)) == 0
+    return grid, count.value

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 import oracle as co                                   # noqa: E402
-from kernel_names import kernels                      # noqa: E402
+from kernel_names import kernels, places              # noqa: E402
 from workloads import rng                             # noqa: E402
 
 
@@ -332,3 +332,32 @@ def test_group_members_share_activations(ctx, kind, m, k, names):
         ctx.set_tuning(comet.TUNE_GROUP, 0)
     for j, want in enumerate(wants):
         assert np.array_equal(down(got[j]), want), "member %d" % j
+
+
+# Up to 8 rows: one round of workgroups fills the chip as far as the kernel's registers allow (two columns per lane; two rows
+# take two or three rounds, long runs of opened ones about sixteen workgroups a unit), six or seven a unit word by word.
+@pytest.mark.parametrize("unopened", [False, True])
+@pytest.mark.parametrize("kind", ["somm", "simm"])
+@pytest.mark.parametrize("m", [2, 3, 6, 7])
+def test_slices_fill_the_chip(ctx, kind, m, unopened):
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    draw = lambda *shape: torch.randint(-2 ** 63, 2 ** 63 - 1, shape, dtype=torch.int64, device="cuda")
+
+    def plan(k, n, bs):
+        print("[gpu-kernels] slices %s m=%d k=%d n=%d unopened=%s" % (kind, m, k, n, unopened), flush=True)
+        t = (n if kind == "somm" else k) // bs
+        idx = torch.arange(t, dtype=torch.int32, device="cuda")
+        e, a, c, b, w = draw(m, k), draw(m, k), draw(m, n), draw(k, n), [draw(k, n) for _ in range(1 + unopened)]
+        z = torch.empty_like(c)
+        call = getattr(ctx, "%s_share%s" % (kind, "_unopened" if unopened else ""))
+        return places(lambda: call(1, bs, idx, None, t, e, *w, a, b, c, out=z), "ring_skinny_kernel<")
+
+    grid, most = plan(1 << 15, 256, 32)                       # two tiles of columns
+    rounds = (3 if unopened else 2) if m == 2 else 1
+    assert grid == rounds * most * units, (grid, most)
+    grid, most = plan(1 << 14, 128 if kind == "simm" else 127, 1)
+    assert grid == (7 if m == 2 else 6) * units and most >= grid // units, (grid, most)
+    if not unopened and m > 2 and (m != 6 or kind == "simm"):
+        grid, most = plan(512 * 40, 128 * units // 8, 32)     # thirty-two tiles on 256 units
+        tiles = units // 8
+        assert 14 * units <= grid <= 16 * units and grid % tiles == 0, (grid, most)
