@@ -8,12 +8,14 @@ exception is raised.
 
 The calls a layer makes over and over go through the native module ``_host`` (csrc/host.cpp), which makes the
 same checks on tensors in one call and declines (None) whatever is not plain; the methods below then take their own way,
-and the messages of what they refuse come from there.
+and the messages of what they refuse come from there.  Where the module is missing, or was built for another Python or
+torch, load_library() warns and every call takes that way.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional
 
 import torch
@@ -49,14 +51,12 @@ class CometError(RuntimeError):
 
 def load_library() -> ctypes.CDLL:
     """dlopen the in-tree library (build it first with ``paper_2505_07239_amd.build``)."""
-    global _lib
+    global _lib, _Host
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
         raise FileNotFoundError(
             "%s not found: run `python -m paper_2505_07239_amd.build` (needs hipcc)" % LIB_PATH)
-    if not os.path.exists(os.path.join(_HERE, "_host.so")):
-        raise FileNotFoundError("_host.so not found beside the library: run `python -m paper_2505_07239_amd.build` (needs g++)")
     lib = ctypes.CDLL(LIB_PATH)
     vp, i32, i64, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t
     lib.comet_create.argtypes = [ctypes.POINTER(vp), i32]
@@ -98,10 +98,36 @@ def load_library() -> ctypes.CDLL:
     lib.comet_set_tuning.argtypes = [vp, i32, i32]
     lib.comet_timing_begin.argtypes = [vp, i32]
     lib.comet_timing_end.argtypes = [vp, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int)]
-    from . import _host
-    _host.bind({name: ctypes.cast(getattr(lib, name), vp).value for name in EXPORTS}, WeightPlanes)
+    try:
+        from ._host import Host, bind
+    except ImportError as err:
+        warnings.warn("the native part of the binding cannot be imported (%s): calls take two to five microseconds more of the "
+                      "host's time each.  Run `python -m paper_2505_07239_amd.build` with this Python and torch (needs g++)" % err,
+                      RuntimeWarning, stacklevel=2)
+        _Host = _NoHost
+    else:
+        bind({name: ctypes.cast(getattr(lib, name), vp).value for name in EXPORTS}, WeightPlanes)
+        _Host = Host
     _lib = lib
     return lib
+
+
+class _NoHost:
+    """In the place of the native part where it is missing or was built for another Python or torch: declines every call."""
+
+    def __init__(self, ctx, device):
+        pass
+
+    def close(self):
+        pass
+
+    def _decline(self, *args):
+        return None
+
+    elementwise = gather = open_planes = compact = share = group = _decline
+
+
+_Host = None                       # set by load_library()
 
 
 def workspace_bytes(op: int, m: int, k: int, n: int, bs: int) -> int:
@@ -194,8 +220,7 @@ class Context:
             raise CometError(rc, "comet_create failed (is device %d an MI355X?)" % device)
         self.h = h
         self._ws = None
-        from . import _host
-        self._host = _host.Host(h.value, device)
+        self._host = _Host(h.value, device)
 
     def close(self):
         if getattr(self, "_host", None):

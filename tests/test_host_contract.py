@@ -47,6 +47,23 @@ def test_missing_library_raises(monkeypatch, tmp_path):
         binding.load_library()
 
 
+def test_library_loads_without_the_native_part_of_the_binding(monkeypatch):
+    """It saves host time only: where it is missing, or does not fit this Python or torch, the binding says so and goes its
+    own way through every call."""
+    import paper_2505_07239_amd.binding as binding
+    if not os.path.exists(binding.LIB_PATH):
+        pytest.skip("library not built")
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_Host", None)
+    monkeypatch.setitem(sys.modules, "paper_2505_07239_amd._host", None)         # (an import of it raises ImportError)
+    with pytest.warns(RuntimeWarning, match="native part"):
+        lib = binding.load_library()
+    assert lib.comet_version and binding.workspace_bytes(binding.OP_SOMM, 8, 64, 64, 8) > 0
+    host = binding._Host(0, 0)
+    assert [getattr(host, call)(1, 2) for call in ("elementwise", "gather", "open_planes", "compact", "share", "group")] == [None] * 6
+    host.close()
+
+
 def test_null_context_is_rejected_without_touching_a_device():
     lib_path = os.path.join(ROOT, "paper_2505_07239_amd", "libcomet_ring.so")
     if not os.path.exists(lib_path):
