@@ -28,13 +28,22 @@ FLAGS = ["-O3", "-std=c++20", "--offload-arch=gfx950", "-fPIC", "-fvisibility=de
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 
+def hipcc() -> str:
+    return os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+def rocm() -> str:
+    """The ROCm installation whose headers torch's include: ROCM_PATH, or the one that hipcc() belongs to."""
+    return os.environ.get("ROCM_PATH") or os.path.dirname(os.path.dirname(hipcc()))
+
+
 def host_command():
     """The command that builds ``_host.so``: the CPython and torch of the interpreter that runs this."""
     import sysconfig
     import torch
     base = os.path.dirname(torch.__file__)
     include = [os.path.join(base, "include"), os.path.join(base, "include", "torch", "csrc", "api", "include"),
-               sysconfig.get_paths()["include"], "/opt/rocm/include", os.path.join(ROOT, "include")]
+               sysconfig.get_paths()["include"], os.path.join(rocm(), "include"), os.path.join(ROOT, "include")]
     return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
              "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1"] + ["-I" + i for i in include] +
             [os.path.join(CSRC, "host.cpp"), "-o", HOST, "-L" + os.path.join(base, "lib"),
@@ -45,7 +54,6 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
     """Compiles every translation unit and links the library.  ``incremental``: skip a unit whose
     object file is newer than its source and every header (development convenience; the default
     compiles everything)."""
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     build_dir = os.path.join(HERE, "_build")
     os.makedirs(build_dir, exist_ok=True)
     headers = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")]
@@ -57,7 +65,7 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
         if incremental and os.path.exists(obj) and \
                 os.path.getmtime(obj) > max(newest_header, os.path.getmtime(os.path.join(CSRC, src))):
             return obj
-        cmd = [hipcc] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc()] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         res = subprocess.run(cmd, capture_output=True, text=True)
@@ -81,11 +89,11 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=jobs) as pool:
         host = pool.submit(compile_host)
         objs = list(pool.map(compile_one, SOURCES))
-        host.result()
-    cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
+    cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("link failed:\n" + res.stderr)
+    host.result()              # (behind the link: the library works without it)
     return LIB
 
 

@@ -64,6 +64,17 @@ def test_library_loads_without_the_native_part_of_the_binding(monkeypatch):
     host.close()
 
 
+def test_host_part_is_built_against_the_same_rocm(monkeypatch):
+    from paper_2505_07239_amd import build
+    monkeypatch.delenv("ROCM_PATH", raising=False)
+    monkeypatch.delenv("HIPCC", raising=False)
+    assert "-I/opt/rocm/include" in build.host_command()
+    monkeypatch.setenv("HIPCC", "/usr/local/rocm-x/bin/hipcc")
+    assert "-I/usr/local/rocm-x/include" in build.host_command()
+    monkeypatch.setenv("ROCM_PATH", "/usr/local/rocm-y")
+    assert "-I/usr/local/rocm-y/include" in build.host_command() and build.hipcc() == "/usr/local/rocm-x/bin/hipcc"
+
+
 def test_null_context_is_rejected_without_touching_a_device():
     lib_path = os.path.join(ROOT, "paper_2505_07239_amd", "libcomet_ring.so")
     if not os.path.exists(lib_path):
