@@ -355,12 +355,13 @@ def test_somm_result_blocks_spare_capacity_and_compact_triples(ctx, m):
     _somm_blocks_case(ctx, 450 + m, m, 48, 14, 16, 3, 2, spare_rows=5, spare_blocks=2, b_full=False)
 
 
-def test_somm_result_blocks_matrix_path_for_few_rows(ctx):
+@pytest.mark.parametrize("m", [6, 12])
+def test_somm_result_blocks_matrix_path_for_few_rows(ctx, m):
     """m <= 8 with the vector-ALU path switched off: the matrix-core kernel's 32-row tile."""
     import paper_2505_07239_amd as comet
     ctx.set_tuning(comet.TUNE_SKINNY, 1)
     try:
-        _somm_blocks_case(ctx, 470, 12, 64, 18, 16, 3, 2)
+        _somm_blocks_case(ctx, 470, m, 64, 18, 16, 3, 2)
     finally:
         ctx.set_tuning(comet.TUNE_SKINNY, 0)
 

@@ -149,21 +149,49 @@ def test_share_group_one_launch(ctx, kind, m, k, n, bs, kept, spare, parties, gr
         ctx.set_tuning(comet.TUNE_GEMM_GRID, 0)
 
 
-@pytest.mark.parametrize("single", [False, True])
+@pytest.mark.parametrize("grid", [4, 8])
 @pytest.mark.parametrize("kept,spare", [((0, 1, 4, 5), 0), ((0, 4, 5), 1), ((1, 5), 2), ((3,), 3), ((), 4)])
-def test_owned_tiles_follow_the_device_side_block_count(ctx, kept, spare, single):
+def test_owned_tiles_follow_the_device_side_block_count(ctx, kept, spare, grid):
     """A launch planned for owned tiles (capacity of four blocks: 2 x 2 tiles per product on a grid
     that divides their number) with fewer blocks on the device: a ragged last tile still owned,
     a tile count the grid no longer divides (shared tiles after all, and the packing kernel has to
-    initialise Z after all), and no block at all.  Weight planes (single and grouped calls)."""
+    initialise Z after all), and no block at all.  Grouped calls on weight planes."""
     import paper_2505_07239_amd as comet
-    say("owned tiles, kept=%s capacity=%d single=%s" % (kept, len(kept) + spare, single))
+    say("owned tiles, kept=%s capacity=%d grid=%d" % (kept, len(kept) + spare, grid))
     ctx.set_tuning(comet.TUNE_GROUP, 1)
-    ctx.set_tuning(comet.TUNE_GEMM_GRID, 4)
+    ctx.set_tuning(comet.TUNE_GEMM_GRID, grid)
     try:
-        _run_group(ctx, "somm", 256, 64, 8 * 32, 32, kept, spare, (0, 1), seed=980, single=single)
+        _run_group(ctx, "somm", 256, 64, 8 * 32, 32, kept, spare, (0, 1), seed=980,
+                   names=["xpack_group_kernel", "ring_planes_group_kernel<2, 2, 4, 2,"])
     finally:
         ctx.set_tuning(comet.TUNE_GROUP, 0)
+        ctx.set_tuning(comet.TUNE_GEMM_GRID, 0)
+
+
+# Single calls, planned as owned by their capacity.  Planes, 128 x 64 tiles: 2 x 33 of them on 22 and 33 workgroups, so that 66, 43
+# and 44 blocks of 32 keep the tiles owned on 22 (66 and 44 tiles) and 64 and 11 blocks do not.  Words, 64 x 64 tiles: 4 x 2 on 4
+# and 8 workgroups, four, three and two blocks owned on 4, four and three on 8.
+@pytest.mark.parametrize("kind", ["somm", "simm"])
+@pytest.mark.parametrize("planes,cap,grid", [(True, 66, 22), (True, 66, 33), (False, 4, 4), (False, 4, 8)])
+def test_single_calls_owned_by_capacity(ctx, kind, planes, cap, grid):
+    import paper_2505_07239_amd as comet
+    tiles = lambda blocks: (2 if planes else 4) * ((blocks * 32 + 63) // 64)
+    assert tiles(cap) % grid == 0
+    ctx.set_tuning(comet.TUNE_GEMM_TILE, 0 if planes else 2)
+    ctx.set_tuning(comet.TUNE_GEMM_GRID, grid)
+    try:
+        for n_kept in (66, 64, 44, 43, 11, 0) if planes else (4, 3, 2, 1, 0):
+            if kind == "simm" and planes:
+                n_kept = n_kept // 11                          # (the count cuts the contraction, the tiles are those of n)
+            spare = (6 if kind == "simm" and planes else cap) - n_kept
+            say("%s planes=%s grid=%d: %d blocks of %d" % (kind, planes, grid, n_kept, n_kept + spare))
+            kept = tuple(range(1, 2 * n_kept, 2))
+            dims = (256, 64, 2 * cap * 32) if kind == "somm" else (256, 2 * (n_kept + spare) * 32, cap * 32)
+            kernel = "ring_planes_kernel<2, 2, 4, 2," if planes else "ring_words_kernel<"
+            _run_group(ctx, kind, *dims, 32, kept, spare, (0, 1), planes=planes, seed=985, single=True,
+                       names=["xpack_kernel", kernel] * 2)
+    finally:
+        ctx.set_tuning(comet.TUNE_GEMM_TILE, 0)
         ctx.set_tuning(comet.TUNE_GEMM_GRID, 0)
 
 
@@ -176,7 +204,9 @@ def test_share_group_automatic_and_switched_off(ctx, kind, mode):
     ctx.set_tuning(comet.TUNE_GROUP, mode)
     try:
         dims = (200, 96, 16 * 32) if kind == "somm" else (200, 16 * 32, 96)
-        _run_group(ctx, kind, *dims, 32, (0, 2, 3, 9), 1, (0, 1, 1), seed=950)
+        _run_group(ctx, kind, *dims, 32, (0, 2, 3, 9), 1, (0, 1, 1), seed=950,
+                   names=["xpack_group_kernel", "ring_fewrow_group_kernel"] if mode == 0 else
+                   ["ring_direct_kernel"] * 3 if kind == "somm" else ["xpack_kernel", "ring_fewrow_kernel"] * 3)
     finally:
         ctx.set_tuning(comet.TUNE_GROUP, 0)
 

@@ -76,13 +76,21 @@ def check(ctx, kind, m, other, bs, kept, fmt, full, party=1, seed=900, kernel=No
 
 
 # Contraction of one half in words (steps of 32, stacked and taken in pairs): one step (the only pair
-# takes one step of each half), odd and even step counts.  Few tiles, so every m takes the 64 x 64 tile.
+# takes one step of each half), odd and even step counts.  The 64 x 64 tile (forced: products this small take the few-row
+# and the one-launch kernel), and whatever the size takes.
+@pytest.mark.parametrize("tile", [0, 2])
 @pytest.mark.parametrize("m", [33, 64, 65, 128, 129])
 @pytest.mark.parametrize("k", [1, 31, 33, 64, 95, 160])
-def test_planes_tiles_and_step_pairs(ctx, m, k):
-    check(ctx, "somm", m, k, 16, (0, 2, 3, 5, 6), "planes", True)
-    if k >= 16:
-        check(ctx, "simm", m, 65, 16, tuple(range(0, 2 * ((k + 15) // 16), 2)), "planes", True)
+def test_planes_tiles_and_step_pairs(ctx, m, k, tile):
+    import paper_2505_07239_amd as comet
+    kernel = "ring_planes_kernel<2, 2, 2, 2," if tile else "ring_direct_kernel<" if k <= 100 else "ring_fewrow_kernel<"
+    ctx.set_tuning(comet.TUNE_GEMM_TILE, tile)
+    try:
+        check(ctx, "somm", m, k, 16, (0, 2, 3, 5, 6), "planes", True, kernel=kernel)
+        if k >= 16:
+            check(ctx, "simm", m, 65, 16, tuple(range(0, 2 * ((k + 15) // 16), 2)), "planes", True, kernel=kernel)
+    finally:
+        ctx.set_tuning(comet.TUNE_GEMM_TILE, 0)
 
 
 @pytest.mark.parametrize("m,n", [(33, 64), (128, 64)])
@@ -91,17 +99,17 @@ def test_planes_long_contraction(ctx, m, n):
     import paper_2505_07239_amd as comet
     ctx.set_tuning(comet.TUNE_GEMM_GRID, 1)
     try:
-        check(ctx, "somm", m, 513 * 32, n, (0,), "planes", True)
+        check(ctx, "somm", m, 513 * 32, n, (0,), "planes", True, kernel="ring_planes_kernel<2, 2, 2, 2,")
     finally:
         ctx.set_tuning(comet.TUNE_GEMM_GRID, 0)
 
 
-def check_columns(ctx, kind, m, k, n, fmt, grid=0, seed=920):
+def check_columns(ctx, kind, m, k, n, fmt, grid=0, seed=920, kernel=None, bs=16):
     """One share call too large for the oracle as a whole: the first and last column of every 64, compared
-    in full.  bs = 16; every second block of the indexed axis (n of SOMM, k of SIMM) is kept."""
+    in full.  Every second block of the indexed axis (n of SOMM, k of SIMM) is kept."""
     import paper_2505_07239_amd as comet
-    print("[gpu-kernels] columns %s m=%d k=%d n=%d %s grid=%d" % (kind, m, k, n, fmt, grid), flush=True)
-    bs, t = 16, (n if kind == "somm" else k) // 16
+    print("[gpu-kernels] columns %s m=%d k=%d n=%d bs=%d %s grid=%d" % (kind, m, k, n, bs, fmt, grid), flush=True)
+    t = (n if kind == "somm" else k) // bs
     idx = np.arange(0, 2 * t, 2, dtype=np.int32)
     e, c = u64(seed, 1, m, k), u64(seed, 5, m, n)
     f = torch.randint(-2 ** 63, 2 ** 63 - 1, (k, n), dtype=torch.int64, device="cuda")
@@ -118,13 +126,16 @@ def check_columns(ctx, kind, m, k, n, fmt, grid=0, seed=920):
     want = co.beaver_share(1, e, down(f[:, cols_d]), a_sel, b_sel, np.ascontiguousarray(c[:, cols]))
     if fmt == "planes":
         f, b = ctx.open_weight_planes(f), ctx.open_weight_planes(b)
+    gi, e, a, c = torch.from_numpy(idx).cuda(), up(e), up(a), up(c)
+    call = lambda: (ctx.somm_share if kind == "somm" else ctx.simm_share)(1, bs, gi, None, t, e, f, a, b, c)
     ctx.set_tuning(comet.TUNE_GEMM_GRID, grid)
     try:
-        call = ctx.somm_share if kind == "somm" else ctx.simm_share
-        z = call(1, bs, torch.from_numpy(idx).cuda(), None, t, up(e), f, up(a), b, up(c))
+        z = call()
+        ran = kernels(call) if kernel else []
     finally:
         ctx.set_tuning(comet.TUNE_GEMM_GRID, 0)
     assert np.array_equal(down(z[:, cols_d]), want)
+    assert not kernel or len([name for name in ran if name.startswith(kernel)]) == 1, ran
 
 
 # The 128 x 64 tile of a single call (more than 32 tiles, rows not ragged): shared tiles; and owned ones
@@ -134,18 +145,27 @@ def check_columns(ctx, kind, m, k, n, fmt, grid=0, seed=920):
                                              ("somm", 128, 33, 2112, 11), ("simm", 128, 48, 2112, 11),
                                              ("somm", 250, 129 * 32 + 5, 2112, 33), ("simm", 250, 129 * 32 + 16, 2112, 33)])
 def test_planes_128x64_single_calls(ctx, kind, m, k, n, grid):
-    check_columns(ctx, kind, m, k, n, "planes", grid)
+    check_columns(ctx, kind, m, k, n, "planes", grid, kernel="ring_planes_kernel<2, 2, 4, 2,")
 
 
 # The choice between 64 x 64 and 64 x 128: below and from 32 pairs per compute unit on (5 x 15 tiles), a multiple of 64
 # tiles below and from 256 pairs on, a single row tile.
-@pytest.mark.parametrize("kind,m,k,n", [("somm", 320, 3488, 960), ("somm", 320, 3520, 960), ("simm", 300, 3520, 912),
-                                        ("somm", 192, 1664, 4096), ("somm", 192, 10928, 4096), ("simm", 64, 4096, 2560)])
-def test_planes_narrow_tile_choice(ctx, kind, m, k, n):
-    check_columns(ctx, kind, m, k, n, "planes")
+@pytest.mark.parametrize("kind,m,k,n,wide", [("somm", 320, 3488, 960, False), ("somm", 320, 3520, 960, True), ("simm", 300, 3520, 912, True),
+                                             ("somm", 192, 1664, 4096, False), ("somm", 192, 10928, 4096, True),
+                                             ("simm", 64, 4096, 2560, False)])
+def test_planes_narrow_tile_choice(ctx, kind, m, k, n, wide):
+    check_columns(ctx, kind, m, k, n, "planes", kernel="ring_planes_kernel<1, 4, 4, 2," if wide else "ring_planes_kernel<2, 2, 2, 2,")
 
 
-# Weight words beyond 320 MB, read past the caches up to 128 rows and from 193 to 768.
+# The 32 x 256 tile on words where it is taken without being asked for (more than sixteen units of the few-row kernel per
+# compute unit), below 320 MB: rows of B_i gathered by blocks of a power of two, of another length, and column gathers.
+@pytest.mark.parametrize("kind,m,k,n,bs", [("simm", 16, 4096, 2560, 32), ("simm", 32, 4095, 2500, 21), ("simm", 9, 4096, 2600, 16),
+                                           ("somm", 32, 4001, 2496, 32), ("somm", 16, 4100, 2499, 21)])
+def test_words_32x256_tile(ctx, kind, m, k, n, bs):
+    check_columns(ctx, kind, m, k, n, "words", kernel="ring_gemm_kernel<1, 4, 1, 2,", bs=bs)
+
+
+# Weight words beyond 320 MB, read past the caches up to 64 rows.
 @pytest.mark.parametrize("kind", ["somm", "simm"])
 @pytest.mark.parametrize("m", [9, 33, 64, 128, 129, 192, 193, 300, 768, 769])
 def test_words_beyond_the_cache(ctx, kind, m):
@@ -186,7 +206,7 @@ def masked_mask(m, nb, per_block, seed=950):
     return mask
 
 
-def check_masked(ctx, m, nb, bs, n, fmt, per_block, full=True, replays=0):
+def check_masked(ctx, m, nb, bs, n, fmt, per_block, full=True, replays=0, kernel=None):
     print("[gpu-kernels] masked m=%d nb=%d bs=%d n=%d %s full=%s" % (m, nb, bs, n, fmt, full), flush=True)
     k, seed = nb * bs, 940
     e, a, f, b, c = u64(seed, 1, m, k), u64(seed, 2, m, k), u64(seed, 3, k, n), u64(seed, 4, k, n), u64(seed, 5, m, n)
@@ -208,6 +228,9 @@ def check_masked(ctx, m, nb, bs, n, fmt, per_block, full=True, replays=0):
     want = inputs(0)
     call()
     assert np.array_equal(down(z), want)
+    if kernel:
+        ran = kernels(call)
+        assert len([name for name in ran if name.startswith(kernel)]) == 1, ran
     if not replays:
         return
     graph = torch.cuda.CUDAGraph()
@@ -239,6 +262,21 @@ def test_masked_planes(ctx, m, nb, bs, n, full):
 @pytest.mark.parametrize("fmt", ["words", "planes"])
 def test_masked_step_list_chunks(ctx, m, nb, bs, fmt):
     check_masked(ctx, m, nb, bs, 40, fmt, 1, fmt == "words" or bs % 16 == 0)
+
+
+# One workgroup: runs of more than 128 listed pairs (256 steps) in both kernels of 64 rows on words, rows of B_i found by
+# sixteen, one by one and as they come; one row tile and two with different lists.
+@pytest.mark.parametrize("m,nb,bs,full", [(40, 560, 16, True), (70, 560, 16, True), (40, 930, 9, True), (70, 930, 9, False)])
+@pytest.mark.parametrize("tile", [2, 3])
+def test_masked_words_long_runs(ctx, m, nb, bs, full, tile):
+    import paper_2505_07239_amd as comet
+    ctx.set_tuning(comet.TUNE_GEMM_GRID, 1)
+    ctx.set_tuning(comet.TUNE_GEMM_TILE, tile)
+    try:
+        check_masked(ctx, m, nb, bs, 70, "words", 2, full, kernel="ring_words_kernel<" if tile == 2 else "ring_gemm_kernel<2, 2, 1, 1,")
+    finally:
+        ctx.set_tuning(comet.TUNE_GEMM_GRID, 0)
+        ctx.set_tuning(comet.TUNE_GEMM_TILE, 0)
 
 
 # The counter of finished workgroups starts from zero in every call, replayed or not.

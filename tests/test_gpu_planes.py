@@ -168,8 +168,8 @@ def _run(ctx, cs, party, b_full):
         assert np.array_equal(down(z), cs["want"][party])
 
 
-# (m, other dimension, bs, kept blocks, spare capacity): the few-row kernel (m <= 32) and the 64 x 64 tile (few
-# tiles; the other shapes are in test_gpu_kernels.py), ragged tails, one and several blocks per contraction step
+# (m, other dimension, bs, kept blocks, spare capacity): the one-launch, the few-row and, forced, the 64 x 64 tile (the
+# other shapes are in test_gpu_kernels.py), ragged tails, one and several blocks per contraction step
 SHAPES = [
     (5, 96, 8, (0, 3, 4, 9), 0), (20, 130, 16, (1, 2, 6), 1), (32, 64, 32, (0, 2), 0),
     (50, 200, 16, (0, 5, 6, 7, 11), 2), (64, 96, 48, (1, 3), 0),
@@ -178,9 +178,17 @@ SHAPES = [
 ]
 
 
+@pytest.fixture(params=[0, 2])
+def tile(ctx, request):
+    import paper_2505_07239_amd as comet
+    ctx.set_tuning(comet.TUNE_GEMM_TILE, request.param)
+    yield request.param
+    ctx.set_tuning(comet.TUNE_GEMM_TILE, 0)
+
+
 @pytest.mark.parametrize("m,other,bs,kept,spare", SHAPES)
 @pytest.mark.parametrize("b_full", [True, False])
-def test_somm_share_with_weight_planes(ctx, m, other, bs, kept, spare, b_full):
+def test_somm_share_with_weight_planes(ctx, tile, m, other, bs, kept, spare, b_full):
     nb = max(kept) + 2
     cs = _case(700 + m, "somm", m, other, nb * bs, bs, kept, spare)
     for party in (0, 1):
@@ -190,7 +198,7 @@ def test_somm_share_with_weight_planes(ctx, m, other, bs, kept, spare, b_full):
 
 @pytest.mark.parametrize("m,other,bs,kept,spare", SHAPES)
 @pytest.mark.parametrize("b_full", [True, False])
-def test_simm_share_with_weight_planes(ctx, m, other, bs, kept, spare, b_full):
+def test_simm_share_with_weight_planes(ctx, tile, m, other, bs, kept, spare, b_full):
     if b_full and bs % 16:
         pytest.skip("planes of a full-size B_i are gathered in units of sixteen rows")
     nb = max(kept) + 2
@@ -204,7 +212,7 @@ def test_simm_share_with_weight_planes(ctx, m, other, bs, kept, spare, b_full):
 # its own fragments: several column groups of 128 with a ragged last one, contraction lengths that
 # are no multiple of 32, blocks of 16 / 48 / 64, every row count that matters for the 32-row
 # matrix-instruction tile; grids of 1, 3 and 7 workgroups make the runs of steps cross from one
-# column group into the next.
+# column group into the next (without a forced grid the shortest contractions take the one-launch kernel).
 FEW_SHAPES = [
     (1, 96, 16, (0, 3, 4, 9, 10, 11, 12, 20, 21), 0), (8, 130, 64, (1, 2, 6), 1), (9, 70, 48, (0, 2, 3, 5), 0),
     (17, 200, 32, tuple(range(0, 22, 2)), 2), (31, 33, 16, tuple(range(19)), 0), (32, 515, 64, (0, 1, 4, 5, 6), 0),

@@ -129,6 +129,53 @@ def test_work_split(ctx, fmt, m, k, n, grid):
             check(ctx, "simm", fmt, m, n // 4, 16, k // 16, TUNE_GEMM_TILE=tile)
 
 
+# The same with fewer blocks on the device than the capacity the launch was planned for: even shares with and without teams
+# of row tiles, slices, owned tiles (128 x 256 on 8 workgroups), down to one block and none.
+@pytest.mark.parametrize("fmt", ["words", "planes", "neuron_major"])
+@pytest.mark.parametrize("m,other,cap,grid", [(64, 300, 288, 0), (128, 300, 144, 0), (250, 260, 72, 0), (150, 300, 60, 7), (250, 260, 72, 12),
+                                              (128, 100, 16, 8), (64, 200, 20, 0)])
+def test_work_split_device_counts(ctx, fmt, m, other, cap, grid):
+    import paper_2505_07239_amd as comet
+    for kind in ("somm", "simm") if fmt != "neuron_major" else ("somm",):
+        bs, seed = 16, 945
+        for t in sorted({cap - 1, cap * 2 // 3, cap // 3, 1, 0}, reverse=True):
+            print("[gpu-words] %s %s m=%d other=%d blocks=%d of %d grid=%d" % (kind, fmt, m, other, t, cap, grid), flush=True)
+            ld, nf = cap * bs, 2 * cap * bs
+            idx = np.arange(0, 2 * cap, 2, dtype=np.int32)
+            on, sel = t * bs, idx[:t]
+            if kind == "somm":
+                e, a, f, b, c = u64(seed, 1, m, other), u64(seed, 2, m, other), u64(seed, 3, other, ld), u64(seed, 4, other, nf), \
+                    u64(seed, 5, m, ld)
+                want = co.beaver_share(1, e, f[:, :on], a, co.index_cols(b, sel, bs), c[:, :on]) if t else None
+            else:
+                e, a, f, b, c = u64(seed, 1, m, ld), u64(seed, 2, m, nf), u64(seed, 3, ld, other), u64(seed, 4, nf, other), \
+                    u64(seed, 5, m, other)
+                want = co.beaver_share(1, e[:, :on], f[:on], co.index_cols(a, sel, bs), co.index_rows(b, sel, bs), c) if t else c
+            turn = (lambda w: up(w.T)) if fmt == "neuron_major" else up
+            f_d, b_d = turn(f), turn(b)
+            if fmt == "planes":
+                f_d, b_d = ctx.open_weight_planes(f_d), ctx.open_weight_planes(b_d)
+            gi, n_dev, e_d, a_d, c_d = torch.from_numpy(idx).cuda(), torch.tensor([t], dtype=torch.int32, device="cuda"), up(e), up(a), up(c)
+            for tile in (2, 3) if fmt != "planes" else (2,):
+                z = torch.full(c.shape, 77, dtype=torch.int64, device="cuda")
+                ctx.set_tuning(comet.TUNE_GEMM_TILE, tile)
+                ctx.set_tuning(comet.TUNE_GEMM_GRID, grid)
+                try:
+                    if kind == "somm":
+                        ctx.somm_share(1, bs, gi, n_dev, cap, e_d, f_d, a_d, b_d, c_d, neuron_major=fmt == "neuron_major", out=z)
+                    else:
+                        ctx.simm_share(1, bs, gi, n_dev, cap, e_d, f_d, a_d, b_d, c_d, out=z)
+                    torch.cuda.synchronize()
+                finally:
+                    ctx.set_tuning(comet.TUNE_GEMM_TILE, 0)
+                    ctx.set_tuning(comet.TUNE_GEMM_GRID, 0)
+                got = down(z)
+                if kind == "simm":
+                    assert np.array_equal(got, want), tile
+                else:
+                    assert (not t or np.array_equal(got[:, :on], want)) and np.all(got[:, on:] == 77), tile
+
+
 STAGED, WORDS = "ring_gemm_kernel<2, 2, 1, 1,", "ring_words_kernel<"
 
 
