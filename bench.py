@@ -304,7 +304,14 @@ def run_timed(ctx, layer, steps, warmup, run_step=None):
     gemm_ms, n_timed = ctx.timing_end()
     ctx.set_tuning(comet.TUNE_TIMING_STRIDE, 0)
     return {"ms_per_step": (t1 - t0) * 1e3 / steps, "gemm_ms": gemm_ms, "n_timed": n_timed,
-            "launches_per_step": per_step, "timing_stride": stride}
+            "launches_per_step": per_step, "timing_stride": stride,
+            "kernels": share_kernels(layer.step if run_step == layer.step_overlapped else run_step)}
+
+
+def share_kernels(run_step):
+    """The share kernels that a step launches, by name, in the order of their first launch."""
+    from workloads import launches
+    return list(dict.fromkeys(name.split("<")[0] for name in launches.kernels(run_step) if name.startswith("ring_")))
 
 
 def roofline_of(layer, wname, timing, skinny_forced, probes):
@@ -323,13 +330,16 @@ def roofline_of(layer, wname, timing, skinny_forced, probes):
     common = {"traffic": traffic, "traffic_source": source, "avg_launch_ms": avg_ms, "launches_timed": n_timed,
               "launches_per_step": per_step, "timing_stride": timing["timing_stride"],
               "ring_macs_per_launch": macs_per_launch, "gemm_share_of_step": share, "weight_operands": fmt}
+    kernel = "+".join(timing["kernels"])
+    # what they multiply with: 16 x 16 x 64, or 32 x 32 x 32 in the others
+    k64 = set(timing["kernels"]) <= {"ring_planes_kernel", "ring_planes_group_kernel", "ring_words_kernel"}
     if cfg.tokens <= 8 and not skinny_forced:
         # a few activation rows: the share calls take the vector-ALU kernel, bound by reading the
         # weight-side operands once per launch: B_i and F (kc x n words each), or B_i and the two
         # masked shares F is the sum of when the opening is folded into the kernel
         wbytes = macs_per_launch / cfg.tokens * 8.0 * (1.5 if layer.unopened else 1.0)
         ach = wbytes / (avg_ms * 1e-3) / 1e9
-        r = {"bound": "hbm", "kernel": "ring_skinny_kernel", "achieved": ach, "peak": PEAK_HBM_GBS,
+        r = {"bound": "hbm", "kernel": kernel, "achieved": ach, "peak": PEAK_HBM_GBS,
              "unit": "GB/s", "frac": ach / PEAK_HBM_GBS,
              "note": "algorithmic bytes: the weight-side operands of one launch, 8 bytes per word, read once: "
                      + ("B_i and the two masked shares [G]_0, [G]_1 whose sum F is (the opening is folded "
@@ -338,8 +348,7 @@ def roofline_of(layer, wname, timing, skinny_forced, probes):
             r["frac_of_measured_copy"] = ach / probes["copy_GBs"]
     else:
         ach = INT8_OPS_PER_RING_MAC * macs_per_launch / (avg_ms * 1e-3) / 1e12
-        r = {"bound": "mfma", "kernel": "ring_planes_group_kernel" if grouped else "ring_planes_kernel" if layer.planes else "ring_words_kernel",
-             "achieved": ach, "peak": PEAK_INT8_TOPS,
+        r = {"bound": "mfma", "kernel": kernel, "achieved": ach, "peak": PEAK_INT8_TOPS,
              "unit": "TOP/s", "frac": ach / PEAK_INT8_TOPS,
              "note": "algorithmic int8 ops: 36 digit products x 2 ops per ring MAC, two products per "
                      "party (2*m*k*n_act ring MACs per share product; a grouped launch computes "
@@ -347,7 +356,7 @@ def roofline_of(layer, wname, timing, skinny_forced, probes):
         if probes:
             r["frac_of_measured_mfma_issue"] = ach / probes["mfma_i8_issue_TOPs"]
             r["frac_of_measured_mfma_issue_random_operands"] = ach / probes[
-                "mfma_i8_issue_random_operands_16x16x64_TOPs" if layer.planes else "mfma_i8_issue_random_operands_TOPs"]
+                "mfma_i8_issue_random_operands_16x16x64_TOPs" if k64 else "mfma_i8_issue_random_operands_TOPs"]
     r.update(common)
     return r
 

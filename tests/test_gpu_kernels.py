@@ -11,8 +11,8 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 import oracle as co                                   # noqa: E402
-from kernel_names import kernels, places              # noqa: E402
 from workloads import rng                             # noqa: E402
+from workloads.launches import kernels, places        # noqa: E402
 
 
 @pytest.fixture(scope="module")
