@@ -31,7 +31,7 @@ struct GemmParams {
     int w_nt;       // weight words are read past the caches (see words_past_caches)
     // packed digit planes of [E | A']
     unsigned char* xp;
-    int mpad;       // rows of xp, multiple of 128
+    int mpad;       // rows of xp: a multiple of 128, or the 32 of the few-row kernel's only row tile
     int chunk;      // contraction units per scheduling slice fixed by the caller, or 0
     int ks_cap;     // contraction steps per half, ceil(kc_cap / 32)
     int xstep[2];   // first step of a half in xp: 0 and ks_cap, or (group call) where the member's half lies in the common planes
@@ -123,7 +123,7 @@ using GemmGroupKernel = void (*)(GemmGroup);
 
 // Matrix-core path whose wavefronts stream their weight fragments from memory into registers (plain products only: no
 // result blocks, no per-token row sets): up to COMET_FEWROW_MAX_ROWS activation rows on weight planes, and small
-// products (see small_product() in ring_gemm.hip).  Runs after the packing kernel (digit planes of
+// products (see takes_few_rows() in ring_gemm.hip).  Runs after the packing kernel (digit planes of
 // [E | A'] in p.xp, Z := C).
 static const int COMET_FEWROW_MAX_ROWS = 32;
 int comet_launch_fewrow(comet_ctx* ctx, const char* what, const GemmParams& p);

@@ -565,10 +565,13 @@ bool group_takes_few_rows(const comet_ctx* ctx, const GemmParams& p, int members
     return few_units(p, members) <= 20l * ctx->num_cu;
 }
 
-// The smallest products take one launch: up to 100 contraction words and a 32 x 32 tile per compute unit. 64 x 64 x 64 9.0
-// us packed, multiplied by the few-row kernel -> 7.9 us, 16 x 64 x 3072 8.3 -> 6.5, 256 x 64 x 1024 13.7 -> 8.9, 256 x
-// 100 x 64 11.0 -> 9.0, and 2.5 us less of the host's time; but 64 x 128 x 256 9.5 -> 10.5, 128 x 64 x 3072 (384 tiles)
-// 14.6 -> 15.7.
+// The smallest products take one launch: up to 100 contraction words and a 32 x 32 tile per compute unit, 2.5 us less of the
+// host's time.  On the GPU it is well ahead up to 64 words (few-row kernel with its packing / one launch, words: 64 x 64
+// outputs 8.3 / 7.9 us, 256 x 256 9.3 / 8.1, 33 x 3072 9.4 / 8.2) and about even from there to 100, ahead with many tiles,
+// behind with few (64 x 64 outputs, 96 words 8.7 / 9.3, 100 words 8.9 / 8.9, 104 words 8.9 / 9.0; 256 x 256 10.3 / 9.8,
+// 11.2 / 9.4, 11.3 / 9.5); beyond, up to the 128 words that the kernel holds, it falls behind (112 words 8.9 / 10.3, 128 words
+// 8.3 / 10.2; 256 x 256 11.5 / 10.5, 10.9 / 10.8): all eight wavefronts fetch words of 32 rows one by one by then.
+// More tiles than units: 128 x 64 x 3072 (384 tiles) 14.6 / 15.7.
 bool takes_direct(const comet_ctx* ctx, const GemmParams& p) {
     if (p.row_comp || p.tmask || ctx->gemm_tile >= 2 || ctx->gemm_chunk > 0 || ctx->gemm_grid > 0 || rows_to_tiles(ctx, p)) return false;
     const long tiles = (long)((p.m + 31) / 32) * ((p.n_cap + 31) / 32);

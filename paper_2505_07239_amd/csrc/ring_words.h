@@ -28,6 +28,9 @@
 // in a long run of them, and the planes kernel 172 and 220; without the digit split it is no faster.
 // Against those kernels, whole calls: 192 x 1664 x 4096 106 -> 91 us, 512 x 4096 x 1664 238 -> 212, 512 x 4096 x 11008
 // 1486 -> 1361, 64 x 11008 x 4096 235 -> 216; rows gathered in blocks that are no multiple of 16 (256 x 819 x 1001) 50 -> 39.
+// The multiplying wavefronts take every register they can have; what does not fit (20 bytes of scratch per lane with step
+// lists, 40 to 44 without) is stored and read back around a segment, in its set-up and its write-out: no scratch access lies
+// in the loops over the pairs, of either kind of wavefront, in any variant.
 // A pair is the least a workgroup can do; where a workgroup has one or two the 64 x 64 tile of ring_tile.h is ahead
 // (takes_staged_tile() in ring_gemm.hip).
 #pragma once
