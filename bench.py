@@ -49,18 +49,18 @@ ALL_CONFIGS = ["c1", "c2", "c3", "c4", "c5_d100", "c5_d050", "c5_d025", "c5_d010
 # the copy probe of known size in the same run.  The summaries, with the commands, are the
 # files named here under profiles/.  None until measured for that workload and operand format.
 GEMM_TRAFFIC = {
-    ("c2", "planes", "grouped"): (34605254, "profiles/bench_c2_kernel_trace_and_hbm_counters.md"),
-    ("c2", "planes", "single"): (13394338, "profiles/bench_c2_kernel_trace_and_hbm_counters.md"),
-    ("c3", "planes", "grouped"): (615195728, "profiles/bench_c3_kernel_trace_and_hbm_counters.md"),
-    ("c3", "planes", "single"): (198728434, "profiles/bench_c3_kernel_trace_and_hbm_counters.md"),
-    ("c4", "words", "single"): (1456336446, "profiles/bench_c4_kernel_trace_and_hbm_counters.md"),
-    ("c5_d100", "planes", "single"): (1550173485, "profiles/bench_c5_d100_kernel_trace_and_hbm_counters.md"),
-    ("c5_d050", "planes", "single"): (793542696, "profiles/bench_c5_d050_kernel_trace_and_hbm_counters.md"),
-    ("c5_d025", "planes", "single"): (397598246, "profiles/bench_c5_d025_kernel_trace_and_hbm_counters.md"),
-    ("c5_d010", "planes", "grouped"): (355121085, "profiles/bench_c5_d010_kernel_trace_and_hbm_counters.md"),
-    ("c5_d010", "planes", "single"): (179509076, "profiles/bench_c5_d010_kernel_trace_and_hbm_counters.md"),
-    ("c5_d005", "planes", "grouped"): (212522707, "profiles/bench_c5_d005_kernel_trace_and_hbm_counters.md"),
-    ("c5_d005", "planes", "single"): (108210023, "profiles/bench_c5_d005_kernel_trace_and_hbm_counters.md"),
+    ("c2", "planes", "grouped"): (29197025, "profiles/bench_c2_kernel_trace_and_hbm_counters.md"),
+    ("c2", "planes", "single"): (13402652, "profiles/bench_c2_kernel_trace_and_hbm_counters.md"),
+    ("c3", "planes", "grouped"): (614540265, "profiles/bench_c3_kernel_trace_and_hbm_counters.md"),
+    ("c3", "planes", "single"): (197943334, "profiles/bench_c3_kernel_trace_and_hbm_counters.md"),
+    ("c4", "words", "single"): (1428583490, "profiles/bench_c4_kernel_trace_and_hbm_counters.md"),
+    ("c5_d100", "planes", "single"): (1551190703, "profiles/bench_c5_d100_kernel_trace_and_hbm_counters.md"),
+    ("c5_d050", "planes", "single"): (794229038, "profiles/bench_c5_d050_kernel_trace_and_hbm_counters.md"),
+    ("c5_d025", "planes", "single"): (397958067, "profiles/bench_c5_d025_kernel_trace_and_hbm_counters.md"),
+    ("c5_d010", "planes", "grouped"): (355120250, "profiles/bench_c5_d010_kernel_trace_and_hbm_counters.md"),
+    ("c5_d010", "planes", "single"): (179868607, "profiles/bench_c5_d010_kernel_trace_and_hbm_counters.md"),
+    ("c5_d005", "planes", "grouped"): (212521575, "profiles/bench_c5_d005_kernel_trace_and_hbm_counters.md"),
+    ("c5_d005", "planes", "single"): (108569167, "profiles/bench_c5_d005_kernel_trace_and_hbm_counters.md"),
 }
 
 

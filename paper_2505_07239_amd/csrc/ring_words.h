@@ -23,9 +23,11 @@
 // the instruction stream of the matrix instructions, and the two share the SIMD's issue slots without
 // waiting for each other.  Kernels that do both in every wavefront (32x32x32, operands of both sides staged in LDS,
 // 64 x 64 and 128 x 64 tiles) take, for 64 rows, k = 4096, n = 11008 (722 MB of words), 220 us, of which 180
-// remained when every load hit the cache and 160 when eight of nine matrix instructions were left out.  What bounds this
-// one is power, as for the kernel on planes (ring_gemm_planes.h): 185 us for the same product from a cool chip, 245
-// in a long run of them, and the planes kernel 172 and 220; without the digit split it is no faster.
+// remained when every load hit the cache and 160 when eight of nine matrix instructions were left out.
+// What bounds this one, by the counters: with 512 rows the clock falls to 1.74 GHz (1.90 in the row product) at 66 % busy
+// matrix units, so power for the most part; with 64 rows the clock holds, the matrix units are busy half of the time, the
+// words come at 3.9 TB/s and a third of the wavefronts' cycles is waiting (193 us from a cool chip, 245 in a long run; the
+// planes kernel 172 and 220).  Without the digit split it is no faster.
 // Against those kernels, whole calls: 192 x 1664 x 4096 106 -> 91 us, 512 x 4096 x 1664 238 -> 212, 512 x 4096 x 11008
 // 1486 -> 1361, 64 x 11008 x 4096 235 -> 216; rows gathered in blocks that are no multiple of 16 (256 x 819 x 1001) 50 -> 39.
 // The multiplying wavefronts take every register they can have; what does not fit (20 bytes of scratch per lane with step
