@@ -176,16 +176,12 @@ def test_words_beyond_the_cache(ctx, kind, m):
 # The 32 x 128 tile on planes and the 32 x 256 tile on words, whatever the size, with the few-row kernels switched off:
 # remainders of the contraction and of the columns, rows of B_i as they come, gathered by blocks of a power of two and of
 # any other length, neuron-major weights.
-@pytest.mark.parametrize("kind", ["somm", "simm"])
+@pytest.mark.parametrize("kind,fmt,bs", [(kind, fmt, bs) for kind in ("somm", "simm") for fmt, bs in (
+    ("planes", 16), ("planes", 48), ("words", 32), ("words", 21), ("words", 8), ("words", 5))] + [("somm", "neuron_major", 16)])
 @pytest.mark.parametrize("m,other", [(1, 31), (9, 33), (31, 64), (32, 95), (32, 300)])
-@pytest.mark.parametrize("fmt,bs", [("planes", 16), ("planes", 48), ("words", 32), ("words", 21), ("words", 8), ("words", 5),
-                                    ("neuron_major", 16)])
 def test_32_row_tiles(ctx, kind, m, other, fmt, bs):
     import paper_2505_07239_amd as comet
-    if fmt == "neuron_major":
-        if kind == "simm":
-            pytest.skip("neuron-major weights belong to SOMM")
-        other += other % 2
+    other += fmt == "neuron_major" and other % 2
     kernel = "ring_planes_kernel<1, 4, 2, 2," if fmt == "planes" else "ring_gemm_kernel<1, 4, 1, 2,"
     ctx.set_tuning(comet.TUNE_SKINNY, 1)
     try:

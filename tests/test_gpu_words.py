@@ -84,24 +84,20 @@ def check(ctx, kind, fmt, m, other, bs, t, full=True, party=1, kernel=None, **tu
 
 # Contraction lengths at the edges of a step (32), a pair (64) and the one-launch path (100 words).  tile 0: the one-launch
 # path and the few-row kernel; 2 and 3: the tiles of 64 rows whatever the size, on words of both kernels.
-@pytest.mark.parametrize("fmt", ["words", "planes", "neuron_major"])
-@pytest.mark.parametrize("tile", [0, 2, 3])
+@pytest.mark.parametrize("fmt,tile", [(fmt, tile) for fmt in ("words", "planes", "neuron_major") for tile in (0, 2, 3)
+                                      if (fmt, tile) != ("planes", 3)])
 @pytest.mark.parametrize("m", [9, 32, 33, 64, 130])
 def test_small_somm(ctx, fmt, tile, m):
-    if fmt == "planes" and tile == 3:
-        pytest.skip("one tile of 64 rows on planes")
     for k in (1, 2, 31, 32, 33, 64, 65, 95, 97, 100, 101, 160, 193, 224):
         if fmt != "neuron_major" or k % 2 == 0:
             check(ctx, "somm", fmt, m, k, 5 if k % 3 == 0 and fmt == "words" else 16, 5, party=k & 1, TUNE_GEMM_TILE=tile)
 
 
 # Blocks of 7 neurons (rows looked up one by one), of 16 (sixteen at a time) and of 32; compact operands.
-@pytest.mark.parametrize("tile", [0, 2, 3])
 @pytest.mark.parametrize("m", [9, 32, 33, 64, 130])
-@pytest.mark.parametrize("fmt,bs", [("words", 7), ("words", 16), ("words", 32), ("planes", 16), ("planes", 48)])
+@pytest.mark.parametrize("fmt,bs,tile", [("words", bs, tile) for bs in (7, 16, 32) for tile in (0, 2, 3)] +
+                         [("planes", bs, tile) for bs in (16, 48) for tile in (0, 2)])
 def test_small_simm(ctx, fmt, bs, m, tile):
-    if fmt == "planes" and tile == 3:
-        pytest.skip("one tile of 64 rows on planes")
     for t in (1, 2, 3, 5, 6, 7, 14):
         check(ctx, "simm", fmt, m, 65 if t & 1 else 33, bs, t, party=t & 1, TUNE_GEMM_TILE=tile)
     check(ctx, "simm", fmt, m, 64, bs, 5, full=False, TUNE_GEMM_TILE=tile)
