@@ -103,7 +103,9 @@ struct Segment {
 // tile, when their number divides the grid, are walked side by side by as many consecutive workgroups: the weights of a
 // unit are fetched once for all of them.  What that saves is the traffic of workgroups that start anywhere in
 // the contraction (and the power it takes): planes, 256 x 4096 x 11008 662 -> 594 us, 512 x 4096 x 11008 1300 -> 1135,
-// 512 x 2560 x 3000 229 -> 200; but 77 x 4096 x 1664, a fifth of a tile per workgroup, 55 -> 59.
+// 512 x 2560 x 3000 229 -> 200; but 77 x 4096 x 1664, a fifth of a tile per workgroup, 55 -> 59.  With result blocks
+// the same where every tile is listed, one component: words, 512 x 4096 x 11008 1709 -> 1402, 256 rows 830 -> 723, planes
+// 256 x 4199 x 4800 307 -> 294.
 //
 // Either way, workgroups that run side by side sweep the same slice of the contraction at the same
 // time (the activation planes of that slice stay hot in L2) and each XCD ends up with whole
@@ -136,7 +138,8 @@ struct UnitWalk {
         }
         CH = p.chunk;
         if (!LISTED && !own && CH == 0 && 3l * tiles > G) {
-            const bool team = !p.row_comp && q.tiles_m > 1 && G % q.tiles_m == 0;
+            // (a list of all tiles is the plain order)
+            const bool team = tiles == q.tiles_m * q.tiles_n && q.tiles_m > 1 && G % q.tiles_m == 0;
             const int part = team ? b / q.tiles_m : b, parts = team ? G / q.tiles_m : G;
             if (team) {
                 team_tm = b % q.tiles_m;

@@ -366,6 +366,26 @@ def test_somm_result_blocks_matrix_path_for_few_rows(ctx, m):
         ctx.set_tuning(comet.TUNE_SKINNY, 0)
 
 
+# Even shares of the listed tiles, two to four row tiles of 64 (about half of the tokens use a block): one component, where
+# every tile is listed and the row tiles go side by side when they divide the workgroups; several, where they do not; both
+# kernels of words (2, 3) and both plane tiles; more tiles than workgroups and fewer.
+@pytest.mark.parametrize("planes,tile", [(False, 2), (False, 3), (True, 0), (True, 2)])
+@pytest.mark.parametrize("m,k,nb,bs,groups,per_tok", [(220, 97, 40, 16, 1, 4), (340, 64, 24, 32, 1, 3), (460, 130, 33, 16, 1, 3),
+                                                      (460, 97, 60, 16, 2, 4)])
+def test_somm_result_blocks_even_shares(ctx, m, k, nb, bs, groups, per_tok, planes, tile):
+    import paper_2505_07239_amd as comet
+    ctx.set_tuning(comet.TUNE_GEMM_TILE, tile)
+    try:
+        for grid in (1, 4, 6, 8, 12, 48):
+            say("somm blocks even shares m=%d k=%d groups=%d planes=%s tile=%d grid=%d" % (m, k, groups, planes, tile, grid))
+            ctx.set_tuning(comet.TUNE_GEMM_GRID, grid)
+            assert _somm_blocks_case(ctx, 480 + m, m, k, nb, bs, groups, per_tok, spare_rows=3, spare_blocks=1, b_full=False,
+                                     planes=planes) == groups
+    finally:
+        ctx.set_tuning(comet.TUNE_GEMM_GRID, 0)
+        ctx.set_tuning(comet.TUNE_GEMM_TILE, 0)
+
+
 # ---------------------------------------------------------------------------
 # MHA-shaped workload: head-granular sparsity (block = one attention head)
 # ---------------------------------------------------------------------------
